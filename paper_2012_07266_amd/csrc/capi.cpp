@@ -82,6 +82,10 @@ ArenaPlan plan_arena(const pm_params& p, const lens_params& l, size_t es) {
         a.nyq[j] = L.take(nm * nm * 2 * es);
     }
     a.halo = L.take((size_t)paint_halo_elems((int)nt, (int)es) * es);
+    // reverse pass: sorted-order cotangent scratch; together with the meshes
+    // before it, the scratch of a projection's image bins (lens_bins)
+    a.xbc = L.take(3 * n * es);
+    a.fbc = L.take(3 * n * es);
     a.tw_nm = L.take(nm * 2 * es);
     a.tw_hm = L.take(nm / 2 * 2 * es);
     a.twp_nm = L.take((nm / 2 + 1) * 2 * es);
@@ -93,10 +97,8 @@ ArenaPlan plan_arena(const pm_params& p, const lens_params& l, size_t es) {
     a.atab = L.take(2 * ATAB_N * es);
     a.dtab = L.take(2 * ATAB_N * es);
     a.pmax = L.take(256);
-    // reverse pass: sorted-order cotangent scratch, reductions, the noise of
-    // the last initial conditions, Omega_m derivative tables
-    a.xbc = L.take(3 * n * es);
-    a.fbc = L.take(3 * n * es);
+    // reverse pass: reductions, the noise of the last initial conditions,
+    // Omega_m derivative tables
     a.dots = L.take(64 * sizeof(double));
     a.fmax = L.take(256);
     a.noise = L.take(n * es);
@@ -332,6 +334,10 @@ template <class T> struct Sim final : SimBase {
     double tan_om = 0;       // its Omega_m component
     double cell = 0;  // mesh cell, Mpc/h
     int ntiles = 0;
+
+    // the counters of the image bins (at the end of fbc) are zero: a
+    // projection leaves them so, the derivative passes overwrite them
+    bool bins_clear = false;
 
     bool own_arena = true;  // false: the arena is the static scratch array
     // pm_run projects each shell on a second stream, beside the paint and the
@@ -609,7 +615,8 @@ template <class T> struct Sim final : SimBase {
 
     void fft_forward_grad(int n, const T* G, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
                           HaloMerge<T> hm = HaloMerge<T>(),
-                          const std::function<void()>& after_fwd = nullptr) {
+                          const std::function<void()>& after_fwd = nullptr,
+                          const std::function<void()>& after_inv = nullptr) {
         // Poisson: G(q) = 1 / (2 pi q Nm^2) computed in the kernel (G == NULL)
         const T gscale = (T)(1.0 / (2.0 * PI * (double)n * (double)n));
         { ProfScope ps(prof, "fft_r2c_axis2"); fft_r2c_rows<T>(n, mesh[0], nyq[0], twh, twp, st, hm); }
@@ -622,6 +629,7 @@ template <class T> struct Sim final : SimBase {
           fft_grad_axis0<T>(n, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw, G, gscale, st); }
         { ProfScope ps(prof, "fft_c2c_axis1_inv");
           fft_c2c_axis1<T>(n, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw, st); }
+        if (after_inv) after_inv();
         // axis 1: n1 times mesh 1 in place, the plain transform into mesh 2
         { ProfScope ps(prof, "fft_c2c_axis1_dual");
           fft_c2c_axis1_dual<T>(n, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
@@ -646,6 +654,7 @@ template <class T> struct Sim final : SimBase {
         fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm, paint_halo_merge<T>(geo, halo));
         meshes_valid = true;
         if (tan_gather) {  // the first part of force_jvp_cur, on the same force boxes
+            bins_clear = false;
             launch_fill_u32(fmax_bits, 0u, 1, st);
             TanGather<T> tg;
             tg.xdot = tx;
@@ -741,7 +750,12 @@ template <class T> struct Sim final : SimBase {
                        std::fabs(a1 - kdk_a1) > 1e-12 * std::fabs(a1) + 1e-15))
             return PM_ESTATE;
         if (pgd) pgd_shift(a1);
-        int rc = project_shell(a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0));
+        // (the force meshes are recomputed where a reverse step needs them;
+        // checkpoints that carry them need them at once)
+        const bool meshes = !ckpt_force() && shell_takes_meshes(a0, a1);
+        int rc = project_shell(a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0), nullptr,
+                               meshes);
+        if (meshes) meshes_valid = false;
         return rc ? rc : check_launch();
     }
 
@@ -918,11 +932,84 @@ template <class T> struct Sim final : SimBase {
         return ((size_t)ns * 64 * 64 * 8 <= 131072 && np_ >= 256) ? 64 : 32;
     }
 
+    // Region side of a binned projection: small enough that the map gives a
+    // workgroup to every CU (an image on a border is stored once for each
+    // region it touches, so not smaller than that).
+    static int bin_side(int np_) {
+        for (int rs = 32; rs > 8; rs /= 2)
+            if ((long)((np_ + rs - 1) / rs) * ((np_ + rs - 1) / rs) >= 1024) return rs;
+        return 8;
+    }
+
+    // The counters of the image bins, at the end of fbc, and where they begin
+    // in the arena; false when a map of this size leaves no room for them.
+    bool bin_counters(LensBins<T>& b, size_t& at) const {
+        const int nreg = (npix + bin_side(npix) - 1) / bin_side(npix);
+        const size_t bytes = (3 * (size_t)nreg * nreg + 1) * sizeof(uint32_t);
+        const size_t end = ap.fbc + 3 * (size_t)geo.npart * sizeof(T);
+        if (bytes + 256 > end - ap.xbc) return false;
+        at = (end - bytes) & ~size_t(255);
+        b.nreg2 = nreg * nreg;
+        b.cnt = reinterpret_cast<uint32_t*>(arena + at);
+        b.begin = b.cnt + b.nreg2;
+        b.cur = b.cnt + 2 * b.nreg2;
+        b.pool = b.cnt + 3 * b.nreg2;
+        return true;
+    }
+    void clear_bins(const LensBins<T>& b, hipStream_t s) {
+        if (bins_clear) return;
+        launch_fill_u32(b.cnt, 0u, 3L * b.nreg2 + 1, s);
+        bins_clear = true;
+    }
+
+    double half_map() const { return 0.5 * fov * PI / 180.0 * (1.0 + 2.0 / npix); }  // radians
+
+    // Entries that the images of a shell take in the bins, at the mean density.
+    double shell_images(const LensArgs<T>& la) const {
+        double chis_max = 0;
+        for (double c : chisrc) chis_max = std::max(chis_max, c);
+        const double near = la.cnear_d * cell, far = std::min(la.cfar_d * cell, chis_max);
+        const double vol = 4.0 * half_map() * half_map() *
+                           std::max(0.0, std::pow(far, 3) - std::pow(near, 3)) / 3.0;
+        const double dup = 1.0 + 1.0 / bin_side(npix);
+        return (double)geo.npart * vol / (P.box * P.box * P.box) * dup * dup;
+    }
+
+    // The image bins of a shell whose images, at the mean density, fill at
+    // most 4/5 of the scratch that is free: xbc and fbc, and with `meshes`
+    // (nothing in them yet) also the meshes and the halo before them in the
+    // arena.  Else `on` stays 0 and the shell is projected by regions alone.
+    LensBins<T> lens_bins(const LensArgs<T>& la, bool meshes) const {
+        LensBins<T> b;
+        size_t at_cnt;
+        if (!bin_counters(b, at_cnt)) return b;
+        const int rs = bin_side(npix);
+        const size_t at_ent = meshes ? ap.mesh[0] : ap.xbc;
+        const size_t cap = (at_cnt - at_ent) / (3 * sizeof(T));
+        if (!(shell_images(la) <= 0.8 * (double)cap)) return b;
+        const double chi_far = la.cfar_d * cell;
+        const double half = half_map();
+        // tiles per unit: one when replicas are rotated; else as many as
+        // leave a few units to every workgroup of the pass
+        const double reach = half * chi_far / cell / TILE;
+        const double tiles = 4.0 * (reach + 1.0) * (reach + 1.0) *
+                             ((chi_far / cell - la.cnear_d) / TILE + 1.0);
+        if (tiles > 1e9) return b;
+        for (b.zt = rot ? 1 : 4; b.zt > 1; b.zt /= 2)
+            if (geo.nt % b.zt == 0 && tiles / b.zt >= 4096) break;
+        b.ent = reinterpret_cast<T*>(arena + at_ent);
+        b.cap = (uint32_t)std::min<size_t>(cap, 0xf0000000u);
+        b.on = 1;
+        return b;
+    }
+
     // Born projection of the shell (chi(a1), chi(a0)] of the current,
     // tile-sorted positions (which must be those at a1) into kappa.  With
     // sub-evolution the step's drift momentum is mom - sub_k2 * acc.
-    // With PGD on, pgd_shift must have run for the current state.
-    int project_shell(double a0, double a1, T* kappa, T sub_k2 = T(0), hipStream_t ls = nullptr) {
+    // With PGD on, pgd_shift must have run for the current state.  meshes: the
+    // meshes hold nothing yet and may be used as scratch.
+    int project_shell(double a0, double a1, T* kappa, T sub_k2 = T(0), hipStream_t ls = nullptr,
+                      bool meshes = false) {
         if (!ls) ls = st;
         LensArgs<T> la;
         MapAdd<T> mv;
@@ -948,9 +1035,62 @@ template <class T> struct Sim final : SimBase {
             la.shift_bits = pgd_bits;
         }
         if (interp || pgd) plan_sources(la, cosmo.chi(a1), cosmo.chi(a0), false);
-        { ProfScope ps(prof, "lens_gather", ls);
-          launch_lens_gather<T>(cur, sb, geo, la, mv, kappa, ls); }
+        ProfScope ps(prof, "lens_gather", ls);
+        LensBins<T> bn = lens_bins(la, meshes);
+        if (bn.on) {
+            la.rs = bin_side(npix);
+            clear_bins(bn, ls);
+            launch_lens_gather<T>(cur, sb, geo, la, mv, kappa, ls, bn);
+            return PM_OK;
+        }
+        // Too many images for the scratch.  In double precision the shell is
+        // then projected as a few thinner ones (the walk by regions has to
+        // few workgroups for it: 0.7 ms against 0.2 at 64^3 particles and a
+        // 256^2 map); in single precision its maps would depend on where the
+        // scratch lies, through the rounding of the partial sums.
+        if constexpr (sizeof(T) == 8) {
+            for (int q = 2; q <= 16; ++q) {
+                std::vector<LensArgs<T>> part(q, la);
+                bool fits = true;
+                for (int i = 0; i < q && fits; ++i) {
+                    // cuts of equal volume
+                    const double n3 = std::pow(la.cnear_d, 3), f3 = std::pow(la.cfar_d, 3);
+                    if (i > 0) part[i].cnear_d = std::cbrt(n3 + (f3 - n3) * i / q);
+                    if (i + 1 < q) part[i].cfar_d = std::cbrt(n3 + (f3 - n3) * (i + 1) / q);
+                    part[i].chi_near = (T)(part[i].cnear_d * cell);
+                    part[i].chi_far = (T)(part[i].cfar_d * cell);
+                    part[i].rs = bin_side(npix);
+                    fits = lens_bins(part[i], meshes).on != 0;
+                }
+                if (!fits) continue;
+                for (int i = 0; i < q; ++i) {
+                    bn = lens_bins(part[i], meshes);
+                    clear_bins(bn, ls);
+                    launch_lens_gather<T>(cur, sb, geo, part[i], mv, kappa, ls, bn);
+                    mv = MapAdd<T>{};  // the mean term once
+                }
+                return PM_OK;
+            }
+        }
+        launch_lens_gather<T>(cur, sb, geo, la, mv, kappa, ls, bn);
         return PM_OK;
+    }
+
+    // Whether the shell's images are binned in xbc and fbc.
+    bool shell_binned(double a0, double a1) const {
+        LensArgs<T> la;
+        MapAdd<T> mv;
+        return plain_lens_args(a0, a1, la, mv) && lens_bins(la, false).on;
+    }
+
+    // Whether the shell's images go to the meshes: they outgrow xbc and fbc,
+    // and fit with the meshes (or, in double precision, are cut to fit).
+    bool shell_takes_meshes(double a0, double a1) const {
+        LensArgs<T> la;
+        MapAdd<T> mv;
+        if (pgd || !plain_lens_args(a0, a1, la, mv)) return false;
+        if (lens_bins(la, false).on) return false;
+        return sizeof(T) == 8 || lens_bins(la, true).on;
     }
 
     // nsteps KDK steps along agrid with the projection of every shell: the
@@ -980,22 +1120,33 @@ template <class T> struct Sim final : SimBase {
             // with PGD the shift's paint and forward passes are the force's
             // (and the projection needs the shift); without, the projection
             // runs on the second stream beside the transform
-            if (pgd || !st_lens) {
-                if (pgd) pgd_shift(a1);
-                else paint(true);
-                int rc = project_shell(a0, a1, kap, T(0));  // mom is the drift momentum here
-                if (rc) return rc;
+            // the meshes are free until the paint
+            const bool early = shell_takes_meshes(a0, a1);
+            if (pgd || !st_lens || early) {
+                int rc;
+                if (early) {
+                    if ((rc = project_shell(a0, a1, kap, T(0), nullptr, true))) return rc;
+                    paint(true);
+                } else {
+                    if (pgd) pgd_shift(a1);
+                    else paint(true);
+                    rc = project_shell(a0, a1, kap, T(0));  // mom is the drift momentum here
+                    if (rc) return rc;
+                }
                 if (pgd) force_from_spectrum();
                 else fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm,
                                       paint_halo_merge<T>(geo, halo));
             } else {
-                // The shell's projection, started after the forward axis-1
-                // pass, shares the GPU with the fused axis-0 pass and the
-                // inverse passes: it costs the step less there than beside
-                // the paint, the axis-2 or the forward axis-1 pass.
+                // The shell's projection shares the GPU with the rest of the
+                // transform.  By regions alone it takes 1 ms at 256^3/512^3
+                // and starts after the forward axis-1 pass; with its images
+                // binned it takes 0.2 ms and costs the step least beside the
+                // dual pass (4 steps from a snapshot at 256^3/512^3, started
+                // after the forward pass, the fused axis-0 pass, the inverse
+                // pass or the dual pass: 17.57, 17.34, 17.41, 17.46 ms; at
+                // 192^3/384^3 8.18, 8.21, 8.14, 8.18 ms).
                 int rc = 0;
-                paint(true);
-                fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm, paint_halo_merge<T>(geo, halo), [&] {
+                const auto shell = [&] {
                     if (hipEventRecord(ev_fork, st) != hipSuccess ||
                         hipStreamWaitEvent(st_lens, ev_fork, 0) != hipSuccess) {
                         rc = PM_EDEVICE;
@@ -1003,7 +1154,12 @@ template <class T> struct Sim final : SimBase {
                     }
                     rc = project_shell(a0, a1, kap, T(0), st_lens);
                     if (hipEventRecord(ev_join, st_lens) != hipSuccess && !rc) rc = PM_EDEVICE;
-                });
+                };
+                const bool binned = shell_binned(a0, a1);
+                paint(true);
+                fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm, paint_halo_merge<T>(geo, halo),
+                                 binned ? std::function<void()>() : std::function<void()>(shell),
+                                 binned ? std::function<void()>(shell) : std::function<void()>());
                 if (rc) return rc;
                 HIPCHK(hipStreamWaitEvent(st, ev_join, 0));
             }
@@ -1172,6 +1328,7 @@ template <class T> struct Sim final : SimBase {
                    T gp0, T* xbar_out, T* pbar_out, const T* phbar = nullptr) {
         const long n = geo.npart;
         const T H = (T)cell;
+        bins_clear = false;  // xbc and fbc are written
         if (!meshes_valid) {
             paint();
             fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm);
@@ -1397,6 +1554,7 @@ template <class T> struct Sim final : SimBase {
     void force_jvp_cur(T* pd, T k2, T ck2, bool gathered = false) {
         const T H = (T)cell;
         const T mass = (T)std::pow((double)geo.B, 3);
+        bins_clear = false;  // fbc is written
         if (!gathered) {
             if (!meshes_valid) {
                 paint();
@@ -1574,6 +1732,9 @@ template <class T> struct Sim final : SimBase {
         if (a_cur < 0 || std::fabs(a0 - a_cur) > 1e-12 * std::fabs(a_cur) + 1e-15) return PM_ESTATE;
         const double ah = 0.5 * (a0 + a1);
         launch_fill_u32(sb.count, 0u, ntiles, bst);
+        LensBins<T> bn;
+        size_t at;
+        if (bin_counters(bn, at)) clear_bins(bn, bst);
         launch_kick_drift_key<T>(cur, sb, geo, (T)cosmo.kick(a0, ah, a0),
                                  (T)cosmo.drift(a0, a1, ah), MODE_KICK | MODE_DRIFT, status, bst);
         a_cur = -1.0;  // between steps until the batch leaves it at a step's end
@@ -1601,7 +1762,8 @@ template <class T> struct Sim final : SimBase {
             // the batch's grid has one region side for every shell: one
             // accumulator per source
             o.lens.la.dec = 0;
-            o.lens.la.rs = region_side(nsrc, npix);
+            o.lens.bins = lens_bins(o.lens.la, true);  // before the paint
+            o.lens.la.rs = bin_side(npix);
             o.lens.p = cur;
             o.lens.sb = sb;
             o.lens.g = geo;
@@ -1738,7 +1900,7 @@ template <class T> struct Batch final : BatchBase {
         geo.npart = (long)p->np * p->np * p->np;
         lshape.npix = npix;
         lshape.nsrc = nsrc;
-        lshape.rs = Sim<T>::region_side(nsrc, npix);
+        lshape.rs = Sim<T>::bin_side(npix);
         slots.resize(cap);
         size_t b = 0;
         auto take = [&](size_t n) {
@@ -1849,8 +2011,9 @@ template <class T> struct Batch final : BatchBase {
         const int ntiles = geo.nt * geo.nt * geo.ncb;
         launch_scan_batch(arr<ScanArgs>(base, o_scan), ntiles, cap, st);
         launch_scatter_batch<T>(arr<ScatterArgs<T>>(base, o_scatter), geo, cap, st);
+        // before the paint: the image bins use the meshes
+        launch_lens_gather_batch<T>(arr<LensGatherArgs<T>>(base, o_lens), lshape, true, cap, st);
         launch_paint_batch<T>(arr<PaintArgs<T>>(base, o_paint), geo, cap, st);
-        launch_lens_gather_batch<T>(arr<LensGatherArgs<T>>(base, o_lens), lshape, cap, st);
         fft_r2c_rows_batch<T>(nm, arr<R2cArgs<T>>(base, o_r2c), cap, st);
         fft_c2c_axis1_batch<T>(nm, 1, arr<C2cArgs<T>>(base, o_fwd), cap, st);
         fft_grad_axis0_batch<T>(nm, arr<GradArgs<T>>(base, o_grad), cap, st);

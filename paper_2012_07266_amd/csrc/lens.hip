@@ -13,19 +13,31 @@
 
 namespace ml {
 
-// Cubic Hermite interpolation of a table [ntab][2] of values and exact
-// slopes on the grid chi_k = k dchi.
+// The functions that place and weigh an image are inlined into several
+// kernels whose results must agree bit for bit (a shell projected with and
+// without bins), so they leave no contraction to the compiler: every fused
+// multiply-add in them is written out.
+
+// Cubic Hermite interpolant of values a0, a1 and slopes d0, d1 (times the
+// grid step) at s in [0, 1].
+template <class T>
+__device__ __forceinline__ T hermite(T s, T a0, T d0, T a1, T d1) {
+#pragma clang fp contract(off)
+    const T s2 = s * s, s3 = s2 * s;
+    const T h01 = fma(T(-2), s3, T(3) * s2), h11 = s3 - s2;
+    return fma(T(1) - h01, a0, fma((h11 - s2) + s, d0, fma(h01, a1, h11 * d1)));
+}
+
+// Interpolation of a table [ntab][2] of values and exact slopes on the grid
+// chi_k = k dchi.
 template <class T>
 __device__ __forceinline__ T chi_table(const T* tab, const LensArgs<T>& la, T chi) {
+#pragma clang fp contract(off)
     T xk = chi / la.dchi;
     int k = (int)floor(xk);
     k = min(max(k, 0), la.ntab - 2);
-    T s = xk - T(k);
-    T a0 = tab[2 * k], d0 = tab[2 * k + 1] * la.dchi;
-    T a1 = tab[2 * k + 2], d1 = tab[2 * k + 3] * la.dchi;
-    T s2 = s * s, s3 = s2 * s;
-    return (T(2) * s3 - T(3) * s2 + T(1)) * a0 + (s3 - T(2) * s2 + s) * d0 +
-           (T(3) * s2 - T(2) * s3) * a1 + (s3 - s2) * d1;
+    const T* e = tab + 2 * k;
+    return hermite(xk - T(k), e[0], e[1] * la.dchi, e[2], e[3] * la.dchi);
 }
 
 template <class T>
@@ -37,17 +49,13 @@ __device__ __forceinline__ T a_of_chi(const LensArgs<T>& la, T chi) {
 template <class T>
 __device__ __forceinline__ T chi_window(const T* w, int k_lo, int k_hi, const LensArgs<T>& la,
                                         T chi) {
+#pragma clang fp contract(off)
     T xk = chi / la.dchi;
     int k = (int)floor(xk);
     k = min(max(k, 0), la.ntab - 2);
     k = min(max(k, k_lo), k_hi - 1);
-    T s = xk - T(k);
     const T* e = w + 2 * (k - k_lo);
-    T a0 = e[0], d0 = e[1] * la.dchi;
-    T a1 = e[2], d1 = e[3] * la.dchi;
-    T s2 = s * s, s3 = s2 * s;
-    return (T(2) * s3 - T(3) * s2 + T(1)) * a0 + (s3 - T(2) * s2 + s) * d0 +
-           (T(3) * s2 - T(2) * s3) * a1 + (s3 - s2) * d1;
+    return hermite(xk - T(k), e[0], e[1] * la.dchi, e[2], e[3] * la.dchi);
 }
 
 // ---------------------------------------------------------------------------
@@ -125,29 +133,55 @@ template <> struct LensAcc<double> {
     static __device__ __forceinline__ double dec_d(S v) { return v; }
 };
 
-// The bilinear splat of weight w at pixel coordinates (t0, t1) into the
-// region's accumulator, a corner weight at or above the fixed-point limit
-// (or every corner, global_only) going to the map kmap with a float atomic.
+// The four corners of an image's bilinear splat: their weights (0 for a
+// corner outside the region or the map) and their place in the region's
+// accumulator and in a map.  Shared by the image's sources.
+template <class T> struct Corners {
+    T w[4];
+    int at[4];       // accumulator index of a corner; -1: not this region's
+    int row, col;    // of the low corner, map pixels
+};
 template <class T>
-__device__ __forceinline__ void splat_region(typename LensAcc<T>::S* acc, int rs, int p0x, int p0y,
-                                             int npix, T* kmap, T t0, T t1, T w,
-                                             bool global_only = false) {
+__device__ __forceinline__ Corners<T> corners(int rs, int p0x, int p0y, int npix, T t0, T t1) {
+#pragma clang fp contract(off)
+    Corners<T> k;
+    const T fl0 = floor(t0), fl1 = floor(t1);
+    k.row = (int)fl0;
+    k.col = (int)fl1;
+    const T f0 = t0 - fl0, f1 = t1 - fl1;
+    const T wa[2] = {T(1) - f0, f0}, wb[2] = {T(1) - f1, f1};
+    const int r = k.row - p0x, c = k.col - p0y;
+    const bool ra[2] = {(unsigned)r < (unsigned)rs && k.row < npix,
+                        (unsigned)(r + 1) < (unsigned)rs && k.row + 1 < npix};
+    const bool cb[2] = {(unsigned)c < (unsigned)rs && k.col < npix,
+                        (unsigned)(c + 1) < (unsigned)rs && k.col + 1 < npix};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int a = q >> 1, b = q & 1;
+        k.at[q] = ra[a] && cb[b] ? (r + a) * rs + c + b : -1;
+        k.w[q] = wa[a] * wb[b];
+    }
+    return k;
+}
+
+// Weight w over an image's corners into an accumulator, a corner at or
+// above the fixed-point limit (or every corner, global_only) going to the
+// map kmap with a float atomic.
+template <class T>
+__device__ __forceinline__ void splat_region(typename LensAcc<T>::S* acc, const Corners<T>& k,
+                                             int npix, T* kmap, T w, bool global_only = false) {
+#pragma clang fp contract(off)
     using A = LensAcc<T>;
-    T fl0 = floor(t0), fl1 = floor(t1);
-    int j0 = (int)fl0, j1 = (int)fl1;
-    T f0 = t0 - fl0, f1 = t1 - fl1;
-    T wa[2] = {T(1) - f0, f0}, wb[2] = {T(1) - f1, f1};
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        int r = j0 + a;
-        if (r < p0x || r >= p0x + rs || r >= npix) continue;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            int c = j1 + b;
-            if (c < p0y || c >= p0y + rs || c >= npix) continue;
-            T v = w * wa[a] * wb[b];
-            if (!global_only && v < T(A::LIM)) atomicAdd(&acc[(r - p0x) * rs + (c - p0y)], A::enc(v));
-            else unsafeAtomicAdd(&kmap[(long)r * npix + c], v);
+    for (int q = 0; q < 4; ++q) {
+        const T v = w * k.w[q];
+        if (k.at[q] >= 0 && !global_only && v < T(A::LIM)) atomicAdd(&acc[k.at[q]], A::enc(v));
+    }
+    if (global_only || !(w < T(A::LIM))) {  // rare
+        for (int q = 0; q < 4; ++q) {
+            const T v = w * k.w[q];
+            if (k.at[q] >= 0 && (global_only || !(v < T(A::LIM))))
+                unsafeAtomicAdd(&kmap[(long)(k.row + (q >> 1)) * npix + k.col + (q & 1)], v);
         }
     }
 }
@@ -177,6 +211,120 @@ __device__ __forceinline__ bool column_depths(T alo, T ahi, T Xa, T margin, T& z
     return zmin <= zmax;
 }
 
+// What a lens pass needs of a shell and replica to place a particle's image.
+template <class T> struct ShellReplica {
+    int nx, ny, nz, sym;
+    ZBound<T> near, far;  // the shell's bounds in the replica's box
+};
+
+// The image of a particle (lattice id, displacement d; with EXT its PGD shift
+// sv and drift momentum pv) in replica r: its pixel coordinates and distance
+// when it lies in the shell, in front of a source and above the map's low
+// edges.  w: the sub-evolution table window (w_on) of entries k_lo .. k_hi.
+// Every pass that places images calls this one function, so that they agree
+// on every image.
+template <class T, bool EXT>
+__device__ __forceinline__ bool shell_image(const LensArgs<T>& la, const Geo& g,
+                                            const ShellReplica<T>& r, uint32_t id, const T (&d)[3],
+                                            const T (&sv)[3], const T (&pv)[3], T chi_max_src,
+                                            const T* w, int k_lo, int k_hi, bool w_on, T& t0, T& t1,
+                                            T& chi) {
+#pragma clang fp contract(off)
+    const int nm = g.nm;
+    const T nmf = T(nm), half = T(0.5) * nmf;
+    const T hp = T(0.5) * T(la.npix) - T(0.5);
+    int li[3];
+    lattice_of_l(id, g.np, li);
+    T uu[3];
+    int cz = 0;
+    T fz = T(0);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        T v = T(0.5) + d[a];
+        T fl = floor(v);
+        int c = g.B * li[a] + (int)fl;
+        if ((unsigned)c >= (unsigned)nm) c = pmod(c, nm);
+        uu[a] = T(c) + (v - fl);
+        if (a == 2) {
+            cz = c;
+            fz = v - fl;
+        }
+    }
+    T pimg[3] = {T(0), T(0), T(0)};
+    if constexpr (EXT) {
+        if (la.shift) {  // PGD: on the wrapped position
+#pragma unroll
+            for (int a = 0; a < 3; ++a) uu[a] = fma(la.shift_scale, sv[a], uu[a]);
+        }
+        if (la.sub) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) pimg[a] = pv[a];
+        }
+        if (r.sym) {  // into the replica's frame
+            sym_apply(r.sym, uu, nmf, false);
+            sym_apply(r.sym, pimg, T(0), true);
+        }
+        if (r.sym || la.shift) split_cell(uu[2], cz, fz);
+    }
+    T rz = uu[2] + T(r.nz) * nmf;
+    if (!depth_in_shell(cz, fz, r.near, r.far) || !(rz > T(0))) return false;
+    if (EXT && la.sub) {
+        // along the step's drift to a(chi) of the end-of-step depth
+        const T chi_e = rz * la.cell;
+        const T dd = ((w_on ? chi_window(w, k_lo, k_hi, la, chi_e) : chi_table(la.dtab, la, chi_e)) -
+                      la.d_end) *
+                     la.sub_scale;
+        uu[0] = fma(dd, pimg[0], uu[0]);
+        uu[1] = fma(dd, pimg[1], uu[1]);
+        rz = fma(dd, pimg[2], rz);
+        if (!(rz > T(0))) return false;
+    }
+    chi = rz * la.cell;
+    if (!(chi < chi_max_src)) return false;
+    T inv = la.inv_dtheta / rz;
+    // the replica's offset is exact
+    t0 = fma(uu[0] + (T(r.nx) * nmf - half), inv, hp);
+    t1 = fma(uu[1] + (T(r.ny) * nmf - half), inv, hp);
+    return t0 > T(-1) && t1 > T(-1);
+}
+
+// A particle's PGD shift and drift momentum (each only where the shell's
+// options ask for it).
+template <class T>
+__device__ __forceinline__ void load_ext(const LensArgs<T>& la, const Parts<T>& p, long n,
+                                         uint32_t k, T (&sv)[3], T (&pv)[3]) {
+    if (la.sub) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            pv[a] = p.mom[a * n + k];
+            if (la.sub_k2 != T(0)) pv[a] = fma(-la.sub_k2, p.acc[a * n + k], pv[a]);
+        }
+    }
+    if (la.shift) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sv[a] = la.shift[a * n + k];
+    }
+}
+
+// Cells of slack on every bound of a lens pass: one, and the largest move of
+// an image with sub-evolution (the step's drift factor times max |p_h|) and
+// with a shift (PGD: zclip, by which a shifted image can also leave its
+// replica's box, since it is not wrapped again); each capped at one box so
+// that the replica ranges stay bounded whatever the inputs.
+template <class T, bool EXT>
+__device__ __forceinline__ T lens_margin(const LensArgs<T>& la, T nmf, T& zclip) {
+    T margin = T(1);
+    zclip = T(0);
+    if constexpr (EXT) {
+        if (la.sub) margin += min(la.sub_dr * (T)__uint_as_float(*la.pmax_bits), nmf);
+        if (la.shift) {
+            zclip = min(fabs(la.shift_scale) * (T)__uint_as_float(*la.shift_bits), nmf);
+            margin += zclip;
+        }
+    }
+    return margin;
+}
+
 constexpr int LU = 4;   // particles per thread in flight
 constexpr int LQ = 128;  // entries of a wave's image queue (63 waiting + 64 new at most)
 
@@ -190,8 +338,10 @@ template <class T> constexpr size_t lens_queue_bytes(int lg) {
 // DEC: the maps of the sources beyond the shell come from the shared
 // accumulators A and B (la.dec); else one accumulator per source.
 template <class T, int LG, bool EXT, bool DEC>
-__device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
-                                                    MapAdd<T> mean, T* kappa) {
+__device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBufs& sb,
+                                                 const Geo& g, const LensArgs<T>& la,
+                                                 const MapAdd<T>& mean, T* kappa,
+                                                 const LensBins<T>& bn) {
     using A = LensAcc<T>;
     using S = typename A::S;
     constexpr int LUT = sizeof(T) == 4 ? LU : LU / 2;  // registers of double
@@ -199,6 +349,7 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
     extern __shared__ unsigned char smem[];
     S* acc = reinterpret_cast<S*>(smem);
     const int rs = la.rs;
+    const int ls = 31 - __clz(rs);  // rs is a power of two
     const int nreg = (la.npix + rs - 1) / rs;
     // renumber workgroups so each of the 8 XCDs (round-robin dispatch) walks a
     // contiguous band of regions: neighbouring regions read the same particle
@@ -240,57 +391,45 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
     // angular window of images touching the region: t in [p0 - 1, p0 + rs)
     const T a0lo = (T(p0x - 1) - hp) * dth, a0hi = (T(p0x + rs) - hp) * dth;
     const T a1lo = (T(p0y - 1) - hp) * dth, a1hi = (T(p0y + rs) - hp) * dth;
-    // cells of slack on every bound; with sub-evolution also the largest
-    // move of an image (the step's drift factor times max |p_h|), with a
-    // shift (PGD) its largest size; each capped at one box so that the
-    // replica ranges stay bounded whatever the inputs
-    T margin = T(1);
-    // a shifted image can leave its replica's box by up to the shift (it is
-    // added to the wrapped position, not wrapped again)
-    T zclip = T(0);
-    if constexpr (EXT) {
-        if (la.sub) margin += min(la.sub_dr * (T)__uint_as_float(*la.pmax_bits), nmf);
-        if (la.shift) {
-            zclip = min(fabs(la.shift_scale) * (T)__uint_as_float(*la.shift_bits), nmf);
-            margin += zclip;
-        }
-    }
+    T zclip;
+    const T margin = lens_margin<T, EXT>(la, nmf, zclip);
     const int npix2 = la.npix * la.npix;
     // an accepted image: its weight for every source behind it, bilinearly
     // into the region (the shared accumulators A and B for the sources
     // beyond the shell, unless the weight is near the fixed-point limit:
     // then per source, as for the sources of their own)
     auto deposit = [&](T t0, T t1, T chi) {
+#pragma clang fp contract(off)
         T base_w = la.wbase / (chi * a_of_chi(la, chi));
+        const Corners<T> k = corners<T>(rs, p0x, p0y, la.npix, t0, t1);
         if constexpr (!DEC) {
             for (int s = 0; s < la.nsrc; ++s) {
                 T cs = la.chi_src[s];
                 if (chi < cs)
-                    splat_region<T>(acc + s * rs2, rs, p0x, p0y, la.npix, kappa + (long)s * npix2,
-                                    t0, t1, base_w * (cs - chi) / cs);
+                    splat_region<T>(acc + s * rs2, k, la.npix, kappa + (long)s * npix2,
+                                    base_w * (cs - chi) / cs);
             }
             return;
         }
         if (base_w < T(0.5) * T(A::LIM)) {
             // every corner weight is below the limit: the map argument is
             // never written
-            splat_region<T>(acc, rs, p0x, p0y, la.npix, kappa, t0, t1, base_w);
-            splat_region<T>(acc + rs2, rs, p0x, p0y, la.npix, kappa, t0, t1,
-                            base_w * chi * la.inv_chi_ref);
+            splat_region<T>(acc, k, la.npix, kappa, base_w);
+            splat_region<T>(acc + rs2, k, la.npix, kappa, base_w * chi * la.inv_chi_ref);
         } else {
             for (int s = 0; s < la.nsrc; ++s) {
                 if (la.slot[s] != -1) continue;
                 T cs = la.chi_src[s];
-                splat_region<T>(acc, rs, p0x, p0y, la.npix, kappa + (long)s * npix2, t0, t1,
-                                base_w * (cs - chi) / cs, true);
+                splat_region<T>(acc, k, la.npix, kappa + (long)s * npix2, base_w * (cs - chi) / cs,
+                                true);
             }
         }
         for (int d = 0; d < la.ndirect; ++d) {
             const int s = la.direct_src[d];
             T cs = la.chi_src[s];
             if (chi < cs)
-                splat_region<T>(acc + (2 + d) * rs2, rs, p0x, p0y, la.npix,
-                                kappa + (long)s * npix2, t0, t1, base_w * (cs - chi) / cs);
+                splat_region<T>(acc + (2 + d) * rs2, k, la.npix, kappa + (long)s * npix2,
+                                base_w * (cs - chi) / cs);
         }
     };
     // float: a wave's accepted images wait in its own LDS queue (after the
@@ -304,6 +443,10 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
     const int lane = tid & 63;
     int qn = 0;
     auto queue_push = [&](bool ok, T t0, T t1, T chi) {
+        if (bn.on) {  // the walk of an overflowed region has no queue
+            if (ok) deposit(t0, t1, chi);
+            return;
+        }
         const unsigned long long m = __ballot(ok);
         if (!m) return;
         if (ok) {
@@ -329,12 +472,57 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
     auto last_block_at = [](T z) { return (int)floor(z / T(TILE)) * BPT + BPT - 1; };
     int nz0 = (int)floor(cnear / nmf) - 1;
     if (nz0 < 0) nz0 = 0;
-    const int nz1 = (int)floor(cmax / nmf) + (zclip > T(0) ? 1 : 0);
+    int nz1 = (int)floor(cmax / nmf) + (zclip > T(0) ? 1 : 0);
+    // the first of the map values that the region adds to
+    constexpr int KU = 8;
+    const int npx = la.nsrc * rs2;
+    T k_old[KU];
+    long k_at[KU];
+    auto read_maps = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const int i = i0 + u * LG;
+            const int s = i >> (2 * ls), rc = i & (rs2 - 1);
+            const int px = p0x + (rc >> ls), py = p0y + (rc & (rs - 1));
+            k_at[u] = i < npx && px < la.npix && py < la.npix
+                          ? (long)s * npix2 + (long)px * la.npix + py
+                          : -1;
+            k_old[u] = k_at[u] >= 0 ? kappa[k_at[u]] : T(0);
+        }
+    };
+    if (bn.on) {
+        // the region's images wait in its bin: no particle is visited, unless
+        // the bins overflowed (then the region is walked as without bins)
+        const uint32_t e0 = bn.begin[b], e1 = bn.cur[b];
+        if (tid == 0) {  // the counters' state between two projections
+            bn.cnt[b] = 0u;
+            if (b == 0) *bn.pool = 0u;
+        }
+        if (e1 <= bn.cap) {
+            nz1 = nz0 - 1;
+            constexpr int EU = 4;  // images per thread in flight
+            for (uint32_t e = e0 + tid; e < e1; e += LG * EU) {
+                T im[EU][3];
+#pragma unroll
+                for (int u = 0; u < EU; ++u) {
+                    const uint32_t x = min(e + u * LG, e1 - 1u);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) im[u][a] = bn.ent[(size_t)x * 3 + a];
+                }
+#pragma unroll
+                for (int u = 0; u < EU; ++u)
+                    if (e + u * LG < e1) deposit(im[u][0], im[u][1], im[u][2]);
+            }
+        }
+    }
     for (int nz = nz0; nz <= nz1; ++nz) {
         T zlo = max(cnear - T(nz) * nmf, -zclip), zhi = min(cmax - T(nz) * nmf, nmf + zclip);
         if (!(zlo < zhi)) continue;
         T ca = zlo + T(nz) * nmf, cb = zhi + T(nz) * nmf;  // depth range, cells
-        const ZBound<T> zb_near = zbound<T>(la.cnear_d, nz, nm), zb_far = zbound<T>(la.cfar_d, nz, nm);
+        ShellReplica<T> rep;
+        rep.nz = nz;
+        rep.near = zbound<T>(la.cnear_d, nz, nm);
+        rep.far = zbound<T>(la.cfar_d, nz, nm);
         T x0lo = min(a0lo * ca, a0lo * cb) - margin, x0hi = max(a0hi * ca, a0hi * cb) + margin;
         T x1lo = min(a1lo * ca, a1lo * cb) - margin, x1hi = max(a1hi * ca, a1hi * cb) + margin;
         // sort blocks of the tiles (TILE cells deep) along axis 2 that the
@@ -351,6 +539,9 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
                 if constexpr (EXT) {
                     if (la.rot) sym = replica_symmetry(nx, ny, nz, la.rot_seed);
                 }
+                rep.nx = nx;
+                rep.ny = ny;
+                rep.sym = sym;
                 // the image-frame box [b*lo, b*hi] in box axes: the tiles and
                 // sort blocks to visit (a rotated replica is culled by this
                 // box alone; an unrotated one also per column below)
@@ -408,84 +599,18 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
                                     dv[u][0] = p.disp[k];
                                     dv[u][1] = p.disp[n + k];
                                     dv[u][2] = p.disp[2 * n + k];
-                                    if constexpr (EXT) {
-                                        if (la.sub) {
-#pragma unroll
-                                            for (int a = 0; a < 3; ++a) {
-                                                pv[u][a] = p.mom[a * n + k];
-                                                if (la.sub_k2 != T(0))
-                                                    pv[u][a] -= la.sub_k2 * p.acc[a * n + k];
-                                            }
-                                        }
-                                        if (la.shift) {
-#pragma unroll
-                                            for (int a = 0; a < 3; ++a)
-                                                sv[u][a] = la.shift[a * n + k];
-                                        }
-                                    }
+                                    if constexpr (EXT) load_ext(la, p, n, k, sv[u], pv[u]);
                                 }
                             }
-                            // the particle's image in this replica: its pixel coordinates and
-                            // distance when it falls in the shell and in the region's window
+                            // the particle's image in this replica, when it falls in the
+                            // shell and in the region's window
                             auto image = [&](int u, T& t0, T& t1, T& chi) -> bool {
-                                int li[3];
-                                lattice_of_l(idv[u], g.np, li);
-                                T uu[3];
-                                int cz = 0;
-                                T fz = T(0);
-#pragma unroll
-                                for (int a = 0; a < 3; ++a) {
-                                    T v = T(0.5) + dv[u][a];
-                                    T fl = floor(v);
-                                    int c = g.B * li[a] + (int)fl;
-                                    if ((unsigned)c >= (unsigned)nm) c = pmod(c, nm);
-                                    uu[a] = T(c) + (v - fl);
-                                    if (a == 2) {
-                                        cz = c;
-                                        fz = v - fl;
-                                    }
-                                }
-                                T pimg[3] = {T(0), T(0), T(0)};
-                                if constexpr (EXT) {
-                                    if (la.shift) {  // PGD: on the wrapped position
-#pragma unroll
-                                        for (int a = 0; a < 3; ++a)
-                                            uu[a] += la.shift_scale * sv[u][a];
-                                    }
-                                    if (la.sub) {
-#pragma unroll
-                                        for (int a = 0; a < 3; ++a) pimg[a] = pv[u][a];
-                                    }
-                                    if (sym) {  // into the replica's frame
-                                        sym_apply(sym, uu, nmf, false);
-                                        sym_apply(sym, pimg, T(0), true);
-                                    }
-                                    if (sym || la.shift) split_cell(uu[2], cz, fz);
-                                }
-                                T rz = uu[2] + T(nz) * nmf;
-                                if (!depth_in_shell(cz, fz, zb_near, zb_far) || !(rz > T(0))) return false;
-                                if (EXT && la.sub) {
-                                    // along the step's drift to a(chi) of the
-                                    // end-of-step depth
-                                    const T chi_e = rz * la.cell;
-                                    const T dd = ((d_lds ? chi_window(dw, d_lo, d_hi, la, chi_e)
-                                                         : chi_table(la.dtab, la, chi_e)) -
-                                                  la.d_end) *
-                                                 la.sub_scale;
-                                    uu[0] += dd * pimg[0];
-                                    uu[1] += dd * pimg[1];
-                                    rz += dd * pimg[2];
-                                    if (!(rz > T(0))) return false;
-                                }
-                                chi = rz * la.cell;
-                                if (!(chi < chi_max_src)) return false;
-                                T inv = la.inv_dtheta / rz;
-                                t0 = (uu[0] + T(nx) * nmf - half) * inv + hp;
-                                t1 = (uu[1] + T(ny) * nmf - half) * inv + hp;
-                                if (!(t0 >= T(p0x - 1) && t0 < T(p0x + rs) && t0 > T(-1) &&
-                                      t1 >= T(p0y - 1) && t1 < T(p0y + rs) && t1 > T(-1)))
-                                    return false;
-                                return true;
+                                return shell_image<T, EXT>(la, g, rep, idv[u], dv[u],
+                                                           sv[EXT ? u : 0], pv[EXT ? u : 0],
+                                                           chi_max_src, dw, d_lo, d_hi, d_lds, t0,
+                                                           t1, chi) &&
+                                       t0 >= T(p0x - 1) && t0 < T(p0x + rs) &&
+                                       t1 >= T(p0y - 1) && t1 < T(p0y + rs);
                             };
 #pragma unroll
                             for (int u = 0; u < LUT; ++u) {
@@ -508,11 +633,15 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
         if (lane < qn) deposit(q[lane], q[LQ + lane], q[2 * LQ + lane]);
     }
     __syncthreads();
-    for (int i = tid; i < la.nsrc * rs2; i += LG) {
-        const int s = i / rs2, rc = i - s * rs2, r = rc / rs, c = rc % rs;
-        int px = p0x + r, py = p0y + c;
-        if (px < la.npix && py < la.npix) {
-            long o = (long)s * npix2 + (long)px * la.npix + py;
+    read_maps(tid);
+    // the region's pixels of every map; a thread reads KU of them before it
+    // writes any, since each read is a round trip to memory
+    for (int i0 = tid; i0 < npx; i0 += LG * KU) {
+        if (i0 != tid) read_maps(i0);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            if (k_at[u] < 0) continue;
+            const int i = i0 + u * LG, s = i >> (2 * ls), rc = i & (rs2 - 1);
             T v;
             if constexpr (DEC) {
                 const int sl = la.slot[s];
@@ -523,21 +652,273 @@ __device__ __forceinline__ void lens_gather_body(Parts<T> p, SortBufs sb, Geo g,
             } else {
                 v = A::dec(acc[i]);
             }
-            kappa[o] += v + mean.v[s];
+            kappa[k_at[u]] = k_old[u] + (v + mean.v[s]);
         }
     }
 }
 
 template <class T, int LG, bool EXT, bool DEC>
 __global__ __launch_bounds__(LG) void k_lens_gather(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
-                                                    MapAdd<T> mean, T* kappa) {
-    lens_gather_body<T, LG, EXT, DEC>(p, sb, g, la, mean, kappa);
+                                                    MapAdd<T> mean, T* kappa, LensBins<T> bn) {
+    lens_gather_body<T, LG, EXT, DEC>(p, sb, g, la, mean, kappa, bn);
 }
 template <class T, int LG>
 __global__ __launch_bounds__(LG) void k_lens_gather_b(const LensGatherArgs<T>* __restrict__ tab) {
-    const LensGatherArgs<T> a = tab[blockIdx.y];
+    const LensGatherArgs<T>& a = tab[blockIdx.y];
     if (!a.on) return;
-    lens_gather_body<T, LG, false, false>(a.p, a.sb, a.g, a.la, a.mean, a.kappa);
+    lens_gather_body<T, LG, false, false>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
+}
+
+// ---------------------------------------------------------------------------
+// Binning: the projection by particles instead of by regions.  A region's
+// pencil is a few cells wide and the tile columns it crosses are 16, so a
+// workgroup that walks them for its region rejects most of the images it
+// evaluates (20 to 60 for one kept at 256^3/512^3).  Here a workgroup takes
+// one tile and evaluates each of its images once: a first pass counts the
+// images of every region, k_lens_place gives each region its segment of the
+// entry buffer, a second pass writes (t0, t1, chi) there, and the region's
+// workgroup of k_lens_gather then weighs and splats its segment with every
+// lane busy.  An image on a region's border goes to every region that one of
+// its four pixels lies in.  Within a workgroup ranks are taken in LDS, one
+// global atomic per region and batch of particles.  A region whose segment
+// ends past the buffer is walked as before (clustering beyond what the host
+// allowed for).
+// Measured (a late shell, walk by regions -> count + place + fill + gather):
+// 256^3/512^3, four 2048^2 maps 1.02 -> 0.041 + 0.005 + 0.065 + 0.096 ms;
+// 512^3/1024^3, ten 4096^2 maps 15.2 -> 0.056 + 0.005 + 0.086 + 0.66 ms;
+// float64 32^3/32^3, one 64^2 map 0.51 -> 0.019 + 0.004 + 0.028 + 0.006 ms.
+// The counting and filling passes wait on memory (about 16 bytes an image
+// read twice, 12 written), the gather on LDS atomics and the maps' read and
+// write.
+// ---------------------------------------------------------------------------
+constexpr int LBT = 256;    // threads per binning workgroup
+constexpr int LBU = 4;      // particles per thread in flight
+constexpr int LBR = 1024;   // regions of a unit's window counted in LDS
+// Workgroups of a binning pass: a few per CU, each walking units with this
+// stride, because a workgroup per unit costs its launch (4 ns) where most
+// units are cut off by the map's window or hold a few hundred particles.
+constexpr int LBG = 2048;
+
+// The units of a binning pass: runs of zt tiles along the line of sight in
+// the image frame, over the box around the shell's part of the map's cone.
+template <class T, bool EXT, bool FILL>
+__device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs& sb, const Geo& g,
+                                              const LensArgs<T>& la, const LensBins<T>& bn) {
+    __shared__ uint32_t cnt[LBR], first[FILL ? LBR : 1];
+    const int tid = threadIdx.x;
+    const int nm = g.nm, nt = g.nt;
+    const long n = g.npart;
+    const T nmf = T(nm), half = T(0.5) * nmf;
+    const T hp = T(0.5) * T(la.npix) - T(0.5);
+    const int rs = la.rs, nreg = (la.npix + rs - 1) / rs;
+    const int ls = 31 - __clz(rs);  // rs is a power of two
+    const T cnear = la.chi_near / la.cell, cfar = la.chi_far / la.cell;  // cells
+    T chi_max_src = la.chi_src[0];
+    for (int s = 1; s < la.nsrc; ++s) chi_max_src = max(chi_max_src, la.chi_src[s]);
+    const T cmax = min(cfar, chi_max_src / la.cell);
+    const T dth = T(1) / la.inv_dtheta;
+    // the map's angular window, a pixel of slack on both sides
+    const T alo = (T(-2) - hp) * dth, ahi = (T(la.npix + 1) - hp) * dth;
+    T zclip;
+    const T margin = lens_margin<T, EXT>(la, nmf, zclip);
+    const T zfar = cmax + margin + T(1), reach = ahi * zfar + margin + T(1);
+    const int t_lo = (int)floor((half - reach) / T(TILE));
+    const int n_xy = (int)floor((half + reach) / T(TILE)) - t_lo + 1;
+    const int z_lo = (int)(max(cnear - margin - T(1), T(0)) / T(TILE * bn.zt));
+    const int n_z = (int)(zfar / T(TILE * bn.zt)) - z_lo + 1;
+    for (int unit = blockIdx.x; unit < n_xy * n_xy * n_z; unit += gridDim.x) {
+        const int uz = unit % n_z, uy = (unit / n_z) % n_xy, ux = unit / (n_z * n_xy);
+        // first tile of the unit in the image frame, its replica and its
+        // place in that replica's box
+        const int ix = t_lo + ux, iy = t_lo + uy, iz = (z_lo + uz) * bn.zt;
+        const int lx = pmod(ix, nt), ly = pmod(iy, nt), lz = pmod(iz, nt);
+        ShellReplica<T> rep;
+        rep.nx = (ix - lx) / nt;
+        rep.ny = (iy - ly) / nt;
+        rep.nz = (iz - lz) / nt;
+        rep.sym = 0;
+        // its box, cells from the observer, widened by the slack
+        const T xa = T(ix * TILE) - half - margin, xb = T(ix * TILE) - half + T(TILE) + margin;
+        const T ya = T(iy * TILE) - half - margin, yb = T(iy * TILE) - half + T(TILE) + margin;
+        const T za = max(T(iz * TILE), cnear) - margin;
+        const T zb = min(T((iz + bn.zt) * TILE), cmax) + margin;
+        // (uniform over the workgroup)
+        if (!(za < zb) || !(zb > T(0))) continue;
+        if (xb < alo * zb || xa > ahi * zb || yb < alo * zb || ya > ahi * zb) continue;
+        int bt[3] = {lx, ly, lz};
+        if constexpr (EXT) {
+            if (la.rot) rep.sym = replica_symmetry(rep.nx, rep.ny, rep.nz, la.rot_seed);
+            if (rep.sym) {  // image axis j is box axis sym_axis(j) (zt is 1)
+                const int l3[3] = {lx, ly, lz};
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    const int v = ((rep.sym >> j) & 1) ? nt - 1 - l3[j] : l3[j];
+                    const int ax = sym_axis(rep.sym, j);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        if (q == ax) bt[q] = v;
+                }
+            }
+        }
+        const int b0 = tile_block(g, bt[0], bt[1], bt[2]);
+        const uint32_t lo = sb.start[b0], hi = sb.start[b0 + bn.zt * BPT];
+        if (lo == hi) continue;
+        rep.near = zbound<T>(la.cnear_d, rep.nz, nm);
+        rep.far = zbound<T>(la.cfar_d, rep.nz, nm);
+        {
+            // the regions its images can touch
+            int r0 = 0, r1 = nreg - 1, c0 = 0, c1 = nreg - 1;
+            if (za > T(1)) {
+                const T ia = la.inv_dtheta / za, ib = la.inv_dtheta / zb;
+                const T lim = T(2 * la.npix);
+                r0 = (int)(max(min(xa * ia, xa * ib) + hp - T(1), T(0))) >> ls;
+                r1 = (int)(min(max(xb * ia, xb * ib) + hp + T(2), lim)) >> ls;
+                c0 = (int)(max(min(ya * ia, ya * ib) + hp - T(1), T(0))) >> ls;
+                c1 = (int)(min(max(yb * ia, yb * ib) + hp + T(2), lim)) >> ls;
+                r0 = min(r0, nreg - 1);
+                c0 = min(c0, nreg - 1);
+                r1 = min(max(r1, r0), nreg - 1);
+                c1 = min(max(c1, c0), nreg - 1);
+            }
+            const int nc = c1 - c0 + 1, nloc = (r1 - r0 + 1) * nc;
+            const bool in_lds = nloc <= LBR;
+            if (in_lds)
+                for (int i = tid; i < nloc; i += LBT) cnt[i] = 0u;
+            __syncthreads();
+            // index of region (r, c) in LDS, or -1
+            auto local = [&](int r, int c) {
+                return in_lds && r >= r0 && r <= r1 && c >= c0 && c <= c1 ? (r - r0) * nc + c - c0 : -1;
+            };
+            // the (at most four) regions that the pixels of an image lie in
+            auto touched = [&](T t0, T t1, auto f) {
+                const int j0 = (int)floor(t0), j1 = (int)floor(t1);
+                const int ra = max(j0, 0) >> ls, rb = min(j0 + 1, la.npix - 1) >> ls;
+                const int ca = max(j1, 0) >> ls, cb = min(j1 + 1, la.npix - 1) >> ls;
+                f(0, ra, ca);
+                if (rb != ra) f(1, rb, ca);
+                if (cb != ca) f(2, ra, cb);
+                if (rb != ra && cb != ca) f(3, rb, cb);
+            };
+            for (uint32_t base = lo; base < hi; base += LBT * LBU) {
+                uint32_t idv[LBU];
+                T dv[LBU][3], pv[EXT ? LBU : 1][3], sv[EXT ? LBU : 1][3];
+#pragma unroll
+                for (int u = 0; u < LBU; ++u) {
+                    const uint32_t k = min(base + u * LBT + tid, hi - 1u);
+                    idv[u] = p.id[k];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) dv[u][a] = p.disp[a * n + k];
+                    if constexpr (EXT) load_ext(la, p, n, k, sv[u], pv[u]);
+                }
+                T t0[LBU], t1[LBU], chi[LBU];
+                bool ok[LBU];
+                uint32_t rank[FILL ? LBU : 1][4];
+#pragma unroll
+                for (int u = 0; u < LBU; ++u) {
+                    ok[u] = base + u * LBT + tid < hi &&
+                            shell_image<T, EXT>(la, g, rep, idv[u], dv[u], sv[EXT ? u : 0],
+                                                pv[EXT ? u : 0], chi_max_src, (const T*)nullptr, 0,
+                                                0, false, t0[u], t1[u], chi[u]) &&
+                            t0[u] < T(la.npix) && t1[u] < T(la.npix);
+                    if (!ok[u]) continue;
+                    touched(t0[u], t1[u], [&](int q, int r, int c) {
+                        const int l = local(r, c);
+                        if constexpr (FILL) {
+                            if (l >= 0) rank[u][q] = atomicAdd(&cnt[l], 1u);
+                        } else {
+                            if (l >= 0) atomicAdd(&cnt[l], 1u);
+                            else atomicAdd(&bn.cnt[r * nreg + c], 1u);
+                        }
+                    });
+                }
+                if constexpr (FILL) {
+                    if (in_lds) {
+                        __syncthreads();
+                        for (int i = tid; i < nloc; i += LBT)
+                            if (cnt[i]) {
+                                first[i] =
+                                    atomicAdd(&bn.cur[(r0 + i / nc) * nreg + c0 + i % nc], cnt[i]);
+                                cnt[i] = 0u;
+                            }
+                        __syncthreads();
+                    }
+#pragma unroll
+                    for (int u = 0; u < LBU; ++u) {
+                        if (!ok[u]) continue;
+                        touched(t0[u], t1[u], [&](int q, int r, int c) {
+                            const int l = local(r, c);
+                            const uint32_t e = l >= 0 ? first[l] + rank[u][q]
+                                                      : atomicAdd(&bn.cur[r * nreg + c], 1u);
+                            if (e >= bn.cap) return;
+                            T* o = bn.ent + (size_t)e * 3;
+                            o[0] = t0[u];
+                            o[1] = t1[u];
+                            o[2] = chi[u];
+                        });
+                    }
+                }
+            }
+            if constexpr (!FILL) {
+                __syncthreads();
+                if (in_lds)
+                    for (int i = tid; i < nloc; i += LBT)
+                        if (cnt[i])
+                            atomicAdd(&bn.cnt[(r0 + i / nc) * nreg + c0 + i % nc], cnt[i]);
+            }
+            __syncthreads();  // before the next unit's counters
+        }
+    }
+}
+
+template <class T, bool EXT, bool FILL>
+__global__ __launch_bounds__(LBT) void k_lens_bin(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
+                                                  LensBins<T> bn) {
+    lens_bin_body<T, EXT, FILL>(p, sb, g, la, bn);
+}
+template <class T, bool FILL>
+__global__ __launch_bounds__(LBT) void k_lens_bin_b(const LensGatherArgs<T>* __restrict__ tab) {
+    const LensGatherArgs<T>& a = tab[blockIdx.y];
+    if (!a.on || !a.bins.on) return;
+    lens_bin_body<T, false, FILL>(a.p, a.sb, a.g, a.la, a.bins);
+}
+
+// Segments of the regions: exclusive prefix of the counts within a workgroup,
+// workgroups in any order (one atomic each).
+__device__ __forceinline__ void lens_place_body(const uint32_t* count, uint32_t* begin,
+                                                uint32_t* cur, uint32_t* pool, int n) {
+    __shared__ uint32_t ws[16], base;
+    const int i = blockIdx.x * 1024 + threadIdx.x, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const uint32_t v = i < n ? count[i] : 0u;
+    uint32_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) ws[wid] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t c = ws[w];
+            ws[w] = t;
+            t += c;
+        }
+        base = atomicAdd(pool, t);
+    }
+    __syncthreads();
+    if (i < n) begin[i] = cur[i] = base + ws[wid] + x - v;
+}
+
+template <class T>
+__global__ __launch_bounds__(1024) void k_lens_place(LensBins<T> bn) {
+    lens_place_body(bn.cnt, bn.begin, bn.cur, bn.pool, bn.nreg2);
+}
+template <class T>
+__global__ __launch_bounds__(1024) void k_lens_place_b(const LensGatherArgs<T>* __restrict__ tab) {
+    const LensGatherArgs<T>& a = tab[blockIdx.y];
+    if (!a.on || !a.bins.on) return;
+    lens_place_body(a.bins.cnt, a.bins.begin, a.bins.cur, a.bins.pool, a.bins.nreg2);
 }
 
 // LDS bytes after the accumulator for the D(a(chi)) window of sub-evolution
@@ -545,7 +926,8 @@ constexpr size_t DWIN_BYTES = 16384;
 
 template <class T, int LG, bool EXT, bool DEC>
 static void launch_lens_gather_k(Parts<T> p, SortBufs sb, Geo g, const LensArgs<T>& la,
-                                 const MapAdd<T>& mean, T* kappa, size_t lds, hipStream_t st) {
+                                 const MapAdd<T>& mean, T* kappa, size_t lds, hipStream_t st,
+                                 const LensBins<T>& bn) {
     constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
     // above the default dynamic LDS limit: raised once per instantiation
     static bool raised = false;
@@ -556,16 +938,16 @@ static void launch_lens_gather_k(Parts<T> p, SortBufs sb, Geo g, const LensArgs<
     }
     const int nreg = (la.npix + la.rs - 1) / la.rs;
     hipLaunchKernelGGL((k_lens_gather<T, LG, EXT, DEC>), dim3(nreg * nreg), dim3(LG), lds, st, p,
-                       sb, g, la, mean, kappa);
+                       sb, g, la, mean, kappa, bn);
 }
 
 template <class T, bool EXT>
 void launch_lens_gather_t(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
-                          const MapAdd<T>& mean, T* kappa, hipStream_t st) {
-    const int lg = la.rs >= 64 ? 1024 : 256;
+                          const MapAdd<T>& mean, T* kappa, hipStream_t st, const LensBins<T>& bn) {
+    const int lg = la.rs >= 64 ? 1024 : bn.on && la.rs >= 32 ? 512 : 256;
     size_t lds = (size_t)(la.dec ? la.nacc : la.nsrc) * la.rs * la.rs *
                      sizeof(typename LensAcc<T>::S) +
-                 lens_queue_bytes<T>(lg);
+                 (bn.on ? 0 : lens_queue_bytes<T>(lg));
     constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
     la.dwin = 0;
     if (EXT && la.sub && lds < LDS_MAX) {
@@ -574,12 +956,21 @@ void launch_lens_gather_t(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
         la.dwin = (int)w;
         lds += w * 2 * sizeof(T);
     }
+    if (bn.on) {
+        const dim3 grid(LBG);
+        hipLaunchKernelGGL((k_lens_bin<T, EXT, false>), grid, dim3(LBT), 0, st, p, sb, g, la, bn);
+        hipLaunchKernelGGL((k_lens_place<T>), dim3((bn.nreg2 + 1023) / 1024), dim3(1024), 0, st, bn);
+        hipLaunchKernelGGL((k_lens_bin<T, EXT, true>), grid, dim3(LBT), 0, st, p, sb, g, la, bn);
+    }
     if (lg == 1024) {
-        if (la.dec) launch_lens_gather_k<T, 1024, EXT, true>(p, sb, g, la, mean, kappa, lds, st);
-        else launch_lens_gather_k<T, 1024, EXT, false>(p, sb, g, la, mean, kappa, lds, st);
+        if (la.dec) launch_lens_gather_k<T, 1024, EXT, true>(p, sb, g, la, mean, kappa, lds, st, bn);
+        else launch_lens_gather_k<T, 1024, EXT, false>(p, sb, g, la, mean, kappa, lds, st, bn);
+    } else if (lg == 512) {
+        if (la.dec) launch_lens_gather_k<T, 512, EXT, true>(p, sb, g, la, mean, kappa, lds, st, bn);
+        else launch_lens_gather_k<T, 512, EXT, false>(p, sb, g, la, mean, kappa, lds, st, bn);
     } else {
-        if (la.dec) launch_lens_gather_k<T, 256, EXT, true>(p, sb, g, la, mean, kappa, lds, st);
-        else launch_lens_gather_k<T, 256, EXT, false>(p, sb, g, la, mean, kappa, lds, st);
+        if (la.dec) launch_lens_gather_k<T, 256, EXT, true>(p, sb, g, la, mean, kappa, lds, st, bn);
+        else launch_lens_gather_k<T, 256, EXT, false>(p, sb, g, la, mean, kappa, lds, st, bn);
     }
 }
 
@@ -589,35 +980,35 @@ void launch_lens_gather_t(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
 template <class T>
 void prepare_lens_gather_batch() {
     constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lens_gather_b<T, 1024>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lens_gather_b<T, 256>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
 }
 
 template <class T>
-void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape, int slots,
-                              hipStream_t st) {
+void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape,
+                              bool bins, int slots, hipStream_t st) {
     const int nreg = (shape.npix + shape.rs - 1) / shape.rs;
+    if (bins) {
+        const dim3 grid(std::max(LBG / slots, 64), slots);
+        hipLaunchKernelGGL((k_lens_bin_b<T, false>), grid, dim3(LBT), 0, st, tab);
+        hipLaunchKernelGGL((k_lens_place_b<T>), dim3((nreg * nreg + 1023) / 1024, slots), dim3(1024),
+                           0, st, tab);
+        hipLaunchKernelGGL((k_lens_bin_b<T, true>), grid, dim3(LBT), 0, st, tab);
+    }
     const size_t lds = (size_t)shape.nsrc * shape.rs * shape.rs * sizeof(typename LensAcc<T>::S) +
-                       lens_queue_bytes<T>(shape.rs >= 64 ? 1024 : 256);
-    if (shape.rs >= 64)
-        hipLaunchKernelGGL((k_lens_gather_b<T, 1024>), dim3(nreg * nreg, slots), dim3(1024), lds, st,
-                           tab);
-    else
-        hipLaunchKernelGGL((k_lens_gather_b<T, 256>), dim3(nreg * nreg, slots), dim3(256), lds, st,
-                           tab);
+                       lens_queue_bytes<T>(256);
+    hipLaunchKernelGGL((k_lens_gather_b<T, 256>), dim3(nreg * nreg, slots), dim3(256), lds, st, tab);
 }
 
 // The plain projection is its own instantiation, free of the per-particle
 // loads and moves of sub-evolution and of the PGD shift.
 template <class T>
 void launch_lens_gather(Parts<T> p, SortBufs sb, Geo g, const LensArgs<T>& la,
-                        const MapAdd<T>& mean, T* kappa, hipStream_t st) {
+                        const MapAdd<T>& mean, T* kappa, hipStream_t st, const LensBins<T>& bn) {
     if (la.sub || la.shift || la.rot)
-        launch_lens_gather_t<T, true>(p, sb, g, la, mean, kappa, st);
+        launch_lens_gather_t<T, true>(p, sb, g, la, mean, kappa, st, bn);
     else
-        launch_lens_gather_t<T, false>(p, sb, g, la, mean, kappa, st);
+        launch_lens_gather_t<T, false>(p, sb, g, la, mean, kappa, st, bn);
 }
 
 // Largest |mom - k2 acc| over particles and axes, for the frustum margin of
@@ -681,16 +1072,20 @@ template void launch_drift_momentum_max<double>(Parts<double>, long, double, uin
                                                 hipStream_t);
 
 template void launch_lens_gather<float>(Parts<float>, SortBufs, Geo, const LensArgs<float>&,
-                                        const MapAdd<float>&, float*, hipStream_t);
+                                        const MapAdd<float>&, float*, hipStream_t,
+                                        const LensBins<float>&);
 template void launch_lens_gather<double>(Parts<double>, SortBufs, Geo, const LensArgs<double>&,
-                                         const MapAdd<double>&, double*, hipStream_t);
+                                         const MapAdd<double>&, double*, hipStream_t,
+                                         const LensBins<double>&);
 
 
 template void prepare_lens_gather_batch<float>();
 template void prepare_lens_gather_batch<double>();
 template void launch_lens_gather_batch<float>(const LensGatherArgs<float>*,
-                                              const LensArgs<float>&, int, hipStream_t);
+                                              const LensArgs<float>&, bool, int,
+                                              hipStream_t);
 template void launch_lens_gather_batch<double>(const LensGatherArgs<double>*,
-                                               const LensArgs<double>&, int, hipStream_t);
+                                               const LensArgs<double>&, bool, int,
+                                               hipStream_t);
 
 }  // namespace ml

@@ -260,11 +260,25 @@ __device__ __forceinline__ void split_cell(T u, int& c, T& f) {
     c = (int)fl;
     f = u - fl;
 }
+// Scratch of a projection that sorts its images by map region first (on != 0).
+// cnt and *pool are zero between projections; the gather leaves them so.
+template <class T> struct LensBins {
+    int on = 0;
+    int nreg2 = 0;              // regions of the map, ceil(npix / rs)^2
+    uint32_t* cnt = nullptr;    // [nreg2] images per region
+    uint32_t* begin = nullptr;  // [nreg2] first entry of a region's segment
+    uint32_t* cur = nullptr;    // [nreg2] fill cursor, then the segment's end
+    uint32_t* pool = nullptr;   // [1] entries given out
+    T* ent = nullptr;           // [cap][3] t0, t1, chi
+    uint32_t cap = 0;
+    int zt = 1;                 // tiles per unit of the binning passes
+};
 // Region-driven projection (each pixel written by one workgroup) that also
 // adds mean.v[s] to every pixel of map s.  Particles must be tile-sorted.
 template <class T>
 void launch_lens_gather(Parts<T> p, SortBufs sb, Geo g, const LensArgs<T>& la,
-                        const MapAdd<T>& mean, T* kappa, hipStream_t st);
+                        const MapAdd<T>& mean, T* kappa, hipStream_t st,
+                        const LensBins<T>& bn = LensBins<T>());
 // *out (zeroed by the caller) = bits of max |mom - k2 acc| over all
 // particles and axes, as a float rounded up
 template <class T>
