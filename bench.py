@@ -73,7 +73,7 @@ def algorithmic_bytes(wl, esize=4):
         "fft_grad_axis0": 3 * S,           # R 1 spectrum, W 2
         "fft_c2c_axis1_inv": 2 * S,
         "fft_c2c_axis1_dual": 3 * S,       # R 1 spectrum, W 2
-        "fft_c2r_axis2": S + M,
+        "fft_c2r_axis2": 3 * (S + M),      # the three components
         "readout_kick": 3 * M + 52 * P,    # R 3 meshes, disp,id,mom  W mom,acc
         # fused with the next step's kick, drift and keys:
         "readout_kick_drift_key": 3 * M + 56 * P,  # R 3 meshes, disp,id,mom  W disp,mom,key
@@ -119,7 +119,7 @@ KERNEL_SYMBOL = {
     "fft_grad_axis0": ("k_grad_x0<float", "paper_2012_07266_amd/csrc/fft.hip"),
     "fft_c2c_axis1_inv": ("k_c2c_view<float, 512, 16, -1>", "paper_2012_07266_amd/csrc/fft.hip"),
     "fft_c2c_axis1_dual": ("k_c2c_view_dual<float", "paper_2012_07266_amd/csrc/fft.hip"),
-    "fft_c2r_axis2": ("k_c2r_rows<float", "paper_2012_07266_amd/csrc/fft.hip"),
+    "fft_c2r_axis2": ("k_c2r_rows3<float", "paper_2012_07266_amd/csrc/fft.hip"),
     "readout_kick_drift_key": ("k_readout<float>", "paper_2012_07266_amd/csrc/particles.hip"),
     "fill": ("k_fill", "paper_2012_07266_amd/csrc/particles.hip"),
 }

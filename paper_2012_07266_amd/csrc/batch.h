@@ -11,12 +11,6 @@
 
 namespace ml {
 
-struct FillArgs {
-    uint32_t* p;
-    long n;
-    int on;
-};
-
 struct ScanArgs {
     const uint32_t* count;
     uint32_t* start;
@@ -118,7 +112,6 @@ GradArgs<T> fft_grad_axis0_args(int n, cx<T>* main_in, cx<T>* nyq_in, PtrTriple 
                                 PtrTriple out_nyq, const cx<T>* tw, const T* G, T gscale);
 
 // Batched launches over `slots` argument structs at `tab` (device memory).
-void launch_fill_batch(const FillArgs* tab, long n_max, int slots, hipStream_t st);
 void launch_scan_batch(const ScanArgs* tab, int n, int slots, hipStream_t st);
 template <class T>
 void launch_scatter_batch(const ScatterArgs<T>* tab, const Geo& g, int slots, hipStream_t st);
@@ -136,8 +129,10 @@ template <class T>
 void fft_c2r_rows_batch(int n, const C2rArgs<T>* tab, int slots, hipStream_t st);
 template <class T>
 void fft_c2c_axis1_batch(int n, int sign, const C2cArgs<T>* tab, int slots, hipStream_t st);
+// the inverse pass of inv's slots and the dual pass of dual's
 template <class T>
-void fft_c2c_axis1_dual_batch(int n, const DualArgs<T>* tab, int slots, hipStream_t st);
+void fft_c2c_axis1_inv_dual_batch(int n, const C2cArgs<T>* inv, const DualArgs<T>* dual, int slots,
+                                  hipStream_t st);
 template <class T>
 void fft_grad_axis0_batch(int n, const GradArgs<T>* tab, int slots, hipStream_t st);
 

@@ -222,7 +222,6 @@ struct ProfScope {
 // The arguments of every pass of one slot's fused step (the device
 // parameter block of a batch holds one array per pass).
 template <class T> struct BatchSlotArgs {
-    FillArgs fill;
     ScanArgs scan;
     ScatterArgs<T> scatter;
     PaintArgs<T> paint;
@@ -335,6 +334,7 @@ template <class T> struct Sim final : SimBase {
     double cell = 0;  // mesh cell, Mpc/h
     int ntiles = 0;
 
+    bool count_clear = false;  // sb.count is zero
     // the counters of the image bins (at the end of fbc) are zero: a
     // projection leaves them so, the derivative passes overwrite them
     bool bins_clear = false;
@@ -591,9 +591,14 @@ template <class T> struct Sim final : SimBase {
     }
 
     // ---- pipeline pieces ---------------------------------------------------
-    void sort(T kick, T drift, int mode) {
-        launch_fill_u32(sb.count, 0u, ntiles, st);
-        { ProfScope ps(prof, "kick_drift_key"); launch_kick_drift_key<T>(cur, sb, geo, kick, drift, mode, status, st); }
+    // The histogram of the sort keys is zero between sorts (the scatter counts
+    // it down); it is cleared only where a sort was begun and not ended.
+    void clear_count(hipStream_t s) {
+        if (!count_clear) launch_fill_u32(sb.count, 0u, ntiles, s);
+        count_clear = false;
+    }
+    // From the particles' keys and histogram: scan and scatter into tile order.
+    void sort_move() {
         { ProfScope ps(prof, "scan"); launch_scan(sb.count, sb.start, scan_sum, ntiles, st); }
         if (tan_carry) {
             TanCarry<T> tc;
@@ -608,9 +613,41 @@ template <class T> struct Sim final : SimBase {
             ProfScope ps(prof, "scatter");
             launch_scatter<T>(cur, alt, sb, geo, st);
         }
+        count_clear = true;
         std::swap(cur.disp, alt.disp);
         std::swap(cur.mom, alt.mom);
         std::swap(cur.id, alt.id);
+    }
+    void sort(T kick, T drift) {
+        clear_count(st);
+        { ProfScope ps(prof, "kick_drift_key");
+          launch_kick_drift_key<T>(cur, sb, geo, kick, drift, MODE_KICK | MODE_DRIFT, status, st); }
+        sort_move();
+    }
+
+    // The inverse passes from the fused axis-0 pass's spectra, component 0 in
+    // (m0, q0), the others in mesh 1 (to mesh 1 and 2).  between: called
+    // between the inverse and the dual axis-1 pass where they are launched
+    // apart, else before both.
+    void fft_inverse(int n, T* m0, cx<T>* q0, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
+                     const std::function<void()>& between = nullptr) {
+        cx<T>*c0 = reinterpret_cast<cx<T>*>(m0), *c1 = reinterpret_cast<cx<T>*>(mesh[1]),
+             *c2 = reinterpret_cast<cx<T>*>(mesh[2]);
+        if (n < 512) {
+            if (between) between();
+            ProfScope ps(prof, "fft_c2c_axis1_inv_dual");
+            fft_c2c_axis1_inv_dual<T>(n, c0, q0, c1, nyq[1], c2, nyq[2], tw, st);
+        } else {
+            { ProfScope ps(prof, "fft_c2c_axis1_inv"); fft_c2c_axis1<T>(n, -1, c0, q0, tw, st); }
+            if (between) between();
+            // axis 1: n1 times mesh 1 in place, the plain transform into mesh 2
+            ProfScope ps(prof, "fft_c2c_axis1_dual");
+            fft_c2c_axis1_dual<T>(n, c1, nyq[1], c2, nyq[2], tw, st);
+        }
+        // axis 2, the last component times n2
+        ProfScope ps(prof, "fft_c2r_axis2");
+        fft_c2r_rows3<T>(n, PtrTriple{{m0, mesh[1], mesh[2]}}, PtrTriple{{q0, nyq[1], nyq[2]}}, twh,
+                         twp, st);
     }
 
     void fft_forward_grad(int n, const T* G, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
@@ -627,18 +664,7 @@ template <class T> struct Sim final : SimBase {
         // axis 0: IFFT0(n0 h) -> mesh 0, IFFT0(h) -> mesh 1 (h = i G X)
         { ProfScope ps(prof, "fft_grad_axis0");
           fft_grad_axis0<T>(n, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw, G, gscale, st); }
-        { ProfScope ps(prof, "fft_c2c_axis1_inv");
-          fft_c2c_axis1<T>(n, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw, st); }
-        if (after_inv) after_inv();
-        // axis 1: n1 times mesh 1 in place, the plain transform into mesh 2
-        { ProfScope ps(prof, "fft_c2c_axis1_dual");
-          fft_c2c_axis1_dual<T>(n, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
-                                reinterpret_cast<cx<T>*>(mesh[2]), nyq[2], tw, st); }
-        // axis 2, the last component times n2
-        for (int j = 0; j < 3; ++j) {
-            ProfScope ps(prof, "fft_c2r_axis2");
-            fft_c2r_rows<T>(n, mesh[j], nyq[j], twh, twp, st, j == 2);
-        }
+        fft_inverse(n, mesh[0], nyq[0], tw, twh, twp, after_inv);
     }
 
     // CIC density into mesh[0].  With defer_merge the paint boxes' shells are
@@ -713,8 +739,10 @@ template <class T> struct Sim final : SimBase {
         HIPCHK(hipMemcpyAsync(mesh[0], noise_copy, n * sizeof(T), hipMemcpyDeviceToDevice, st));
         meshes_valid = false;
         fft_forward_grad(np, g_ic, tw_np, tw_hp, twp_np);
-        launch_init_ic<T>(cur, geo, mesh[0], mesh[1], mesh[2], (T)cosmo.D(a0), (T)cosmo.gp(a0), st);
-        sort(T(0), T(0), 0);
+        clear_count(st);
+        launch_init_ic<T>(cur, sb, geo, mesh[0], mesh[1], mesh[2], (T)cosmo.D(a0), (T)cosmo.gp(a0),
+                          status, st);
+        sort_move();
         force(T(0), 0);
         a_cur = a0;
         ic_fresh = true;
@@ -730,7 +758,7 @@ template <class T> struct Sim final : SimBase {
         T k1 = (T)cosmo.kick(a0, ah, a0);
         T dr = (T)cosmo.drift(a0, a1, ah);
         T k2 = (T)cosmo.kick(ah, a1, a1);
-        sort(k1, dr, MODE_KICK | MODE_DRIFT);
+        sort(k1, dr);
         force(k2, 1);
         a_cur = a1;
         ic_fresh = false;
@@ -806,22 +834,12 @@ template <class T> struct Sim final : SimBase {
           fft_r2c_rows<T>(nm, mesh[0], nyq[0], tw_hm, twp_nm, st, paint_halo_merge<T>(geo, halo)); }
         { ProfScope ps(prof, "fft_c2c_axis1_fwd");
           fft_c2c_axis1<T>(nm, 1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
-        cx<T>* pm_ = reinterpret_cast<cx<T>*>(pgd_m);
         cx<T>* pn_ = reinterpret_cast<cx<T>*>(pgd_nyq);
         PtrTriple om{{pgd_m, mesh[1], mesh[2]}}, on{{pgd_nyq, nyq[1], nyq[2]}};
         { ProfScope ps(prof, "fft_grad_axis0");
           fft_grad_axis0<T>(nm, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, pgd_g,
                             T(0), st); }
-        { ProfScope ps(prof, "fft_c2c_axis1_inv"); fft_c2c_axis1<T>(nm, -1, pm_, pn_, tw_nm, st); }
-        { ProfScope ps(prof, "fft_c2c_axis1_dual");
-          fft_c2c_axis1_dual<T>(nm, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
-                                reinterpret_cast<cx<T>*>(mesh[2]), nyq[2], tw_nm, st); }
-        T* comp[3] = {pgd_m, mesh[1], mesh[2]};
-        const cx<T>* cn[3] = {pn_, nyq[1], nyq[2]};
-        for (int j = 0; j < 3; ++j) {
-            ProfScope ps(prof, "fft_c2r_axis2");
-            fft_c2r_rows<T>(nm, comp[j], cn[j], tw_hm, twp_nm, st, j == 2);
-        }
+        fft_inverse(nm, pgd_m, pn_, tw_nm, tw_hm, twp_nm);
         Parts<T> q = cur;
         q.acc = pgd_s;
         { ProfScope ps(prof, "pgd_readout");
@@ -843,15 +861,7 @@ template <class T> struct Sim final : SimBase {
         { ProfScope ps(prof, "fft_grad_axis0");
           fft_grad_axis0<T>(n, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, nullptr,
                             gscale, st); }
-        { ProfScope ps(prof, "fft_c2c_axis1_inv");
-          fft_c2c_axis1<T>(n, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
-        { ProfScope ps(prof, "fft_c2c_axis1_dual");
-          fft_c2c_axis1_dual<T>(n, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
-                                reinterpret_cast<cx<T>*>(mesh[2]), nyq[2], tw_nm, st); }
-        for (int j = 0; j < 3; ++j) {
-            ProfScope ps(prof, "fft_c2r_axis2");
-            fft_c2r_rows<T>(n, mesh[j], nyq[j], tw_hm, twp_nm, st, j == 2);
-        }
+        fft_inverse(n, mesh[0], nyq[0], tw_nm, tw_hm, twp_nm);
     }
 
     // The plain projection's arguments and mean terms of the shell
@@ -1109,13 +1119,9 @@ template <class T> struct Sim final : SimBase {
         for (int i = 0; i < nsteps; ++i) {
             const double a0 = agrid[i], a1 = agrid[i + 1], ah = 0.5 * (a0 + a1);
             if (i == 0) {
-                sort((T)cosmo.kick(a0, ah, a0), (T)cosmo.drift(a0, a1, ah), MODE_KICK | MODE_DRIFT);
+                sort((T)cosmo.kick(a0, ah, a0), (T)cosmo.drift(a0, a1, ah));
             } else {  // keys and histogram come from the previous readout
-                { ProfScope ps(prof, "scan"); launch_scan(sb.count, sb.start, scan_sum, ntiles, st); }
-                { ProfScope ps(prof, "scatter"); launch_scatter<T>(cur, alt, sb, geo, st); }
-                std::swap(cur.disp, alt.disp);
-                std::swap(cur.mom, alt.mom);
-                std::swap(cur.id, alt.id);
+                sort_move();
             }
             // with PGD the shift's paint and forward passes are the force's
             // (and the projection needs the shift); without, the projection
@@ -1170,7 +1176,7 @@ template <class T> struct Sim final : SimBase {
                 nx.on = 1;
                 nx.kick = (T)cosmo.kick(a1, ah2, a1);
                 nx.drift = (T)cosmo.drift(a1, a2, ah2);
-                launch_fill_u32(sb.count, 0u, ntiles, st);
+                clear_count(st);
             }
             ProfScope ps(prof, nx.on ? "readout_kick_drift_key" : "readout_kick");
             launch_readout<T>(cur, sb, geo, mesh[0], mesh[1], mesh[2], k2, 1, status, st, nx);
@@ -1196,9 +1202,10 @@ template <class T> struct Sim final : SimBase {
 
     int set_state(const void* x, const void* p, double a) override {
         if (!x || !p || !(a > 0)) return PM_EINVAL;
-        launch_set_state<T>(cur, geo, (T)cell, reinterpret_cast<const T*>(x),
-                            reinterpret_cast<const T*>(p), st);
-        sort(T(0), T(0), 0);
+        clear_count(st);
+        launch_set_state<T>(cur, sb, geo, (T)cell, reinterpret_cast<const T*>(x),
+                            reinterpret_cast<const T*>(p), status, st);
+        sort_move();
         force(T(0), 0);
         a_cur = a;
         ic_fresh = false;
@@ -1731,7 +1738,7 @@ template <class T> struct Sim final : SimBase {
     int batch_begin(hipStream_t bst, double a0, double a1) {
         if (a_cur < 0 || std::fabs(a0 - a_cur) > 1e-12 * std::fabs(a_cur) + 1e-15) return PM_ESTATE;
         const double ah = 0.5 * (a0 + a1);
-        launch_fill_u32(sb.count, 0u, ntiles, bst);
+        clear_count(bst);
         LensBins<T> bn;
         size_t at;
         if (bin_counters(bn, at)) clear_bins(bn, bst);
@@ -1784,17 +1791,16 @@ template <class T> struct Sim final : SimBase {
             o.c2r[j] = C2rArgs<T>{mesh[j], nyq[j], tw_hm, twp_nm, j == 2 ? 1 : 0, 1};
         const double ah = 0.5 * (a0 + a1);
         ReadoutNext<T> nx;
-        o.fill = FillArgs{sb.count, (long)ntiles, 0};
         if (a2 > a1) {
             const double ah2 = 0.5 * (a1 + a2);
             nx.on = 1;
             nx.kick = (T)cosmo.kick(a1, ah2, a1);
             nx.drift = (T)cosmo.drift(a1, a2, ah2);
-            o.fill.on = 1;
         }
         o.readout = ReadoutArgs<T>{cur, sb, geo, mesh[0], mesh[1], mesh[2],
                                    (T)cosmo.kick(ah, a1, a1), 1, status, nx, 1};
         if (a2 <= a1) {  // the step ends the handle's run: the state is at a1
+            count_clear = true;
             meshes_valid = true;
             a_cur = a1;
             kdk_a0 = a0;
@@ -1862,7 +1868,7 @@ template <class T> struct Batch final : BatchBase {
     };
     std::vector<Slot> slots;
     // parameter block: offsets of the per-pass arrays
-    size_t o_fill, o_scan, o_scatter, o_paint, o_lens, o_r2c, o_fwd, o_grad, o_inv, o_dual, o_c2r,
+    size_t o_scan, o_scatter, o_paint, o_lens, o_r2c, o_fwd, o_grad, o_inv, o_dual, o_c2r,
         o_readout, bytes;
     char* dev = nullptr;
     char* host[2] = {nullptr, nullptr};
@@ -1908,7 +1914,6 @@ template <class T> struct Batch final : BatchBase {
             b = off + n;
             return off;
         };
-        o_fill = take(cap * sizeof(FillArgs));
         o_scan = take(cap * sizeof(ScanArgs));
         o_scatter = take(cap * sizeof(ScatterArgs<T>));
         o_paint = take(cap * sizeof(PaintArgs<T>));
@@ -2017,10 +2022,9 @@ template <class T> struct Batch final : BatchBase {
         fft_r2c_rows_batch<T>(nm, arr<R2cArgs<T>>(base, o_r2c), cap, st);
         fft_c2c_axis1_batch<T>(nm, 1, arr<C2cArgs<T>>(base, o_fwd), cap, st);
         fft_grad_axis0_batch<T>(nm, arr<GradArgs<T>>(base, o_grad), cap, st);
-        fft_c2c_axis1_batch<T>(nm, -1, arr<C2cArgs<T>>(base, o_inv), cap, st);
-        fft_c2c_axis1_dual_batch<T>(nm, arr<DualArgs<T>>(base, o_dual), cap, st);
+        fft_c2c_axis1_inv_dual_batch<T>(nm, arr<C2cArgs<T>>(base, o_inv),
+                                        arr<DualArgs<T>>(base, o_dual), cap, st);
         fft_c2r_rows_batch<T>(nm, arr<C2rArgs<T>>(base, o_c2r), 3 * cap, st);
-        launch_fill_batch(arr<FillArgs>(base, o_fill), ntiles, cap, st);
         launch_readout_batch<T>(arr<ReadoutArgs<T>>(base, o_readout), geo, cap, st);
     }
 
@@ -2037,7 +2041,6 @@ template <class T> struct Batch final : BatchBase {
             BatchSlotArgs<T> a;
             s.sim->batch_step_args(s.agrid[i], s.agrid[i + 1], i + 1 < n ? s.agrid[i + 2] : -1.0,
                                    s.kappa, a);
-            arr<FillArgs>(h, o_fill)[k] = a.fill;
             arr<ScanArgs>(h, o_scan)[k] = a.scan;
             arr<ScatterArgs<T>>(h, o_scatter)[k] = a.scatter;
             arr<PaintArgs<T>>(h, o_paint)[k] = a.paint;

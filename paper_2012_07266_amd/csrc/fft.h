@@ -36,6 +36,10 @@ void fft_r2c_rows(int n, T* io, cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_p
 template <class T>
 void fft_c2r_rows(int n, T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post,
                   hipStream_t st, bool mul_k2 = false);
+// fft_c2r_rows on three spectra in one launch, the last with mul_k2.
+template <class T>
+void fft_c2r_rows3(int n, PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+                   hipStream_t st);
 // c2c along axis 1 (sign +1 forward, -1 unnormalised inverse) on main and nyq.
 template <class T>
 void fft_c2c_axis1(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st);
@@ -45,6 +49,11 @@ void fft_c2c_axis1(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hi
 template <class T>
 void fft_c2c_axis1_dual(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2, const cx<T>* tw,
                         hipStream_t st);
+// fft_c2c_axis1 (inverse) on (main0, nyq0) and fft_c2c_axis1_dual on the
+// other two, in one launch below 512.
+template <class T>
+void fft_c2c_axis1_inv_dual(int n, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
+                            cx<T>* nyq2, const cx<T>* tw, hipStream_t st);
 // c2c along axis 0 on main and nyq.
 template <class T>
 void fft_c2c_axis0(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st);

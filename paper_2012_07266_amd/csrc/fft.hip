@@ -369,6 +369,16 @@ __global__ __launch_bounds__(NT) void k_c2r_rows(T* io, const cx<T>* nyq, const 
                                                  const cx<T>* tw_post, int mul_k2) {
     c2r_rows_body<T, H, W>(io, nyq, tw_h, tw_post, mul_k2);
 }
+// The three components of a force in one launch (blockIdx.y), the last times
+// n2: at small meshes a launch costs as much as its pass (128^3: 7 us each,
+// 9 us together).
+template <class T, int H, int W>
+__global__ __launch_bounds__(NT) void k_c2r_rows3(PtrTriple io, PtrTriple nyq, const cx<T>* tw_h,
+                                                  const cx<T>* tw_post) {
+    const int j = blockIdx.y;
+    c2r_rows_body<T, H, W>(reinterpret_cast<T*>(io.p[j]), reinterpret_cast<const cx<T>*>(nyq.p[j]),
+                           tw_h, tw_post, j == 2 ? 1 : 0);
+}
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_c2r_rows_b(const C2rArgs<T>* __restrict__ tab) {
     const C2rArgs<T> a = tab[blockIdx.y];
@@ -463,9 +473,8 @@ __device__ __forceinline__ void view_store(const cx<T>* buf, void* dst, const Vi
 }
 
 template <class T, int N, int W, int S>
-__device__ __forceinline__ void c2c_view_body(ViewDesc va, ViewDesc vb, const cx<T>* tw) {
-    __shared__ cx<T> buf[N * (W + 1)];
-    __shared__ cx<T> tws[N];
+__device__ __forceinline__ void c2c_view_body(ViewDesc va, ViewDesc vb, const cx<T>* tw,
+                                              cx<T>* buf, cx<T>* tws) {
     const int tid = threadIdx.x;
     int g = view_wg<T, W, true>(blockIdx.x, gridDim.x);
     const ViewDesc& v = g < va.n_wg ? va : vb;
@@ -512,13 +521,17 @@ __device__ __forceinline__ void c2c_view_body(ViewDesc va, ViewDesc vb, const cx
 
 template <class T, int N, int W, int S>
 __global__ __launch_bounds__(NT) void k_c2c_view(ViewDesc va, ViewDesc vb, const cx<T>* tw) {
-    c2c_view_body<T, N, W, S>(va, vb, tw);
+    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    __shared__ cx<T> tws[N];
+    c2c_view_body<T, N, W, S>(va, vb, tw, buf, tws);
 }
 template <class T, int N, int W, int S>
 __global__ __launch_bounds__(NT) void k_c2c_view_b(const C2cArgs<T>* __restrict__ tab) {
+    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    __shared__ cx<T> tws[N];
     const C2cArgs<T> a = tab[blockIdx.y];
     if (!a.on) return;
-    c2c_view_body<T, N, W, S>(a.va, a.vb, a.tw);
+    c2c_view_body<T, N, W, S>(a.va, a.vb, a.tw, buf, tws);
 }
 
 // ---------------------------------------------------------------------------
@@ -536,9 +549,8 @@ __device__ __forceinline__ T n1_mult(int n) {
 
 template <class T, int N, int W>
 __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
-                                                      cx<T>* dst2b, const cx<T>* tw) {
-    __shared__ cx<T> buf[N * (W + 1)];
-    __shared__ cx<T> tws[N];
+                                                      cx<T>* dst2b, const cx<T>* tw,
+                                                      cx<T>* buf, cx<T>* tws) {
     constexpr int LD = W + 1;
     const int tid = threadIdx.x;
     int g = view_wg<T, W, true>(blockIdx.x, gridDim.x);
@@ -619,13 +631,36 @@ __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<
 template <class T, int N, int W>
 __global__ __launch_bounds__(NT) void k_c2c_view_dual(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
                                                       cx<T>* dst2b, const cx<T>* tw) {
-    c2c_view_dual_body<T, N, W>(va, vb, dst2a, dst2b, tw);
+    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    __shared__ cx<T> tws[N];
+    c2c_view_dual_body<T, N, W>(va, vb, dst2a, dst2b, tw, buf, tws);
+}
+// The inverse pass of one component (blockIdx.y even) and the dual pass of the
+// other two (odd) in one launch, for meshes at which a pass alone leaves the
+// GPU partly idle.
+template <class T, int N, int W>
+__global__ __launch_bounds__(NT) void k_c2c_inv_dual(ViewDesc ia, ViewDesc ib, ViewDesc va,
+                                                     ViewDesc vb, cx<T>* dst2a, cx<T>* dst2b,
+                                                     const cx<T>* tw) {
+    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    __shared__ cx<T> tws[N];
+    if (blockIdx.y) c2c_view_dual_body<T, N, W>(va, vb, dst2a, dst2b, tw, buf, tws);
+    else c2c_view_body<T, N, W, -1>(ia, ib, tw, buf, tws);
 }
 template <class T, int N, int W>
-__global__ __launch_bounds__(NT) void k_c2c_view_dual_b(const DualArgs<T>* __restrict__ tab) {
-    const DualArgs<T> a = tab[blockIdx.y];
-    if (!a.on) return;
-    c2c_view_dual_body<T, N, W>(a.va, a.vb, a.dst2a, a.dst2b, a.tw);
+__global__ __launch_bounds__(NT) void k_c2c_inv_dual_b(const C2cArgs<T>* __restrict__ inv,
+                                                       const DualArgs<T>* __restrict__ dual) {
+    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    __shared__ cx<T> tws[N];
+    if (blockIdx.y & 1) {
+        const DualArgs<T> a = dual[blockIdx.y >> 1];
+        if (!a.on) return;
+        c2c_view_dual_body<T, N, W>(a.va, a.vb, a.dst2a, a.dst2b, a.tw, buf, tws);
+    } else {
+        const C2cArgs<T> a = inv[blockIdx.y >> 1];
+        if (!a.on) return;
+        c2c_view_body<T, N, W, -1>(a.va, a.vb, a.tw, buf, tws);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -926,6 +961,14 @@ static void c2r_rows_n(T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>* 
     ML_LAUNCH((k_c2r_rows<T, H, W>), nrows / W, st, io, nyq, tw_h, tw_post, mul_k2);
 }
 
+template <class T, int H>
+static void c2r_rows3_n(PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+                        long nrows, hipStream_t st) {
+    constexpr int W = rows_w<T>(2 * H);
+    hipLaunchKernelGGL((k_c2r_rows3<T, H, W>), dim3(nrows / W, 3), dim3(NT), 0, st, io, nyq, tw_h,
+                       tw_post);
+}
+
 template <class T, int N, int S>
 static void c2c_axis1_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
     constexpr int W = lanes_w<T>(N);
@@ -941,6 +984,17 @@ static void c2c_axis1_dual_n(cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2,
     ViewDesc va{main, N / 2, 0, (int)((long)N * (N / 2) / W)};
     ViewDesc vb{nyq, 1, 1, N / W};
     ML_LAUNCH((k_c2c_view_dual<T, N, W>), va.n_wg + vb.n_wg, st, va, vb, main2, nyq2, tw);
+}
+
+template <class T, int N>
+static void c2c_axis1_inv_dual_n(cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
+                                 cx<T>* nyq2, const cx<T>* tw, hipStream_t st) {
+    constexpr int W = lanes_w<T>(N);
+    const int n_main = (int)((long)N * (N / 2) / W);
+    ViewDesc ia{main0, N / 2, 0, n_main}, ib{nyq0, 1, 1, N / W};
+    ViewDesc va{main, N / 2, 0, n_main}, vb{nyq, 1, 1, N / W};
+    hipLaunchKernelGGL((k_c2c_inv_dual<T, N, W>), dim3(n_main + N / W, 2), dim3(NT), 0, st, ia, ib,
+                       va, vb, main2, nyq2, tw);
 }
 
 template <class T, int N, int S>
@@ -1011,6 +1065,16 @@ void fft_c2r_rows(int n, T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>
 }
 
 template <class T>
+void fft_c2r_rows3(int n, PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+                   hipStream_t st) {
+    long rows = (long)n * n;
+#define ML_CASE(v) if (n == v) return c2r_rows3_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st);
+    if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
+    else { ML_SIZES_D(ML_CASE) }
+#undef ML_CASE
+}
+
+template <class T>
 void fft_c2c_axis1(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
 #define ML_CASE(v)                                                                  \
     if (n == v) {                                                                   \
@@ -1030,6 +1094,19 @@ void fft_c2c_axis1_dual(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
+}
+
+// From 512 up each pass fills the GPU by itself and the two are launched
+// apart (a projection can then start between them).
+template <class T>
+void fft_c2c_axis1_inv_dual(int n, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
+                            cx<T>* nyq2, const cx<T>* tw, hipStream_t st) {
+#define ML_CASE(v) \
+    if (n == v) return c2c_axis1_inv_dual_n<T, v>(main0, nyq0, main, nyq, main2, nyq2, tw, st);
+    ML_SIZES_D(ML_CASE)
+#undef ML_CASE
+    fft_c2c_axis1<T>(n, -1, main0, nyq0, tw, st);
+    fft_c2c_axis1_dual<T>(n, main, nyq, main2, nyq2, tw, st);
 }
 
 template <class T>
@@ -1121,10 +1198,11 @@ static void c2c_axis1_batch_n(const C2cArgs<T>* tab, int slots, hipStream_t st) 
     hipLaunchKernelGGL((k_c2c_view_b<T, N, W, S>), dim3(nwg, slots), dim3(NT), 0, st, tab);
 }
 template <class T, int N>
-static void c2c_axis1_dual_batch_n(const DualArgs<T>* tab, int slots, hipStream_t st) {
+static void c2c_axis1_inv_dual_batch_n(const C2cArgs<T>* inv, const DualArgs<T>* dual, int slots,
+                                       hipStream_t st) {
     constexpr int W = lanes_w<T>(N);
     const int nwg = (int)((long)N * (N / 2) / W) + N / W;
-    hipLaunchKernelGGL((k_c2c_view_dual_b<T, N, W>), dim3(nwg, slots), dim3(NT), 0, st, tab);
+    hipLaunchKernelGGL((k_c2c_inv_dual_b<T, N, W>), dim3(nwg, 2 * slots), dim3(NT), 0, st, inv, dual);
 }
 template <class T, int N>
 static void grad_axis0_batch_n(const GradArgs<T>* tab, int slots, hipStream_t st) {
@@ -1165,8 +1243,9 @@ void fft_c2c_axis1_batch(int n, int sign, const C2cArgs<T>* tab, int slots, hipS
 }
 
 template <class T>
-void fft_c2c_axis1_dual_batch(int n, const DualArgs<T>* tab, int slots, hipStream_t st) {
-#define ML_CASE(v) if (n == v) return c2c_axis1_dual_batch_n<T, v>(tab, slots, st);
+void fft_c2c_axis1_inv_dual_batch(int n, const C2cArgs<T>* inv, const DualArgs<T>* dual, int slots,
+                                  hipStream_t st) {
+#define ML_CASE(v) if (n == v) return c2c_axis1_inv_dual_batch_n<T, v>(inv, dual, slots, st);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
@@ -1189,7 +1268,8 @@ void fft_grad_axis0_batch(int n, const GradArgs<T>* tab, int slots, hipStream_t 
     template void fft_r2c_rows_batch<T>(int, const R2cArgs<T>*, int, hipStream_t);                \
     template void fft_c2r_rows_batch<T>(int, const C2rArgs<T>*, int, hipStream_t);                \
     template void fft_c2c_axis1_batch<T>(int, int, const C2cArgs<T>*, int, hipStream_t);          \
-    template void fft_c2c_axis1_dual_batch<T>(int, const DualArgs<T>*, int, hipStream_t);         \
+    template void fft_c2c_axis1_inv_dual_batch<T>(int, const C2cArgs<T>*, const DualArgs<T>*, int, \
+                                                  hipStream_t);                                   \
     template void fft_grad_axis0_batch<T>(int, const GradArgs<T>*, int, hipStream_t);
 ML_INST_BATCH(float)
 ML_INST_BATCH(double)
@@ -1202,6 +1282,10 @@ ML_INST_BATCH(double)
                                   HaloMerge<T>);                                                  \
     template void fft_c2r_rows<T>(int, T*, const cx<T>*, const cx<T>*, const cx<T>*, hipStream_t,  \
                                   bool);                                                          \
+    template void fft_c2r_rows3<T>(int, PtrTriple, PtrTriple, const cx<T>*, const cx<T>*,          \
+                                   hipStream_t);                                                  \
+    template void fft_c2c_axis1_inv_dual<T>(int, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*,   \
+                                            const cx<T>*, hipStream_t);                           \
     template void fft_c2c_axis1<T>(int, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
     template void fft_c2c_axis1_dual<T>(int, cx<T>*, cx<T>*, cx<T>*, cx<T>*, const cx<T>*,          \
                                         hipStream_t);                                             \

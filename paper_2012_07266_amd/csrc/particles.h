@@ -164,16 +164,19 @@ void launch_readout_tangent(Parts<T> p, SortBufs s, Geo g, const T* f0, const T*
                             T kick, int do_kick, uint32_t* status, const TanGather<T>& tg,
                             hipStream_t st);
 // Zel'dovich: disp = dfac*s, mom = pfac*s from the three displacement meshes
-// on the particle lattice (cells), id = lattice index.
+// on the particle lattice (cells), id = lattice index; then the particles'
+// sort keys and histogram (count must be zero).
 template <class T>
-void launch_init_ic(Parts<T> p, Geo g, const T* s0, const T* s1, const T* s2, T dfac, T pfac,
-                    hipStream_t st);
+void launch_init_ic(Parts<T> p, SortBufs s, Geo g, const T* s0, const T* s1, const T* s2, T dfac,
+                    T pfac, uint32_t* status, hipStream_t st);
 // State out in lattice order: x in [0, box) and p (Mpc/h), acc (Mpc/h).
 template <class T>
 void launch_get_state(Parts<T> p, Geo g, T cell, T* x, T* mom_out, T* acc_out, hipStream_t st);
-// State in (lattice order, Mpc/h) -> displacement (minimum image), momentum.
+// State in (lattice order, Mpc/h) -> displacement (minimum image), momentum;
+// then the particles' sort keys and histogram (count must be zero).
 template <class T>
-void launch_set_state(Parts<T> p, Geo g, T cell, const T* x, const T* mom_in, hipStream_t st);
+void launch_set_state(Parts<T> p, SortBufs s, Geo g, T cell, const T* x, const T* mom_in,
+                      uint32_t* status, hipStream_t st);
 // N(0,1) noise [n] from Philox4x64-10 keyed by (seed, 0) and Box-Muller
 template <class T>
 void launch_noise(T* out, long n, uint64_t seed, hipStream_t st);

@@ -55,20 +55,6 @@ void launch_fill(T* p, T v, long n, hipStream_t st) {
 }
 void launch_fill_u32(uint32_t* p, uint32_t v, long n, hipStream_t st) { launch_fill<uint32_t>(p, v, n, st); }
 
-__global__ void k_fill_b(const FillArgs* __restrict__ tab) {
-    const FillArgs a = tab[blockIdx.y];
-    if (!a.on) return;
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < a.n; i += (long)gridDim.x * blockDim.x)
-        a.p[i] = 0u;
-}
-
-void launch_fill_batch(const FillArgs* tab, long n_max, int slots, hipStream_t st) {
-    long blocks = (n_max + PB - 1) / PB;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_fill_b, dim3(blocks, slots), dim3(PB), 0, st, tab);
-}
-
 template <class T>
 __global__ void k_scale_copy(T* dst, const T* src, T s, long n) {
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
@@ -292,7 +278,40 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_add_b(const ScanArgs* __restric
     scan_add_body(a.start, a.block_sum, a.n, nblocks);
 }
 
+// Up to SCAN_ONE counts in one workgroup and one launch: each thread scans a
+// run of them.  Two launches of a workgroup per 1024 counts take 9 us at any
+// size (the launches); this takes 5 at 8192 counts, and more beyond.
+constexpr int SCAN_ONE = 8192;
+__device__ __forceinline__ void scan_one_body(const uint32_t* count, uint32_t* start, int n) {
+    constexpr int PT = SCAN_ONE / SCAN_T;
+    const int i0 = threadIdx.x * PT;
+    uint32_t v[PT], sum = 0, total;
+#pragma unroll
+    for (int j = 0; j < PT; ++j) v[j] = i0 + j < n ? count[i0 + j] : 0u;
+#pragma unroll
+    for (int j = 0; j < PT; ++j) sum += v[j];
+    uint32_t e = block_exclusive_scan(sum, &total);
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+        if (i0 + j < n) start[i0 + j] = e;
+        e += v[j];
+    }
+    if (threadIdx.x == 0) start[n] = total;
+}
+__global__ __launch_bounds__(SCAN_T) void k_scan_one(const uint32_t* count, uint32_t* start, int n) {
+    scan_one_body(count, start, n);
+}
+__global__ __launch_bounds__(SCAN_T) void k_scan_one_b(const ScanArgs* __restrict__ tab) {
+    const ScanArgs a = tab[blockIdx.y];
+    if (!a.on) return;
+    scan_one_body(a.count, a.start, a.n);
+}
+
 void launch_scan_batch(const ScanArgs* tab, int n, int slots, hipStream_t st) {
+    if (n <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one_b, dim3(1, slots), dim3(SCAN_T), 0, st, tab);
+        return;
+    }
     const int nb = (n + SCAN_T - 1) / SCAN_T;
     hipLaunchKernelGGL(k_scan_blocks_b, dim3(nb, slots), dim3(SCAN_T), 0, st, tab);
     hipLaunchKernelGGL(k_scan_add_b, dim3(nb, slots), dim3(SCAN_T), 0, st, tab, nb);
@@ -300,6 +319,10 @@ void launch_scan_batch(const ScanArgs* tab, int n, int slots, hipStream_t st) {
 
 void launch_scan(const uint32_t* count, uint32_t* start, uint32_t* block_sum, int n,
                  hipStream_t st) {
+    if (n <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(SCAN_T), 0, st, count, start, n);
+        return;
+    }
     const int nb = (n + SCAN_T - 1) / SCAN_T;
     hipLaunchKernelGGL(k_scan_blocks, dim3(nb), dim3(SCAN_T), 0, st, count, start, block_sum, n);
     hipLaunchKernelGGL(k_scan_add, dim3(nb), dim3(SCAN_T), 0, st, start, block_sum, n, nb);
@@ -949,29 +972,62 @@ void launch_readout(Parts<T> p, SortBufs s, Geo g, const T* f0, const T* f1, con
 // ---------------------------------------------------------------------------
 // initial conditions and state conversion
 // ---------------------------------------------------------------------------
+// A new state's particle: its displacement checked, stored with its momentum
+// and id, its sort key and histogram count.  A pass of its own for the keys
+// (k_kick_drift_key) would read and write the displacements again: 0.22 ms at
+// 256^3 particles.  Every lane of the wave must call it.
 template <class T>
-__global__ void k_init_ic(Parts<T> p, Geo g, const T* s0, const T* s1, const T* s2, T dfac,
-                          T pfac) {
-    const long n = g.npart;
-    for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-        T v[3] = {s0[k], s1[k], s2[k]};
+__device__ __forceinline__ void store_new(const Parts<T>& p, const SortBufs& s, const Geo& g, long n,
+                                          long k, bool valid, T (&d)[3], const T (&m)[3],
+                                          uint32_t id, uint32_t* status) {
+    uint32_t key = 0;
+    if (valid) {
+        if (!finite3(d[0], d[1], d[2])) {
+            atomicOr(status, 1u);
+            d[0] = d[1] = d[2] = T(0);
+        }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            p.disp[a * n + k] = dfac * v[a];
-            p.mom[a * n + k] = pfac * v[a];
-            p.acc[a * n + k] = T(0);
+            p.disp[a * n + k] = d[a];
+            p.mom[a * n + k] = m[a];
         }
-        int i2 = (int)(k % g.np), i1 = (int)((k / g.np) % g.np), i0 = (int)(k / ((long)g.np * g.np));
-        p.id[k] = pack_id(i0, i1, i2);
+        p.id[k] = id;
+        key = tile_key<T>(id, d, g);
+        s.key[k] = key;
+    }
+    wave_count(valid, key, s.count);
+}
+
+template <class T>
+__global__ __launch_bounds__(PB) void k_init_ic(Parts<T> p, SortBufs s, Geo g, const T* s0,
+                                                const T* s1, const T* s2, T dfac, T pfac,
+                                                uint32_t* status) {
+    const long n = g.npart;
+    for (long base = blockIdx.x * (long)PB; base < n; base += (long)gridDim.x * PB) {
+        const long k = base + threadIdx.x;
+        const bool valid = k < n;
+        T d[3], m[3];
+        uint32_t id = 0;
+        if (valid) {
+            const T v[3] = {s0[k], s1[k], s2[k]};
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                d[a] = dfac * v[a];
+                m[a] = pfac * v[a];
+            }
+            id = pack_id((int)(k / ((long)g.np * g.np)), (int)((k / g.np) % g.np), (int)(k % g.np));
+        }
+        store_new<T>(p, s, g, n, k, valid, d, m, id, status);
     }
 }
 
 template <class T>
-void launch_init_ic(Parts<T> p, Geo g, const T* s0, const T* s1, const T* s2, T dfac, T pfac,
-                    hipStream_t st) {
+void launch_init_ic(Parts<T> p, SortBufs s, Geo g, const T* s0, const T* s1, const T* s2, T dfac,
+                    T pfac, uint32_t* status, hipStream_t st) {
     long blocks = (g.npart + PB - 1) / PB;
     if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_init_ic<T>, dim3(blocks), dim3(PB), 0, st, p, g, s0, s1, s2, dfac, pfac);
+    hipLaunchKernelGGL(k_init_ic<T>, dim3(blocks), dim3(PB), 0, st, p, s, g, s0, s1, s2, dfac, pfac,
+                       status);
 }
 
 template <class T>
@@ -1006,29 +1062,38 @@ void launch_get_state(Parts<T> p, Geo g, T cell, T* x, T* mom_out, T* acc_out, h
 }
 
 template <class T>
-__global__ void k_set_state(Parts<T> p, Geo g, T cell, const T* x, const T* mi) {
+__global__ __launch_bounds__(PB) void k_set_state(Parts<T> p, SortBufs s, Geo g, T cell, const T* x,
+                                                  const T* mi, uint32_t* status) {
     const long n = g.npart;
     const T nmf = T(g.nm);
-    for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-        int i[3] = {(int)(k / ((long)g.np * g.np)), (int)((k / g.np) % g.np), (int)(k % g.np)};
+    for (long base = blockIdx.x * (long)PB; base < n; base += (long)gridDim.x * PB) {
+        const long k = base + threadIdx.x;
+        const bool valid = k < n;
+        T dv[3], m[3];
+        uint32_t id = 0;
+        if (valid) {
+            int i[3] = {(int)(k / ((long)g.np * g.np)), (int)((k / g.np) % g.np), (int)(k % g.np)};
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            T u = x[a * n + k] / cell;
-            T d = u - (T(g.B * i[a]) + T(0.5));
-            d -= nmf * floor(d / nmf + T(0.5));  // minimum image, [-nm/2, nm/2)
-            p.disp[a * n + k] = d;
-            p.mom[a * n + k] = mi[a * n + k] / cell;
-            p.acc[a * n + k] = T(0);
+            for (int a = 0; a < 3; ++a) {
+                T u = x[a * n + k] / cell;
+                T d = u - (T(g.B * i[a]) + T(0.5));
+                d -= nmf * floor(d / nmf + T(0.5));  // minimum image, [-nm/2, nm/2)
+                dv[a] = d;
+                m[a] = mi[a * n + k] / cell;
+            }
+            id = pack_id(i[0], i[1], i[2]);
         }
-        p.id[k] = pack_id(i[0], i[1], i[2]);
+        store_new<T>(p, s, g, n, k, valid, dv, m, id, status);
     }
 }
 
 template <class T>
-void launch_set_state(Parts<T> p, Geo g, T cell, const T* x, const T* mom_in, hipStream_t st) {
+void launch_set_state(Parts<T> p, SortBufs s, Geo g, T cell, const T* x, const T* mom_in,
+                      uint32_t* status, hipStream_t st) {
     long blocks = (g.npart + PB - 1) / PB;
     if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_set_state<T>, dim3(blocks), dim3(PB), 0, st, p, g, cell, x, mom_in);
+    hipLaunchKernelGGL(k_set_state<T>, dim3(blocks), dim3(PB), 0, st, p, s, g, cell, x, mom_in,
+                       status);
 }
 
 // ---------------------------------------------------------------------------
@@ -1137,10 +1202,11 @@ ML_INST_BATCH(double)
     template void launch_readout_tangent<T>(Parts<T>, SortBufs, Geo, const T*, const T*,          \
                                             const T*, T, int, uint32_t*, const TanGather<T>&,     \
                                             hipStream_t);                                         \
-    template void launch_init_ic<T>(Parts<T>, Geo, const T*, const T*, const T*, T, T,            \
-                                    hipStream_t);                                                 \
+    template void launch_init_ic<T>(Parts<T>, SortBufs, Geo, const T*, const T*, const T*, T, T,  \
+                                    uint32_t*, hipStream_t);                                      \
     template void launch_get_state<T>(Parts<T>, Geo, T, T*, T*, T*, hipStream_t);                 \
-    template void launch_set_state<T>(Parts<T>, Geo, T, const T*, const T*, hipStream_t);    \
+    template void launch_set_state<T>(Parts<T>, SortBufs, Geo, T, const T*, const T*, uint32_t*, \
+                                      hipStream_t);                                               \
     template void launch_noise<T>(T*, long, uint64_t, hipStream_t);
 ML_INST(float)
 ML_INST(double)
