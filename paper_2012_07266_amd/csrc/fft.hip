@@ -207,6 +207,44 @@ __device__ __forceinline__ void reg_chain(cx<T>* v, cx<T>* buf, const cx<T>* tw,
     }
 }
 
+// reg_chain with the exchange in two halves, the real parts and then the
+// imaginary parts through one buffer of N (W + 1) values: half the LDS for
+// twice the barriers, where other workgroups can use the LDS.
+template <class T, int N, int W, int S, int STAGE, int NTT = NT>
+__device__ __forceinline__ void reg_chain_split(cx<T>* v, T* buf, const cx<T>* tw, int tid) {
+    if constexpr (STAGE < num_stages(N)) {
+        constexpr int LD = W + 1;
+        constexpr int RP = plan_radix(N, STAGE - 1), PP = span_before(N, STAGE - 1);
+        constexpr int R = plan_radix(N, STAGE), P = span_before(N, STAGE);
+        constexpr int ITP = (N / RP) * W / NTT, IT = (N / R) * W / NTT;
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int it = 0; it < ITP; ++it) {
+                const int b = tid + it * NTT, w = b % W, i = b / W, k = i % PP;
+                const int j = (i - k) * RP + k;
+#pragma unroll
+                for (int r = 0; r < RP; ++r)
+                    buf[(j + r * PP) * LD + w] = part ? v[it * RP + r].im : v[it * RP + r].re;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const int b = tid + it * NTT, w = b % W, i = b / W;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const T x = buf[(i + r * (N / R)) * LD + w];
+                    if (part) v[it * R + r].im = x;
+                    else v[it * R + r].re = x;
+                }
+            }
+            __syncthreads();
+        }
+        reg_compute<T, N, W, R, P, S, NTT>(v, tw, tid);
+        reg_chain_split<T, N, W, S, STAGE + 1, NTT>(v, buf, tw, tid);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // pass 1: r2c along the contiguous axis.  H = Nm/2.
 // `io` holds nrows rows of 2H reals on input and H complex on output.
@@ -540,6 +578,12 @@ __global__ __launch_bounds__(NT) void k_c2c_view_b(const C2cArgs<T>* __restrict_
 //   out2:      IFFT1(H)
 // (the gradient components along axes 1 and 2 of the fused axis-0 pass).
 // `dst2a`/`dst2b` are the bases of the second output matching va / vb.
+// The pass moves 3 spectra and is bound by HBM, so where a thread's share of
+// H is at most 24 values it stays in registers between the two transforms
+// (reading it again misses L2 and adds a fourth to the traffic).  384^3: 0.22
+// -> 0.16 ms.  At 512 (32 values of 256 threads) neither that nor 512 threads
+// of 16 values are faster than the second read (17.25-17.38 against 17.21 ms
+// for four steps at 256^3/512^3): too few waves are left to cover it.
 // ---------------------------------------------------------------------------
 template <class T, int N>
 __device__ __forceinline__ T n1_mult(int n) {
@@ -547,11 +591,12 @@ __device__ __forceinline__ T n1_mult(int n) {
     return n == HN ? T(0) : T(n <= HN ? n : n - N);
 }
 
-template <class T, int N, int W>
+template <int N, int W> constexpr bool dual_holds() { return W * N / NT <= 24; }
+
+template <class T, int N, int W, bool SPLIT = false>
 __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
                                                       cx<T>* dst2b, const cx<T>* tw,
                                                       cx<T>* buf, cx<T>* tws) {
-    constexpr int LD = W + 1;
     const int tid = threadIdx.x;
     int g = view_wg<T, W, true>(blockIdx.x, gridDim.x);
     const bool is_a = g < va.n_wg;
@@ -580,26 +625,37 @@ __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<
                     r[it * R0 + q] = src[(long)(it * (NT / W) + q * (N / R0)) * C];
             twr.store(tws, tid);
             __syncthreads();  // twiddles in LDS
+            // HOLD: H stays in registers for the second transform
+            constexpr bool HOLD = dual_holds<N, W>();
+            cx<T> h[HOLD ? E : 1];
+            if constexpr (HOLD) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) h[e] = r[e];
+            }
             reg_compute<T, N, W, R0, 1, -1>(r, tws, tid);
-            reg_chain<T, N, W, -1, 1>(r, buf, tws, tid);
+            if constexpr (SPLIT)
+                reg_chain_split<T, N, W, -1, 1>(r, reinterpret_cast<T*>(buf), tws, tid);
+            else reg_chain<T, N, W, -1, 1>(r, buf, tws, tid);
             cx<T>* d2 = dst2 + tbase;
 #pragma unroll
             for (int it = 0; it < E / RL; ++it)
 #pragma unroll
                 for (int q = 0; q < RL; ++q)
                     d2[(long)(it * (NT / W) + q * (N / RL)) * C] = r[it * RL + q];
-            // reload H (this workgroup's pencils, still in L2) scaled by n1
 #pragma unroll
             for (int it = 0; it < E / R0; ++it)
 #pragma unroll
                 for (int q = 0; q < R0; ++q) {
                     const int n = tid / W + it * (NT / W) + q * (N / R0);
-                    r[it * R0 + q] =
-                        scale(src[(long)(it * (NT / W) + q * (N / R0)) * C], n1_mult<T, N>(n));
+                    const cx<T> x = HOLD ? h[HOLD ? it * R0 + q : 0]
+                                         : src[(long)(it * (NT / W) + q * (N / R0)) * C];
+                    r[it * R0 + q] = scale(x, n1_mult<T, N>(n));
                 }
             __syncthreads();  // the first transform is done with buf
             reg_compute<T, N, W, R0, 1, -1>(r, tws, tid);
-            reg_chain<T, N, W, -1, 1>(r, buf, tws, tid);
+            if constexpr (SPLIT)
+                reg_chain_split<T, N, W, -1, 1>(r, reinterpret_cast<T*>(buf), tws, tid);
+            else reg_chain<T, N, W, -1, 1>(r, buf, tws, tid);
             cx<T>* d1 = reinterpret_cast<cx<T>*>(v.ptr) + tbase;
 #pragma unroll
             for (int it = 0; it < E / RL; ++it)
@@ -610,30 +666,41 @@ __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<
         }
     }
     // LDS path: transform H, store it to out2; reload H scaled by n1,
-    // transform, store in place
-    view_load<T, N, W>(buf, v, g, tid);
-    twr.store(tws, tid);
-    __syncthreads();
-    fft_lds<T, N, W, -1>(buf, tws, tid);
-    view_store<T, N, W>(buf, dst2, v, g, tid);
-    __syncthreads();
-    view_load<T, N, W>(buf, v, g, tid);
-    __syncthreads();
-    for (int f = tid; f < N * W; f += NT) {
-        int n = f / W, w = f % W;
-        buf[n * LD + w] = scale(buf[n * LD + w], n1_mult<T, N>(n));
+    // transform, store in place (with SPLIT, where buf holds half the values
+    // of W pencils, for a quarter of them at a time)
+    constexpr int WL = SPLIT ? W / 4 : W, LD = WL + 1;
+    for (int sub = 0; sub < W / WL; ++sub) {
+        const int gs = g * (W / WL) + sub;
+        view_load<T, N, WL>(buf, v, gs, tid);
+        if (sub == 0) twr.store(tws, tid);
+        __syncthreads();
+        fft_lds<T, N, WL, -1>(buf, tws, tid);
+        view_store<T, N, WL>(buf, dst2, v, gs, tid);
+        __syncthreads();
+        view_load<T, N, WL>(buf, v, gs, tid);
+        __syncthreads();
+        for (int f = tid; f < N * WL; f += NT) {
+            int n = f / WL, w = f % WL;
+            buf[n * LD + w] = scale(buf[n * LD + w], n1_mult<T, N>(n));
+        }
+        __syncthreads();
+        fft_lds<T, N, WL, -1>(buf, tws, tid);
+        view_store<T, N, WL>(buf, v.ptr, v, gs, tid);
+        __syncthreads();
     }
-    __syncthreads();
-    fft_lds<T, N, W, -1>(buf, tws, tid);
-    view_store<T, N, W>(buf, v.ptr, v, g, tid);
 }
 
 template <class T, int N, int W>
 __global__ __launch_bounds__(NT) void k_c2c_view_dual(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
                                                       cx<T>* dst2b, const cx<T>* tw) {
-    __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
+    // Where H is held (registers then leave two workgroups per CU) the values
+    // are exchanged in halves, and half the LDS is left to the projection's
+    // workgroups on the other stream: 8.05 -> 7.83 ms for four steps at
+    // 192^3/384^3.
+    constexpr bool SPLIT = N > 256 && reg_path_ok<N, W>() && dual_holds<N, W>();
+    __shared__ T buf[(SPLIT ? 1 : 2) * N * (W + 1)];  // the pencils, and the twiddles
     __shared__ cx<T> tws[N];
-    c2c_view_dual_body<T, N, W>(va, vb, dst2a, dst2b, tw, buf, tws);
+    c2c_view_dual_body<T, N, W, SPLIT>(va, vb, dst2a, dst2b, tw, reinterpret_cast<cx<T>*>(buf), tws);
 }
 // The inverse pass of one component (blockIdx.y even) and the dual pass of the
 // other two (odd) in one launch, for meshes at which a pass alone leaves the
