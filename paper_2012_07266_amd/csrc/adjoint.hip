@@ -104,10 +104,12 @@ __device__ __forceinline__ long tile_offset(int i, int nm, int ox, int oy, int o
 // Stage the 17^3 boxes of NM meshes into LDS.  Every load of the batch is
 // issued before the first LDS store (slots past the box repeat its last
 // entry and are not stored): a loop that stores each value as it arrives
-// waits for every load in turn.
-template <class T, int NM>
+// waits for every load in turn.  `then` runs between the box's loads and its
+// LDS stores: a kernel issues its first particles' loads there, so that they
+// are in flight together with the box and not a round trip behind it.
+template <class T, int NM, class F>
 __device__ __forceinline__ void stage_tiles(T (*ft)[TE * TE * TE], const T* const (&mesh)[NM],
-                                            int nm, int ox, int oy, int oz, int tid) {
+                                            int nm, int ox, int oy, int oz, int tid, F then) {
     constexpr int TC = TE * TE * TE;
     constexpr int IT = (TC + AB - 1) / AB;
     T v[NM][IT];
@@ -119,6 +121,8 @@ __device__ __forceinline__ void stage_tiles(T (*ft)[TE * TE * TE], const T* cons
 #pragma unroll
         for (int m = 0; m < NM; ++m) v[m][it] = mesh[m][c];
     }
+    issue_fence();
+    then();
     issue_fence();
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -149,30 +153,44 @@ __global__ __launch_bounds__(AB) void k_fvjp_readout(Parts<T> p, SortBufs s, Geo
     const int b0 = tile_block(g, tx, ty, tz);
     const uint32_t lo = s.start[b0], hi = s.start[b0 + BPT];
     if (lo == hi) return;
+    const long n = g.npart;
+    // a thread's particle (past the end the last one, not used)
+    uint32_t id = p.id[min(lo + tid, hi - 1u)];
+    T d[3], pin[3], xin[3], ac[3];
+    const auto load = [&](uint32_t k) {
+        const long L = lattice_index(id, g.np);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d[a] = p.disp[a * n + k];
+            ac[a] = p.acc[a * n + k];
+            pin[a] = pbar_in[a * n + L];
+            xin[a] = xbar_in[a * n + L];
+        }
+    };
     {
         const T* const fm[3] = {f0, f1, f2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid);
+        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
-    const long n = g.npart;
     double dot = 0.0;
     float fmax = 0.f;
     for (uint32_t k0 = lo; k0 < hi; k0 += AB) {
         uint32_t k = k0 + tid;
+        if (k0 != lo) {
+            id = p.id[min(k, hi - 1u)];
+            load(min(k, hi - 1u));
+        }
         if (k < hi) {
-            uint32_t id = p.id[k];
-            long L = lattice_index(id, g.np);
-            T d[3] = {p.disp[k], p.disp[n + k], p.disp[2 * n + k]};
             int base;
             T w[3][2];
             cic_setup(g, id, d, ox, oy, oz, base, w);
             T xb[3], fb[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                T pb = H * pbar_in[a * n + L];
-                xb[a] = H * xbar_in[a * n + L];
+                T pb = H * pin[a];
+                xb[a] = H * xin[a];
                 fb[a] = ckick * pb;
-                dot += (double)pb * (double)p.acc[a * n + k];
+                dot += (double)pb * (double)ac[a];
                 fmax = fmaxf(fmax, fabsf((float)fb[a]));
             }
 #pragma unroll
@@ -214,19 +232,36 @@ __global__ __launch_bounds__(AB) void k_fvjp_paintgrad(Parts<T> p, SortBufs s, G
     const int b0 = tile_block(g, tx, ty, tz);
     const uint32_t lo = s.start[b0], hi = s.start[b0 + BPT];
     if (lo == hi) return;
+    const long n = g.npart;
+    // a thread's particle (past the end the last one, not used)
+    uint32_t id = p.id[min(lo + tid, hi - 1u)];
+    T d[3], xc[3], pin[3], mo[3], ac[3], ph_in[3];
+    const auto load = [&](uint32_t k) {
+        const long L = lattice_index(id, g.np);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d[a] = p.disp[a * n + k];
+            xc[a] = xbc[a * n + k];
+            mo[a] = p.mom[a * n + k];
+            if (mode == 0) ac[a] = p.acc[a * n + k];
+            pin[a] = pbar_in[a * n + L];
+            ph_in[a] = phbar ? phbar[a * n + L] : T(0);
+        }
+    };
     {
         const T* const fm[1] = {rhobar};
-        stage_tiles<T, 1>(ft, fm, g.nm, ox, oy, oz, tid);
+        stage_tiles<T, 1>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
-    const long n = g.npart;
     double a1 = 0.0, a2 = 0.0, a3 = 0.0;
     for (uint32_t k0 = lo; k0 < hi; k0 += AB) {
         uint32_t k = k0 + tid;
+        if (k0 != lo) {
+            id = p.id[min(k, hi - 1u)];
+            load(min(k, hi - 1u));
+        }
         if (k < hi) {
-            uint32_t id = p.id[k];
-            long L = lattice_index(id, g.np);
-            T d[3] = {p.disp[k], p.disp[n + k], p.disp[2 * n + k]};
+            const long L = lattice_index(id, g.np);
             int base;
             T w[3][2];
             cic_setup(g, id, d, ox, oy, oz, base, w);
@@ -235,22 +270,22 @@ __global__ __launch_bounds__(AB) void k_fvjp_paintgrad(Parts<T> p, SortBufs s, G
             T xb[3], pb[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                xb[a] = xbc[a * n + k] + mass * gr[a];
-                pb[a] = H * pbar_in[a * n + L];
+                xb[a] = xc[a] + mass * gr[a];
+                pb[a] = H * pin[a];
             }
             if (mode == 0) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    T ph = p.mom[a * n + k] - k2 * p.acc[a * n + k];
+                    T ph = mo[a] - k2 * ac[a];
                     a1 += (double)xb[a] * (double)ph;
                     xbar_out[a * n + L] = xb[a] / H;
-                    pbar_out[a * n + L] = (pb[a] + dr * xb[a]) / H + (phbar ? phbar[a * n + L] : T(0));
+                    pbar_out[a * n + L] = (pb[a] + dr * xb[a]) / H + ph_in[a];
                 }
             } else {
                 T* sbo[3] = {sb0, sb1, sb2};
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    T sv = p.mom[a * n + k] / gp0;
+                    T sv = mo[a] / gp0;
                     T sbar = d0 * xb[a] + gp0 * pb[a];
                     a1 += (double)xb[a] * (double)sv;
                     a2 += (double)pb[a] * (double)sv;
@@ -310,6 +345,7 @@ __global__ __launch_bounds__(256) void k_map_sums(const T* kbar, long npix2, int
     __shared__ double red[4];
     for (int s = 0; s < nsrc; ++s) {
         double acc = 0.0;
+#pragma unroll 8
         for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < npix2; i += (long)gridDim.x * blockDim.x)
             acc += (double)kbar[(long)s * npix2 + i];
         block_add<256>(&dst[s], acc, red);
@@ -685,24 +721,34 @@ __global__ __launch_bounds__(AB) void k_fjvp_gather(Parts<T> p, SortBufs s, Geo 
     const int b0 = tile_block(g, tx, ty, tz);
     const uint32_t lo = s.start[b0], hi = s.start[b0 + BPT];
     if (lo == hi) return;
+    const long n = g.npart;
+    // a thread's particle (past the end the last one, not used)
+    uint32_t id;
+    T d[3], xd[3];
+    const auto load = [&](uint32_t k) {
+        id = p.id[k];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d[a] = p.disp[a * n + k];
+            xd[a] = xdot[a * n + k];
+        }
+    };
     {
         const T* const fm[3] = {f0, f1, f2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid);
+        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
-    const long n = g.npart;
     float vmax = 0.f;
     for (uint32_t k0 = lo; k0 < hi; k0 += AB) {
         uint32_t k = k0 + tid;
+        if (k0 != lo) load(min(k, hi - 1u));
         if (k < hi) {
-            uint32_t id = p.id[k];
-            T d[3] = {p.disp[k], p.disp[n + k], p.disp[2 * n + k]};
             int base;
             T w[3][2];
             cic_setup(g, id, d, ox, oy, oz, base, w);
             T ud[3];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) ud[a] = invH * xdot[a * n + k];
+            for (int a = 0; a < 3; ++a) ud[a] = invH * xd[a];
             vmax = fmaxf(vmax, (float)(mass * (fabs(ud[0]) + fabs(ud[1]) + fabs(ud[2]))));
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
@@ -733,17 +779,31 @@ __global__ __launch_bounds__(AB) void k_fjvp_readout_kick(Parts<T> p, SortBufs s
     const int b0 = tile_block(g, tx, ty, tz);
     const uint32_t lo = s.start[b0], hi = s.start[b0 + BPT];
     if (lo == hi) return;
+    const long n = g.npart;
+    // a thread's particle (past the end the last one, not used)
+    uint32_t id;
+    T d[3], fc[3], pd[3], ac[3];
+    const auto load = [&](uint32_t k) {
+        id = p.id[k];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            d[a] = p.disp[a * n + k];
+            fc[a] = fbc[a * n + k];
+            if (pdot) {
+                pd[a] = pdot[a * n + k];
+                ac[a] = p.acc[a * n + k];
+            }
+        }
+    };
     {
         const T* const fm[3] = {m0, m1, m2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid);
+        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
-    const long n = g.npart;
     for (uint32_t k0 = lo; k0 < hi; k0 += AB) {
         uint32_t k = k0 + tid;
+        if (k0 != lo) load(min(k, hi - 1u));
         if (k < hi) {
-            uint32_t id = p.id[k];
-            T d[3] = {p.disp[k], p.disp[n + k], p.disp[2 * n + k]};
             int base;
             T w[3][2];
             cic_setup(g, id, d, ox, oy, oz, base, w);
@@ -757,9 +817,9 @@ __global__ __launch_bounds__(AB) void k_fjvp_readout_kick(Parts<T> p, SortBufs s
 #pragma unroll
                         for (int c = 0; c < 2; ++c)
                             val += w[0][a] * w[1][b] * w[2][c] * ft[j][base + (a * TE + b) * TE + c];
-                const T fd = fbc[j * n + k] + val;
+                const T fd = fc[j] + val;
                 fdot[j * n + k] = H * fd;
-                if (pdot) pdot[j * n + k] += H * (k2 * fd + ck2 * p.acc[j * n + k]);
+                if (pdot) pdot[j * n + k] = pd[j] + H * (k2 * fd + ck2 * ac[j]);
             }
         }
     }
@@ -1005,8 +1065,10 @@ void launch_sorted_to_lattice(Parts<T> p, Geo g, const T* sorted, T* l0, T* l1, 
 template <class T>
 void launch_map_sums(const T* kbar, int npix, int nsrc, double* dst, hipStream_t st) {
     long npix2 = (long)npix * npix;
+    // one atomic per workgroup, all to one address (13 ns each): 2048
+    // workgroups took 27 us for a 1024^2 map, 256 take 8
     long blocks = (npix2 + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
+    if (blocks > 256) blocks = 256;
     hipLaunchKernelGGL(k_map_sums<T>, dim3(blocks), dim3(256), 0, st, kbar, npix2, nsrc, dst);
 }
 

@@ -1230,32 +1230,49 @@ template <class T> struct Sim final : SimBase {
         return b;
     }
 
+    // The arrays of a checkpoint and their places in it.
+    struct CkptPart {
+        void* arena;
+        size_t at, bytes;
+    };
+    std::vector<CkptPart> checkpoint_parts() const {
+        const size_t n = (size_t)geo.npart, es = sizeof(T), n3 = (size_t)P.nm * P.nm * P.nm;
+        std::vector<CkptPart> parts;
+        size_t at = 0;
+        const auto add = [&](void* p, size_t bytes) {
+            parts.push_back({p, at, bytes});
+            at += (bytes + 255) / 256 * 256;
+        };
+        add(cur.disp, 3 * n * es);
+        add(cur.mom, 3 * n * es);
+        add(cur.id, n * 4);
+        add(sb.start, ((size_t)ntiles + 1) * 4);
+        if (ckpt_force()) {
+            for (int j = 0; j < 3; ++j) add(mesh[j], n3 * es);
+            add(cur.acc, 3 * n * es);
+        }
+        return parts;
+    }
+    int checkpoint_copy(char* buf, bool save) {
+        CopyParts c;
+        const std::vector<CkptPart> parts = checkpoint_parts();
+        for (const CkptPart& p : parts)
+            save ? c.add(buf + p.at, p.arena, p.bytes) : c.add(p.arena, buf + p.at, p.bytes);
+        if (launch_copy_parts(c, st)) return PM_OK;
+        for (const CkptPart& p : parts)  // a buffer that is not aligned
+            HIPCHK(hipMemcpyAsync(save ? buf + p.at : (char*)p.arena, save ? (char*)p.arena : buf + p.at,
+                                  p.bytes, hipMemcpyDeviceToDevice, st));
+        return PM_OK;
+    }
+
     int checkpoint_save(void* buf) override {
         if (!buf) return PM_EINVAL;
         if (a_cur < 0) return PM_ESTATE;
-        const size_t n = (size_t)geo.npart, es = sizeof(T);
-        auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-        char* b = reinterpret_cast<char*>(buf);
-        HIPCHK(hipMemcpyAsync(b, cur.disp, 3 * n * es, hipMemcpyDeviceToDevice, st));
-        b += al(3 * n * es);
-        HIPCHK(hipMemcpyAsync(b, cur.mom, 3 * n * es, hipMemcpyDeviceToDevice, st));
-        b += al(3 * n * es);
-        HIPCHK(hipMemcpyAsync(b, cur.id, n * 4, hipMemcpyDeviceToDevice, st));
-        b += al(n * 4);
-        HIPCHK(hipMemcpyAsync(b, sb.start, ((size_t)ntiles + 1) * 4, hipMemcpyDeviceToDevice, st));
-        if (ckpt_force()) {
-            b += al(((size_t)ntiles + 1) * 4);
-            // every path that leaves the meshes valid has also left the
-            // accelerations of the current state (its readout wrote them)
-            if (!meshes_valid) force(T(0), 0);
-            const size_t n3 = (size_t)P.nm * P.nm * P.nm;
-            for (int j = 0; j < 3; ++j) {
-                HIPCHK(hipMemcpyAsync(b, mesh[j], n3 * es, hipMemcpyDeviceToDevice, st));
-                b += al(n3 * es);
-            }
-            HIPCHK(hipMemcpyAsync(b, cur.acc, 3 * n * es, hipMemcpyDeviceToDevice, st));
-        }
-        return check_launch();
+        // every path that leaves the meshes valid has also left the
+        // accelerations of the current state (its readout wrote them)
+        if (ckpt_force() && !meshes_valid) force(T(0), 0);
+        int rc = checkpoint_copy(reinterpret_cast<char*>(buf), true);
+        return rc ? rc : check_launch();
     }
 
     // Restore a checkpoint of this handle's shape at scale factor a: the
@@ -1264,28 +1281,10 @@ template <class T> struct Sim final : SimBase {
     // recomputed, as pm_set_state does.
     int checkpoint_load(const void* buf, double a) override {
         if (!buf || !(a > 0)) return PM_EINVAL;
-        const size_t n = (size_t)geo.npart, es = sizeof(T);
-        auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-        const char* b = reinterpret_cast<const char*>(buf);
-        HIPCHK(hipMemcpyAsync(cur.disp, b, 3 * n * es, hipMemcpyDeviceToDevice, st));
-        b += al(3 * n * es);
-        HIPCHK(hipMemcpyAsync(cur.mom, b, 3 * n * es, hipMemcpyDeviceToDevice, st));
-        b += al(3 * n * es);
-        HIPCHK(hipMemcpyAsync(cur.id, b, n * 4, hipMemcpyDeviceToDevice, st));
-        b += al(n * 4);
-        HIPCHK(hipMemcpyAsync(sb.start, b, ((size_t)ntiles + 1) * 4, hipMemcpyDeviceToDevice, st));
-        if (ckpt_force()) {
-            b += al(((size_t)ntiles + 1) * 4);
-            const size_t n3 = (size_t)P.nm * P.nm * P.nm;
-            for (int j = 0; j < 3; ++j) {
-                HIPCHK(hipMemcpyAsync(mesh[j], b, n3 * es, hipMemcpyDeviceToDevice, st));
-                b += al(n3 * es);
-            }
-            HIPCHK(hipMemcpyAsync(cur.acc, b, 3 * n * es, hipMemcpyDeviceToDevice, st));
-            meshes_valid = true;
-        } else {
-            force(T(0), 0);
-        }
+        int rc = checkpoint_copy(const_cast<char*>(reinterpret_cast<const char*>(buf)), false);
+        if (rc) return rc;
+        if (ckpt_force()) meshes_valid = true;
+        else force(T(0), 0);
         a_cur = a;
         ic_fresh = false;
         tan_valid = false;
@@ -1346,15 +1345,16 @@ template <class T> struct Sim final : SimBase {
           launch_fvjp_readout<T>(cur, sb, geo, mesh[0], mesh[1], mesh[2], xbar_in, pbar_in, H, ckick,
                                  xbc, fbc, dots, fmax_bits, st); }
         meshes_valid = false;
-        for (int j = 0; j < 3; ++j) {
-            ProfScope ps(prof, "vjp_paint_values");
-            launch_paint_values<T>(cur, sb, geo, T(1), mesh[j], halo, fbc + j * n, fmax_bits, st);
-        }
         const int nm = P.nm;
         const T gscale = (T)(1.0 / (2.0 * PI * (double)nm * (double)nm));
+        // each component's shells are merged by its r2c pass, before the next
+        // paint overwrites them
         for (int j = 0; j < 3; ++j) {
+            { ProfScope ps(prof, "vjp_paint_values");
+              launch_paint_values<T>(cur, sb, geo, T(1), mesh[j], halo, fbc + j * n, fmax_bits, st,
+                                     false); }
             ProfScope ps(prof, "fft_r2c_axis2");
-            fft_r2c_rows<T>(nm, mesh[j], nyq[j], tw_hm, twp_nm, st);
+            fft_r2c_rows<T>(nm, mesh[j], nyq[j], tw_hm, twp_nm, st, paint_halo_merge<T>(geo, halo));
         }
         for (int j = 0; j < 3; ++j) {
             ProfScope ps(prof, "fft_c2c_axis1_fwd");

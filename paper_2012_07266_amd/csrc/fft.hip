@@ -922,15 +922,16 @@ __global__ __launch_bounds__(NTG, (NTG == 512 ? 4 : 1)) void k_grad_x0_b(
 // = -i G sum_j n_j X_j (component j zero on its Nyquist plane), inverse FFT,
 // store one spectrum (may overwrite input 0).
 // ---------------------------------------------------------------------------
-template <class T, int N, int W>
-__global__ __launch_bounds__(NT) void k_div_x0(ViewDesc va, ViewDesc vb, PtrTriple ina,
-                                               PtrTriple inb, void* outa, void* outb,
-                                               const cx<T>* tw, const T* G, T gscale) {
+// Register path as in the gradient pass (the LDS path wrote and read every
+// value once more per stage and transform: 256^3 0.099 ms).
+template <class T, int N, int W, int NTG>
+__global__ __launch_bounds__(NTG, (NTG == 512 ? 4 : 1)) void k_div_x0(
+    ViewDesc va, ViewDesc vb, PtrTriple ina, PtrTriple inb, void* outa, void* outb, const cx<T>* tw,
+    const T* G, T gscale) {
     __shared__ cx<T> buf[N * (W + 1)];
     __shared__ cx<T> tws[N];
     constexpr int LD = W + 1;
     constexpr int HN = N / 2;
-    constexpr int IT = (W * N + NT - 1) / NT;
     const int tid = threadIdx.x;
     int g = view_wg<T, W, false>(blockIdx.x, gridDim.x);
     const bool is_a = g < va.n_wg;
@@ -938,8 +939,85 @@ __global__ __launch_bounds__(NT) void k_div_x0(ViewDesc va, ViewDesc vb, PtrTrip
     const PtrTriple& in = is_a ? ina : inb;
     void* out = is_a ? outa : outb;
     if (!is_a) g -= va.n_wg;
-    TwFetch<T, N> twr;
+    TwFetch<T, N, NTG> twr;
     twr.fetch(tw, tid);
+    if constexpr (reg_path_ok<N, W, NTG>()) {
+        constexpr int R0 = plan_radix(N, 0);
+        constexpr int RL = plan_radix(N, num_stages(N) - 1);
+        constexpr int PL = span_before(N, num_stages(N) - 1);
+        constexpr int E = W * N / NTG;
+        static_assert(NTG % W == 0, "a thread keeps one column");
+        const int wcol = tid % W;
+        const long tbase = view_offset<T, N, W>(v, g, wcol, tid / W);
+        const long C = v.C;
+        const long c = (long)g * W + wcol;
+        const int k1 = is_a ? (int)(c / HN) : (int)c;
+        const int k2 = is_a ? (int)(c % HN) : HN;
+        const int n1 = k1 <= HN ? k1 : k1 - N;
+        cx<T> acc[E];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const cx<T>* src = reinterpret_cast<const cx<T>*>(in.p[j]) + tbase;
+            cx<T> x[E];
+#pragma unroll
+            for (int it = 0; it < E / R0; ++it)
+#pragma unroll
+                for (int q = 0; q < R0; ++q)
+                    x[it * R0 + q] = src[(long)(it * (NTG / W) + q * (N / R0)) * C];
+            if (j == 0) {
+                twr.store(tws, tid);
+                __syncthreads();
+            }
+            reg_compute<T, N, W, R0, 1, 1, NTG>(x, tws, tid);
+            reg_chain<T, N, W, 1, 1, NTG>(x, buf, tws, tid);
+            // slot (it, q) of the last stage holds k0 = tid/W + it*(NTG/W) + q*N/RL
+#pragma unroll
+            for (int it = 0; it < E / RL; ++it)
+#pragma unroll
+                for (int q = 0; q < RL; ++q) {
+                    const int k0 = tid / W + it * (NTG / W) + q * (N / RL);
+                    const int n0 = k0 <= HN ? k0 : k0 - N;
+                    const int nj = j == 0 ? n0 : (j == 1 ? n1 : k2);
+                    const T m = (nj == HN || nj == -HN) ? T(0) : T(nj);
+                    const int e = it * RL + q;
+                    if (j == 0) {
+                        acc[e] = scale(x[e], m);
+                    } else {
+                        acc[e].re += m * x[e].re;
+                        acc[e].im += m * x[e].im;
+                    }
+                }
+        }
+#pragma unroll
+        for (int it = 0; it < E / RL; ++it)
+#pragma unroll
+            for (int q = 0; q < RL; ++q) {
+                const int k0 = tid / W + it * (NTG / W) + q * (N / RL);
+                const int n0 = k0 <= HN ? k0 : k0 - N;
+                const int nsq = n0 * n0 + n1 * n1 + k2 * k2;
+                const T gg = G ? G[nsq] : (nsq ? gscale / T(nsq) : T(0));
+                const cx<T> y = acc[it * RL + q];
+                acc[it * RL + q] = {gg * y.im, -gg * y.re};  // -i G y
+            }
+        if constexpr (RL != R0) {
+            reg_write_lds<T, N, W, RL, PL, NTG>(acc, buf, tid);
+            __syncthreads();
+            reg_read_lds<T, N, W, R0, NTG>(acc, buf, tid);
+            __syncthreads();
+        }
+        reg_compute<T, N, W, R0, 1, -1, NTG>(acc, tws, tid);
+        reg_chain<T, N, W, -1, 1, NTG>(acc, buf, tws, tid);
+        cx<T>* dst = reinterpret_cast<cx<T>*>(out) + tbase;
+#pragma unroll
+        for (int it = 0; it < E / RL; ++it)
+#pragma unroll
+            for (int q = 0; q < RL; ++q)
+                dst[(long)(it * (NTG / W) + q * (N / RL)) * C] = acc[it * RL + q];
+        return;
+    }
+    static_assert(NTG == NT || reg_path_ok<N, W, NTG>(), "LDS path needs NT threads");
+    if constexpr (NTG == NT) {
+    constexpr int IT = (W * N + NT - 1) / NT;
     cx<T> acc[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) acc[it] = {T(0), T(0)};
@@ -995,6 +1073,7 @@ __global__ __launch_bounds__(NT) void k_div_x0(ViewDesc va, ViewDesc vb, PtrTrip
     __syncthreads();
     fft_lds<T, N, W, -1>(buf, tws, tid);
     view_store<T, N, W>(buf, out, v, g, tid);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1094,7 +1173,8 @@ static void div_axis0_n(PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, cx
     constexpr int W = lanes_w<T>(N);
     ViewDesc va{in_main.p[0], (long)N * (N / 2), 0, (int)((long)N * (N / 2) / W)};
     ViewDesc vb{in_nyq.p[0], N, 0, N / W};
-    hipLaunchKernelGGL((k_div_x0<T, N, W>), dim3(va.n_wg + vb.n_wg), dim3(NT), 0, st, va, vb,
+    constexpr int NTG = (grad_nt<T>(N) == 512 && reg_path_ok<N, W, 512>()) ? 512 : NT;
+    hipLaunchKernelGGL((k_div_x0<T, N, W, NTG>), dim3(va.n_wg + vb.n_wg), dim3(NTG), 0, st, va, vb,
                        in_main, in_nyq, (void*)out_main, (void*)out_nyq, tw, G, gscale);
 }
 

@@ -80,6 +80,21 @@ void launch_fill(T* p, T v, long n, hipStream_t st);
 template <class T>
 void launch_scale_copy(T* dst, const T* src, T s, long n, hipStream_t st);
 void launch_fill_u32(uint32_t* p, uint32_t v, long n, hipStream_t st);
+// Device-to-device copies of arrays that do not overlap, in one launch;
+// false (nothing done) unless every address is a multiple of 16 and every
+// size of 4.
+struct CopyParts {
+    int n = 0;
+    void* dst[8];
+    const void* src[8];
+    size_t bytes[8];
+    void add(void* d, const void* s, size_t b) {
+        dst[n] = d;
+        src[n] = s;
+        bytes[n++] = b;
+    }
+};
+bool launch_copy_parts(const CopyParts& c, hipStream_t st);
 
 // mom += kick*acc (MODE_KICK), disp += drift*mom (MODE_DRIFT); then tile
 // key and histogram of every particle.  `count` must be zero.

@@ -55,6 +55,46 @@ void launch_fill(T* p, T v, long n, hipStream_t st) {
 }
 void launch_fill_u32(uint32_t* p, uint32_t v, long n, hipStream_t st) { launch_fill<uint32_t>(p, v, n, st); }
 
+// Several copies in one launch (blockIdx.y: which), 16 bytes a thread and CU
+// of them in flight.  A checkpoint of 128^3/256^3 with its force, eight arrays
+// and 0.27 GB: 123 us as copies of their own (4.4 TB/s), 95 in one launch.
+__global__ __launch_bounds__(PB) void k_copy_parts(CopyParts c) {
+    constexpr int CU = 4;
+    using V = uint32_t __attribute__((ext_vector_type(4)));
+    const V* s = reinterpret_cast<const V*>(c.src[blockIdx.y]);
+    V* d = reinterpret_cast<V*>(c.dst[blockIdx.y]);
+    const size_t n = c.bytes[blockIdx.y] / 16;
+    for (size_t base = (size_t)blockIdx.x * PB * CU; base < n; base += (size_t)gridDim.x * PB * CU) {
+        V v[CU];
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            const size_t i = base + u * PB + threadIdx.x;
+            v[u] = s[i < n ? i : n - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            const size_t i = base + u * PB + threadIdx.x;
+            if (i < n) d[i] = v[u];
+        }
+    }
+    const uint32_t* st = reinterpret_cast<const uint32_t*>(s + n);  // the last words
+    uint32_t* dt = reinterpret_cast<uint32_t*>(d + n);
+    if (blockIdx.x == 0 && threadIdx.x < (c.bytes[blockIdx.y] % 16) / 4) dt[threadIdx.x] = st[threadIdx.x];
+}
+
+bool launch_copy_parts(const CopyParts& c, hipStream_t st) {
+    size_t most = 0;
+    for (int i = 0; i < c.n; ++i) {
+        if (((uintptr_t)c.src[i] | (uintptr_t)c.dst[i]) % 16 || c.bytes[i] % 4) return false;
+        most = c.bytes[i] > most ? c.bytes[i] : most;
+    }
+    long blocks = (long)((most / 16 + PB * 4 - 1) / (PB * 4));
+    if (blocks > 2048) blocks = 2048;
+    if (blocks < 1) blocks = 1;
+    hipLaunchKernelGGL(k_copy_parts, dim3(blocks, c.n), dim3(PB), 0, st, c);
+    return true;
+}
+
 template <class T>
 __global__ void k_scale_copy(T* dst, const T* src, T s, long n) {
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
