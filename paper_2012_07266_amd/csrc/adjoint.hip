@@ -92,13 +92,13 @@ __device__ __forceinline__ void block_max(uint32_t* dst, float v, float* red) {
 
 // Global offset of entry i of a tile's 17^3 box at origin (ox, oy, oz),
 // periodic.
-__device__ __forceinline__ long tile_offset(int i, int nm, int ox, int oy, int oz) {
+__device__ __forceinline__ long tile_offset(int i, int nm, long px, int ox, int oy, int oz) {
     const int x = i / (TE * TE), y = (i / TE) % TE, z = i % TE;
     int gx = ox + x, gy = oy + y, gz = oz + z;
     if (gx >= nm) gx -= nm;
     if (gy >= nm) gy -= nm;
     if (gz >= nm) gz -= nm;
-    return ((long)gx * nm + gy) * nm + gz;
+    return gx * px + (long)gy * nm + gz;
 }
 
 // Stage the 17^3 boxes of NM meshes into LDS.  Every load of the batch is
@@ -109,7 +109,7 @@ __device__ __forceinline__ long tile_offset(int i, int nm, int ox, int oy, int o
 // are in flight together with the box and not a round trip behind it.
 template <class T, int NM, class F>
 __device__ __forceinline__ void stage_tiles(T (*ft)[TE * TE * TE], const T* const (&mesh)[NM],
-                                            int nm, int ox, int oy, int oz, int tid, F then) {
+                                            const Geo& g, int ox, int oy, int oz, int tid, F then) {
     constexpr int TC = TE * TE * TE;
     constexpr int IT = (TC + AB - 1) / AB;
     T v[NM][IT];
@@ -117,7 +117,7 @@ __device__ __forceinline__ void stage_tiles(T (*ft)[TE * TE * TE], const T* cons
     for (int it = 0; it < IT; ++it) {
         int i = tid + it * AB;
         i = i < TC ? i : TC - 1;
-        const long c = tile_offset(i, nm, ox, oy, oz);
+        const long c = tile_offset(i, g.nm, g.px, ox, oy, oz);
 #pragma unroll
         for (int m = 0; m < NM; ++m) v[m][it] = mesh[m][c];
     }
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(AB) void k_fvjp_readout(Parts<T> p, SortBufs s, Geo
     };
     {
         const T* const fm[3] = {f0, f1, f2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
+        stage_tiles<T, 3>(ft, fm, g, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
     double dot = 0.0;
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(AB) void k_fvjp_paintgrad(Parts<T> p, SortBufs s, G
     };
     {
         const T* const fm[1] = {rhobar};
-        stage_tiles<T, 1>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
+        stage_tiles<T, 1>(ft, fm, g, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
     double a1 = 0.0, a2 = 0.0, a3 = 0.0;
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(AB) void k_fjvp_gather(Parts<T> p, SortBufs s, Geo 
     };
     {
         const T* const fm[3] = {f0, f1, f2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
+        stage_tiles<T, 3>(ft, fm, g, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
     float vmax = 0.f;
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(AB) void k_fjvp_readout_kick(Parts<T> p, SortBufs s
     };
     {
         const T* const fm[3] = {m0, m1, m2};
-        stage_tiles<T, 3>(ft, fm, g.nm, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
+        stage_tiles<T, 3>(ft, fm, g, ox, oy, oz, tid, [&] { load(min(lo + tid, hi - 1u)); });
     }
     __syncthreads();
     for (uint32_t k0 = lo; k0 < hi; k0 += AB) {

@@ -69,6 +69,7 @@ template <class T> struct R2cArgs {
     const cx<T>* tw_h;
     const cx<T>* tw_post;
     HaloMerge<T> hm;
+    long px;
     int on;
 };
 template <class T> struct C2rArgs {
@@ -77,6 +78,7 @@ template <class T> struct C2rArgs {
     const cx<T>* tw_h;
     const cx<T>* tw_post;
     int mul_k2;
+    long px;
     int on;
 };
 // the main and Nyquist-plane views of a strided pass
@@ -103,12 +105,12 @@ template <class T> struct GradArgs {
 
 // Argument builders (the single-simulation launchers' view set-up).
 template <class T>
-C2cArgs<T> fft_c2c_axis1_args(int n, cx<T>* main, cx<T>* nyq, const cx<T>* tw);
+C2cArgs<T> fft_c2c_axis1_args(int n, long px, cx<T>* main, cx<T>* nyq, const cx<T>* tw);
 template <class T>
-DualArgs<T> fft_c2c_axis1_dual_args(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2,
+DualArgs<T> fft_c2c_axis1_dual_args(int n, long px, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2,
                                     const cx<T>* tw);
 template <class T>
-GradArgs<T> fft_grad_axis0_args(int n, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main,
+GradArgs<T> fft_grad_axis0_args(int n, long px, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main,
                                 PtrTriple out_nyq, const cx<T>* tw, const T* G, T gscale);
 
 // Batched launches over `slots` argument structs at `tab` (device memory).

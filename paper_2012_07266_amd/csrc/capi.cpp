@@ -71,14 +71,15 @@ ArenaPlan plan_arena(const pm_params& p, const lens_params& l, size_t es) {
         a.id[b] = L.take(n * 4);
     }
     a.acc = L.take(3 * n * es);
-    a.key = L.take(n * 4);
+    const bool gaps = plane_values(p.nm) != (long)p.nm * p.nm;
+    if (!gaps) a.key = L.take(n * 4);
     const size_t nkeys = nt * nt * nt * BPT;  // sort blocks
     a.count = L.take(nkeys * 4);
     a.start = L.take((nkeys + 1) * 4);
     a.scan_sum = L.take((nkeys + 1023) / 1024 * 4);
     a.status = L.take(256);
     for (int j = 0; j < 3; ++j) {
-        a.mesh[j] = L.take(nm * nm * nm * es);
+        a.mesh[j] = L.take(nm * plane_values(p.nm) * es);
         a.nyq[j] = L.take(nm * nm * 2 * es);
     }
     a.halo = L.take((size_t)paint_halo_elems((int)nt, (int)es) * es);
@@ -86,6 +87,10 @@ ArenaPlan plan_arena(const pm_params& p, const lens_params& l, size_t es) {
     // before it, the scratch of a projection's image bins (lens_bins)
     a.xbc = L.take(3 * n * es);
     a.fbc = L.take(3 * n * es);
+    // A sort key lives from the pass that writes it to the scatter, xbc within
+    // a call of the reverse pass or a projection between two sorts: one place
+    // serves both, and makes up for the gaps between the planes of the meshes.
+    if (gaps) a.key = a.xbc;
     a.tw_nm = L.take(nm * 2 * es);
     a.tw_hm = L.take(nm / 2 * 2 * es);
     a.twp_nm = L.take((nm / 2 + 1) * 2 * es);
@@ -111,7 +116,7 @@ ArenaPlan plan_arena(const pm_params& p, const lens_params& l, size_t es) {
         a.pgd_g = L.take((3 * (nm / 2) * (nm / 2) + 1) * es);
         a.pgd_s = L.take(3 * n * es);
         a.pgd_bits = L.take(256);
-        a.pgd_m = L.take(nm * nm * nm * es);
+        a.pgd_m = L.take(nm * plane_values(p.nm) * es);
         a.pgd_nyq = L.take(nm * nm * 2 * es);
     }
     if (p.modes & PM_MODE_TANGENT) a.tan = L.take(15 * n * es);
@@ -396,6 +401,7 @@ template <class T> struct Sim final : SimBase {
         geo.nt = p->nm / TILE;
         geo.ncb = geo.nt * BPT;
         geo.npart = (long)p->np * p->np * p->np;
+        geo.px = plane_values(p->nm);
         ntiles = geo.nt * geo.nt * geo.ncb;  // sort blocks (keys)
         ap = plan_arena(*p, *l, sizeof(T));
         // (a handle in the static scratch creates nothing: it projects in line)
@@ -629,24 +635,24 @@ template <class T> struct Sim final : SimBase {
     // (m0, q0), the others in mesh 1 (to mesh 1 and 2).  between: called
     // between the inverse and the dual axis-1 pass where they are launched
     // apart, else before both.
-    void fft_inverse(int n, T* m0, cx<T>* q0, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
+    void fft_inverse(int n, long px, T* m0, cx<T>* q0, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
                      const std::function<void()>& between = nullptr) {
         cx<T>*c0 = reinterpret_cast<cx<T>*>(m0), *c1 = reinterpret_cast<cx<T>*>(mesh[1]),
              *c2 = reinterpret_cast<cx<T>*>(mesh[2]);
         if (n < 512) {
             if (between) between();
             ProfScope ps(prof, "fft_c2c_axis1_inv_dual");
-            fft_c2c_axis1_inv_dual<T>(n, c0, q0, c1, nyq[1], c2, nyq[2], tw, st);
+            fft_c2c_axis1_inv_dual<T>(n, px, c0, q0, c1, nyq[1], c2, nyq[2], tw, st);
         } else {
-            { ProfScope ps(prof, "fft_c2c_axis1_inv"); fft_c2c_axis1<T>(n, -1, c0, q0, tw, st); }
+            { ProfScope ps(prof, "fft_c2c_axis1_inv"); fft_c2c_axis1<T>(n, px, -1, c0, q0, tw, st); }
             if (between) between();
             // axis 1: n1 times mesh 1 in place, the plain transform into mesh 2
             ProfScope ps(prof, "fft_c2c_axis1_dual");
-            fft_c2c_axis1_dual<T>(n, c1, nyq[1], c2, nyq[2], tw, st);
+            fft_c2c_axis1_dual<T>(n, px, c1, nyq[1], c2, nyq[2], tw, st);
         }
         // axis 2, the last component times n2
         ProfScope ps(prof, "fft_c2r_axis2");
-        fft_c2r_rows3<T>(n, PtrTriple{{m0, mesh[1], mesh[2]}}, PtrTriple{{q0, nyq[1], nyq[2]}}, twh,
+        fft_c2r_rows3<T>(n, px, PtrTriple{{m0, mesh[1], mesh[2]}}, PtrTriple{{q0, nyq[1], nyq[2]}}, twh,
                          twp, st);
     }
 
@@ -656,15 +662,17 @@ template <class T> struct Sim final : SimBase {
                           const std::function<void()>& after_inv = nullptr) {
         // Poisson: G(q) = 1 / (2 pi q Nm^2) computed in the kernel (G == NULL)
         const T gscale = (T)(1.0 / (2.0 * PI * (double)n * (double)n));
-        { ProfScope ps(prof, "fft_r2c_axis2"); fft_r2c_rows<T>(n, mesh[0], nyq[0], twh, twp, st, hm); }
+        // the particle lattice (G set) has its planes adjacent
+        const long px = G ? (long)n * n : geo.px;
+        { ProfScope ps(prof, "fft_r2c_axis2"); fft_r2c_rows<T>(n, px, mesh[0], nyq[0], twh, twp, st, hm); }
         { ProfScope ps(prof, "fft_c2c_axis1_fwd");
-          fft_c2c_axis1<T>(n, 1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw, st); }
+          fft_c2c_axis1<T>(n, px, 1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw, st); }
         if (after_fwd) after_fwd();  // work to overlap with the rest of the transform
         PtrTriple om{{mesh[0], mesh[1], mesh[2]}}, on{{nyq[0], nyq[1], nyq[2]}};
         // axis 0: IFFT0(n0 h) -> mesh 0, IFFT0(h) -> mesh 1 (h = i G X)
         { ProfScope ps(prof, "fft_grad_axis0");
-          fft_grad_axis0<T>(n, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw, G, gscale, st); }
-        fft_inverse(n, mesh[0], nyq[0], tw, twh, twp, after_inv);
+          fft_grad_axis0<T>(n, px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw, G, gscale, st); }
+        fft_inverse(n, px, mesh[0], nyq[0], tw, twh, twp, after_inv);
     }
 
     // CIC density into mesh[0].  With defer_merge the paint boxes' shells are
@@ -831,15 +839,15 @@ template <class T> struct Sim final : SimBase {
         const int nm = P.nm;
         paint(true);
         { ProfScope ps(prof, "fft_r2c_axis2");
-          fft_r2c_rows<T>(nm, mesh[0], nyq[0], tw_hm, twp_nm, st, paint_halo_merge<T>(geo, halo)); }
+          fft_r2c_rows<T>(nm, geo.px, mesh[0], nyq[0], tw_hm, twp_nm, st, paint_halo_merge<T>(geo, halo)); }
         { ProfScope ps(prof, "fft_c2c_axis1_fwd");
-          fft_c2c_axis1<T>(nm, 1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
+          fft_c2c_axis1<T>(nm, geo.px, 1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
         cx<T>* pn_ = reinterpret_cast<cx<T>*>(pgd_nyq);
         PtrTriple om{{pgd_m, mesh[1], mesh[2]}}, on{{pgd_nyq, nyq[1], nyq[2]}};
         { ProfScope ps(prof, "fft_grad_axis0");
-          fft_grad_axis0<T>(nm, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, pgd_g,
+          fft_grad_axis0<T>(nm, geo.px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, pgd_g,
                             T(0), st); }
-        fft_inverse(nm, pgd_m, pn_, tw_nm, tw_hm, twp_nm);
+        fft_inverse(nm, geo.px, pgd_m, pn_, tw_nm, tw_hm, twp_nm);
         Parts<T> q = cur;
         q.acc = pgd_s;
         { ProfScope ps(prof, "pgd_readout");
@@ -859,9 +867,9 @@ template <class T> struct Sim final : SimBase {
         const T gscale = (T)(1.0 / (2.0 * PI * (double)n * (double)n));
         PtrTriple om{{mesh[0], mesh[1], mesh[2]}}, on{{nyq[0], nyq[1], nyq[2]}};
         { ProfScope ps(prof, "fft_grad_axis0");
-          fft_grad_axis0<T>(n, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, nullptr,
+          fft_grad_axis0<T>(n, geo.px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw_nm, nullptr,
                             gscale, st); }
-        fft_inverse(n, mesh[0], nyq[0], tw_nm, tw_hm, twp_nm);
+        fft_inverse(n, geo.px, mesh[0], nyq[0], tw_nm, tw_hm, twp_nm);
     }
 
     // The plain projection's arguments and mean terms of the shell
@@ -1234,13 +1242,14 @@ template <class T> struct Sim final : SimBase {
     struct CkptPart {
         void* arena;
         size_t at, bytes;
+        bool planes;  // a force mesh, stored with its planes adjacent
     };
     std::vector<CkptPart> checkpoint_parts() const {
         const size_t n = (size_t)geo.npart, es = sizeof(T), n3 = (size_t)P.nm * P.nm * P.nm;
         std::vector<CkptPart> parts;
         size_t at = 0;
-        const auto add = [&](void* p, size_t bytes) {
-            parts.push_back({p, at, bytes});
+        const auto add = [&](void* p, size_t bytes, bool planes = false) {
+            parts.push_back({p, at, bytes, planes});
             at += (bytes + 255) / 256 * 256;
         };
         add(cur.disp, 3 * n * es);
@@ -1248,14 +1257,28 @@ template <class T> struct Sim final : SimBase {
         add(cur.id, n * 4);
         add(sb.start, ((size_t)ntiles + 1) * 4);
         if (ckpt_force()) {
-            for (int j = 0; j < 3; ++j) add(mesh[j], n3 * es);
+            for (int j = 0; j < 3; ++j) add(mesh[j], n3 * es, true);
             add(cur.acc, 3 * n * es);
         }
         return parts;
     }
     int checkpoint_copy(char* buf, bool save) {
         CopyParts c;
-        const std::vector<CkptPart> parts = checkpoint_parts();
+        std::vector<CkptPart> parts = checkpoint_parts();
+        const size_t plane = (size_t)P.nm * P.nm * sizeof(T), step = (size_t)geo.px * sizeof(T);
+        if (plane != step)  // planes with gaps between them
+            for (size_t i = 0; i < parts.size();) {
+                if (!parts[i].planes) {
+                    ++i;
+                    continue;
+                }
+                char* b = buf + parts[i].at;
+                HIPCHK(save ? hipMemcpy2DAsync(b, plane, parts[i].arena, step, plane, P.nm,
+                                               hipMemcpyDeviceToDevice, st)
+                            : hipMemcpy2DAsync(parts[i].arena, step, b, plane, plane, P.nm,
+                                               hipMemcpyDeviceToDevice, st));
+                parts.erase(parts.begin() + i);
+            }
         for (const CkptPart& p : parts)
             save ? c.add(buf + p.at, p.arena, p.bytes) : c.add(p.arena, buf + p.at, p.bytes);
         if (launch_copy_parts(c, st)) return PM_OK;
@@ -1296,14 +1319,16 @@ template <class T> struct Sim final : SimBase {
         if (a_cur < 0) return PM_ESTATE;
         size_t n3 = (size_t)P.nm * P.nm * P.nm;
         paint();
-        if (rho) HIPCHK(hipMemcpyAsync(rho, mesh[0], n3 * sizeof(T), hipMemcpyDeviceToDevice, st));
+        const long plane = (long)P.nm * P.nm;
+        if (rho) launch_scale_copy<T>(reinterpret_cast<T*>(rho), mesh[0], T(1), plane, geo.px, (long)n3, st);
         fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm);
         meshes_valid = true;
         launch_readout<T>(cur, sb, geo, mesh[0], mesh[1], mesh[2], T(0), 0, status, st);
         if (fm) {
             // force meshes are in cell units; scale to Mpc/h into the caller's buffer
             for (int j = 0; j < 3; ++j)
-                launch_scale_copy<T>(reinterpret_cast<T*>(fm) + j * n3, mesh[j], (T)cell, (long)n3, st);
+                launch_scale_copy<T>(reinterpret_cast<T*>(fm) + j * n3, mesh[j], (T)cell, plane, geo.px,
+                                     (long)n3, st);
         }
         if (acc)
             launch_get_state<T>(cur, geo, (T)cell, nullptr, nullptr, reinterpret_cast<T*>(acc), st);
@@ -1354,19 +1379,20 @@ template <class T> struct Sim final : SimBase {
               launch_paint_values<T>(cur, sb, geo, T(1), mesh[j], halo, fbc + j * n, fmax_bits, st,
                                      false); }
             ProfScope ps(prof, "fft_r2c_axis2");
-            fft_r2c_rows<T>(nm, mesh[j], nyq[j], tw_hm, twp_nm, st, paint_halo_merge<T>(geo, halo));
+            fft_r2c_rows<T>(nm, geo.px, mesh[j], nyq[j], tw_hm, twp_nm, st,
+                            paint_halo_merge<T>(geo, halo));
         }
         for (int j = 0; j < 3; ++j) {
             ProfScope ps(prof, "fft_c2c_axis1_fwd");
-            fft_c2c_axis1<T>(nm, 1, reinterpret_cast<cx<T>*>(mesh[j]), nyq[j], tw_nm, st);
+            fft_c2c_axis1<T>(nm, geo.px, 1, reinterpret_cast<cx<T>*>(mesh[j]), nyq[j], tw_nm, st);
         }
         PtrTriple im{{mesh[0], mesh[1], mesh[2]}}, in_{{nyq[0], nyq[1], nyq[2]}};
         { ProfScope ps(prof, "fft_div_axis0");
-          fft_div_axis0<T>(nm, im, in_, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, nullptr,
+          fft_div_axis0<T>(nm, geo.px, im, in_, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, nullptr,
                            gscale, st); }
         { ProfScope ps(prof, "fft_c2c_axis1_inv");
-          fft_c2c_axis1<T>(nm, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
-        { ProfScope ps(prof, "fft_c2r_axis2"); fft_c2r_rows<T>(nm, mesh[0], nyq[0], tw_hm, twp_nm, st); }
+          fft_c2c_axis1<T>(nm, geo.px, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm, st); }
+        { ProfScope ps(prof, "fft_c2r_axis2"); fft_c2r_rows<T>(nm, geo.px, mesh[0], nyq[0], tw_hm, twp_nm, st); }
         T mass = (T)std::pow((double)geo.B, 3);
         ProfScope ps(prof, "vjp_paintgrad");
         launch_fvjp_paintgrad<T>(cur, sb, geo, mesh[0], mass, xbc, H, mode, dr, k2, d0, gp0, xbar_out,
@@ -1427,14 +1453,15 @@ template <class T> struct Sim final : SimBase {
         fft_forward_grad(np, g_ic_dom, tw_np, tw_hp, twp_np);
         launch_dot_sorted_lattice<T>(cur, geo, fbc, mesh[0], mesh[1], mesh[2], dots + 5, st);
         // noise_bar = S^T sbar
+        const long lat = (long)np * np;  // the lattice's planes are adjacent
         launch_sorted_to_lattice<T>(cur, geo, fbc, mesh[0], mesh[1], mesh[2], st);
-        for (int j = 0; j < 3; ++j) fft_r2c_rows<T>(np, mesh[j], nyq[j], tw_hp, twp_np, st);
+        for (int j = 0; j < 3; ++j) fft_r2c_rows<T>(np, lat, mesh[j], nyq[j], tw_hp, twp_np, st);
         for (int j = 0; j < 3; ++j)
-            fft_c2c_axis1<T>(np, 1, reinterpret_cast<cx<T>*>(mesh[j]), nyq[j], tw_np, st);
+            fft_c2c_axis1<T>(np, lat, 1, reinterpret_cast<cx<T>*>(mesh[j]), nyq[j], tw_np, st);
         PtrTriple im{{mesh[0], mesh[1], mesh[2]}}, in_{{nyq[0], nyq[1], nyq[2]}};
-        fft_div_axis0<T>(np, im, in_, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_np, g_ic, T(0), st);
-        fft_c2c_axis1<T>(np, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_np, st);
-        fft_c2r_rows<T>(np, mesh[0], nyq[0], tw_hp, twp_np, st);
+        fft_div_axis0<T>(np, lat, im, in_, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_np, g_ic, T(0), st);
+        fft_c2c_axis1<T>(np, lat, -1, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_np, st);
+        fft_c2r_rows<T>(np, lat, mesh[0], nyq[0], tw_hp, twp_np, st);
         HIPCHK(hipMemcpyAsync(nbar, mesh[0], n * sizeof(T), hipMemcpyDeviceToDevice, st));
         meshes_valid = false;
         int rc = check_launch();
@@ -1777,18 +1804,18 @@ template <class T> struct Sim final : SimBase {
             o.lens.kappa = kappa;
             o.lens.on = 1;
         }
-        o.r2c = R2cArgs<T>{mesh[0], nyq[0], tw_hm, twp_nm, paint_halo_merge<T>(geo, halo), 1};
-        o.fwd = fft_c2c_axis1_args<T>(nm, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm);
+        o.r2c = R2cArgs<T>{mesh[0], nyq[0], tw_hm, twp_nm, paint_halo_merge<T>(geo, halo), geo.px, 1};
+        o.fwd = fft_c2c_axis1_args<T>(nm, geo.px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm);
         const T gscale = (T)(1.0 / (2.0 * PI * (double)nm * (double)nm));
         PtrTriple om{{mesh[0], mesh[1], mesh[2]}}, on{{nyq[0], nyq[1], nyq[2]}};
-        o.grad = fft_grad_axis0_args<T>(nm, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on,
+        o.grad = fft_grad_axis0_args<T>(nm, geo.px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on,
                                         tw_nm, nullptr, gscale);
-        C2cArgs<T> inv = fft_c2c_axis1_args<T>(nm, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm);
+        C2cArgs<T> inv = fft_c2c_axis1_args<T>(nm, geo.px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], tw_nm);
         o.inv = inv;
-        o.dual = fft_c2c_axis1_dual_args<T>(nm, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
+        o.dual = fft_c2c_axis1_dual_args<T>(nm, geo.px, reinterpret_cast<cx<T>*>(mesh[1]), nyq[1],
                                             reinterpret_cast<cx<T>*>(mesh[2]), nyq[2], tw_nm);
         for (int j = 0; j < 3; ++j)
-            o.c2r[j] = C2rArgs<T>{mesh[j], nyq[j], tw_hm, twp_nm, j == 2 ? 1 : 0, 1};
+            o.c2r[j] = C2rArgs<T>{mesh[j], nyq[j], tw_hm, twp_nm, j == 2 ? 1 : 0, geo.px, 1};
         const double ah = 0.5 * (a0 + a1);
         ReadoutNext<T> nx;
         if (a2 > a1) {
@@ -1904,6 +1931,7 @@ template <class T> struct Batch final : BatchBase {
         geo.nt = p->nm / TILE;
         geo.ncb = geo.nt * BPT;
         geo.npart = (long)p->np * p->np * p->np;
+        geo.px = plane_values(p->nm);
         lshape.npix = npix;
         lshape.nsrc = nsrc;
         lshape.rs = Sim<T>::bin_side(npix);

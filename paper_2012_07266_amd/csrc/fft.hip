@@ -269,18 +269,20 @@ __device__ __forceinline__ unsigned row_wg(unsigned b, unsigned nb) {
 
 template <class T, int H, int W>
 __device__ __forceinline__ void r2c_rows_body(T* io, cx<T>* nyq, const cx<T>* tw_h,
-                                                 const cx<T>* tw_post, HaloMerge<T> hm) {
+                                                 const cx<T>* tw_post, HaloMerge<T> hm, long px) {
     __shared__ cx<T> buf[H * (W + 1)];
     __shared__ cx<T> tws[H];
     __shared__ cx<T> twp[H / 2 + 1];
     constexpr int LD = W + 1;
     const int tid = threadIdx.x;
     const size_t r0 = (size_t)row_wg<T, W>(blockIdx.x, gridDim.x) * W;
+    // these rows' place: all in one plane (2H rows each)
+    const size_t at = (r0 / (2 * H)) * (size_t)(px / 2) + (r0 % (2 * H)) * H;
     TwFetch<T, H> twr;
     TwFetch<T, H / 2 + 1> twq;
     twr.fetch(tw_h, tid);
     twq.fetch(tw_post, tid);
-    const cx<T>* in = reinterpret_cast<const cx<T>*>(io) + r0 * H;
+    const cx<T>* in = reinterpret_cast<const cx<T>*>(io) + at;
     {
         constexpr int IT = (W * H + NT - 1) / NT;
         cx<T> v[IT];
@@ -301,7 +303,7 @@ __device__ __forceinline__ void r2c_rows_body(T* io, cx<T>* nyq, const cx<T>* tw
     // rows r0 .. r0 + W - 1 share X (2H is a multiple of W)
     if (hm.halo) merge_rows<T, H, W, NT>(hm, buf, (int)(r0 / (2 * H)), (int)(r0 % (2 * H)), tid);
     fft_lds<T, H, W, 1>(buf, tws, tid);
-    cx<T>* out = reinterpret_cast<cx<T>*>(io) + r0 * H;
+    cx<T>* out = reinterpret_cast<cx<T>*>(io) + at;
     constexpr int HK = H / 2 + 1;
     for (int f = tid; f < W * HK; f += NT) {
         int w = f / HK, k = f % HK;
@@ -325,14 +327,14 @@ __device__ __forceinline__ void r2c_rows_body(T* io, cx<T>* nyq, const cx<T>* tw
 
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_r2c_rows(T* io, cx<T>* nyq, const cx<T>* tw_h,
-                                                 const cx<T>* tw_post, HaloMerge<T> hm) {
-    r2c_rows_body<T, H, W>(io, nyq, tw_h, tw_post, hm);
+                                                 const cx<T>* tw_post, HaloMerge<T> hm, long px) {
+    r2c_rows_body<T, H, W>(io, nyq, tw_h, tw_post, hm, px);
 }
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_r2c_rows_b(const R2cArgs<T>* __restrict__ tab) {
     const R2cArgs<T> a = tab[blockIdx.y];
     if (!a.on) return;
-    r2c_rows_body<T, H, W>(a.io, a.nyq, a.tw_h, a.tw_post, a.hm);
+    r2c_rows_body<T, H, W>(a.io, a.nyq, a.tw_h, a.tw_post, a.hm, a.px);
 }
 
 // ---------------------------------------------------------------------------
@@ -343,15 +345,17 @@ __global__ __launch_bounds__(NT) void k_r2c_rows_b(const R2cArgs<T>* __restrict_
 // axis-0 pass.
 template <class T, int H, int W>
 __device__ __forceinline__ void c2r_rows_body(T* io, const cx<T>* nyq, const cx<T>* tw_h,
-                                                 const cx<T>* tw_post, int mul_k2) {
+                                                 const cx<T>* tw_post, int mul_k2, long px) {
     __shared__ cx<T> buf[H * (W + 1)];
     __shared__ cx<T> tws[H];
     constexpr int LD = W + 1;
     const int tid = threadIdx.x;
     const size_t r0 = (size_t)row_wg<T, W>(blockIdx.x, gridDim.x) * W;
+    // these rows' place: all in one plane (2H rows each)
+    const size_t at = (r0 / (2 * H)) * (size_t)(px / 2) + (r0 % (2 * H)) * H;
     TwFetch<T, H> twr;
     twr.fetch(tw_h, tid);
-    const cx<T>* in = reinterpret_cast<const cx<T>*>(io) + r0 * H;
+    const cx<T>* in = reinterpret_cast<const cx<T>*>(io) + at;
     constexpr int HK = H / 2 + 1;
     constexpr int ITK = (W * HK + NT - 1) / NT;
     cx<T> xkv[ITK], xmv[ITK], tpv[ITK];
@@ -394,7 +398,7 @@ __device__ __forceinline__ void c2r_rows_body(T* io, const cx<T>* nyq, const cx<
     }
     __syncthreads();
     fft_lds<T, H, W, -1>(buf, tws, tid);
-    cx<T>* out = reinterpret_cast<cx<T>*>(io) + r0 * H;
+    cx<T>* out = reinterpret_cast<cx<T>*>(io) + at;
 #pragma unroll
     for (int it = 0; it < (W * H + NT - 1) / NT; ++it) {
         int f = tid + it * NT;
@@ -404,30 +408,30 @@ __device__ __forceinline__ void c2r_rows_body(T* io, const cx<T>* nyq, const cx<
 
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_c2r_rows(T* io, const cx<T>* nyq, const cx<T>* tw_h,
-                                                 const cx<T>* tw_post, int mul_k2) {
-    c2r_rows_body<T, H, W>(io, nyq, tw_h, tw_post, mul_k2);
+                                                 const cx<T>* tw_post, int mul_k2, long px) {
+    c2r_rows_body<T, H, W>(io, nyq, tw_h, tw_post, mul_k2, px);
 }
 // The three components of a force in one launch (blockIdx.y), the last times
 // n2: at small meshes a launch costs as much as its pass (128^3: 7 us each,
 // 9 us together).
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_c2r_rows3(PtrTriple io, PtrTriple nyq, const cx<T>* tw_h,
-                                                  const cx<T>* tw_post) {
+                                                  const cx<T>* tw_post, long px) {
     const int j = blockIdx.y;
     c2r_rows_body<T, H, W>(reinterpret_cast<T*>(io.p[j]), reinterpret_cast<const cx<T>*>(nyq.p[j]),
-                           tw_h, tw_post, j == 2 ? 1 : 0);
+                           tw_h, tw_post, j == 2 ? 1 : 0, px);
 }
 template <class T, int H, int W>
 __global__ __launch_bounds__(NT) void k_c2r_rows_b(const C2rArgs<T>* __restrict__ tab) {
     const C2rArgs<T> a = tab[blockIdx.y];
     if (!a.on) return;
-    c2r_rows_body<T, H, W>(a.io, a.nyq, a.tw_h, a.tw_post, a.mul_k2);
+    c2r_rows_body<T, H, W>(a.io, a.nyq, a.tw_h, a.tw_post, a.mul_k2, a.px);
 }
 
 // ---------------------------------------------------------------------------
 // passes 2 and 4: c2c along a strided axis.  A "view" describes pencils of
 // length N: element n of pencil w of workgroup g sits at
-//   strided: base(g) + n*C + w,  base = (g / (C/W)) * N*C + (g % (C/W)) * W
+//   strided: base(g) + n*C + w,  base = (g / (C/W)) * P + (g % (C/W)) * W
 //   contig : g*W*N + w*N + n
 // Workgroups [0, g_main) work on view a, the rest on view b.
 // ---------------------------------------------------------------------------
@@ -453,7 +457,7 @@ template <class T, int N, int W>
 __device__ __forceinline__ long view_offset(const ViewDesc& v, int g, int w, int n) {
     if (v.contig) return ((long)g * W + w) * N + n;
     long cw = v.C / W;
-    long base = (g / cw) * (long)N * v.C + (g % cw) * W;
+    long base = (g / cw) * v.P + (g % cw) * W;
     return base + (long)n * v.C + w;
 }
 
@@ -690,8 +694,10 @@ __device__ __forceinline__ void c2c_view_dual_body(ViewDesc va, ViewDesc vb, cx<
     }
 }
 
+// (two waves per SIMD asked for: at 1024 the compiler otherwise takes two
+// registers too many for them and the pass goes from 3.5 to 4.9 ms)
 template <class T, int N, int W>
-__global__ __launch_bounds__(NT) void k_c2c_view_dual(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
+__global__ __launch_bounds__(NT, 2) void k_c2c_view_dual(ViewDesc va, ViewDesc vb, cx<T>* dst2a,
                                                       cx<T>* dst2b, const cx<T>* tw) {
     // Where H is held (registers then leave two workgroups per CU) the values
     // are exchanged in halves, and half the LDS is left to the projection's
@@ -1096,58 +1102,58 @@ template <class T> constexpr int rows_w(int n) { return (sizeof(T) == 4 && n < 7
 
 template <class T, int H>
 static void r2c_rows_n(T* io, cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post, long nrows,
-                       hipStream_t st, HaloMerge<T> hm) {
+                       hipStream_t st, HaloMerge<T> hm, long px) {
     constexpr int W = rows_w<T>(2 * H);
-    ML_LAUNCH((k_r2c_rows<T, H, W>), nrows / W, st, io, nyq, tw_h, tw_post, hm);
+    ML_LAUNCH((k_r2c_rows<T, H, W>), nrows / W, st, io, nyq, tw_h, tw_post, hm, px);
 }
 template <class T, int H>
 static void c2r_rows_n(T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post,
-                       long nrows, hipStream_t st, int mul_k2) {
+                       long nrows, hipStream_t st, int mul_k2, long px) {
     constexpr int W = rows_w<T>(2 * H);
-    ML_LAUNCH((k_c2r_rows<T, H, W>), nrows / W, st, io, nyq, tw_h, tw_post, mul_k2);
+    ML_LAUNCH((k_c2r_rows<T, H, W>), nrows / W, st, io, nyq, tw_h, tw_post, mul_k2, px);
 }
 
 template <class T, int H>
 static void c2r_rows3_n(PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
-                        long nrows, hipStream_t st) {
+                        long nrows, hipStream_t st, long px) {
     constexpr int W = rows_w<T>(2 * H);
     hipLaunchKernelGGL((k_c2r_rows3<T, H, W>), dim3(nrows / W, 3), dim3(NT), 0, st, io, nyq, tw_h,
-                       tw_post);
+                       tw_post, px);
 }
 
 template <class T, int N, int S>
-static void c2c_axis1_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
+static void c2c_axis1_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
-    ViewDesc va{main, N / 2, 0, (int)((long)N * (N / 2) / W)};
-    ViewDesc vb{nyq, 1, 1, N / W};
+    ViewDesc va{main, N / 2, 0, (int)((long)N * (N / 2) / W), px / 2};
+    ViewDesc vb{nyq, 1, 1, N / W, 0};
     ML_LAUNCH((k_c2c_view<T, N, W, S>), va.n_wg + vb.n_wg, st, va, vb, tw);
 }
 
 template <class T, int N>
 static void c2c_axis1_dual_n(cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2, const cx<T>* tw,
-                             hipStream_t st) {
+                             hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
-    ViewDesc va{main, N / 2, 0, (int)((long)N * (N / 2) / W)};
-    ViewDesc vb{nyq, 1, 1, N / W};
+    ViewDesc va{main, N / 2, 0, (int)((long)N * (N / 2) / W), px / 2};
+    ViewDesc vb{nyq, 1, 1, N / W, 0};
     ML_LAUNCH((k_c2c_view_dual<T, N, W>), va.n_wg + vb.n_wg, st, va, vb, main2, nyq2, tw);
 }
 
 template <class T, int N>
 static void c2c_axis1_inv_dual_n(cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
-                                 cx<T>* nyq2, const cx<T>* tw, hipStream_t st) {
+                                 cx<T>* nyq2, const cx<T>* tw, hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
     const int n_main = (int)((long)N * (N / 2) / W);
-    ViewDesc ia{main0, N / 2, 0, n_main}, ib{nyq0, 1, 1, N / W};
-    ViewDesc va{main, N / 2, 0, n_main}, vb{nyq, 1, 1, N / W};
+    ViewDesc ia{main0, N / 2, 0, n_main, px / 2}, ib{nyq0, 1, 1, N / W, 0};
+    ViewDesc va{main, N / 2, 0, n_main, px / 2}, vb{nyq, 1, 1, N / W, 0};
     hipLaunchKernelGGL((k_c2c_inv_dual<T, N, W>), dim3(n_main + N / W, 2), dim3(NT), 0, st, ia, ib,
                        va, vb, main2, nyq2, tw);
 }
 
 template <class T, int N, int S>
-static void c2c_axis0_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
+static void c2c_axis0_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
-    ViewDesc va{main, (long)N * (N / 2), 0, (int)((long)N * (N / 2) / W)};
-    ViewDesc vb{nyq, N, 0, N / W};
+    ViewDesc va{main, px / 2, 0, (int)((long)N * (N / 2) / W), 0};
+    ViewDesc vb{nyq, N, 0, N / W, 0};
     ML_LAUNCH((k_c2c_view<T, N, W, S>), va.n_wg + vb.n_wg, st, va, vb, tw);
 }
 
@@ -1158,21 +1164,21 @@ template <class T> constexpr int grad_nt(int n) { return (n >= 512 && sizeof(T) 
 
 template <class T, int N>
 static void grad_axis0_n(cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main, PtrTriple out_nyq,
-                         const cx<T>* tw, const T* G, T gscale, hipStream_t st) {
+                         const cx<T>* tw, const T* G, T gscale, hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
     constexpr int NTG = (grad_nt<T>(N) == 512 && reg_path_ok<N, W, 512>()) ? 512 : NT;
-    ViewDesc va{main_in, (long)N * (N / 2), 0, (int)((long)N * (N / 2) / W)};
-    ViewDesc vb{nyq_in, N, 0, N / W};
+    ViewDesc va{main_in, px / 2, 0, (int)((long)N * (N / 2) / W), 0};
+    ViewDesc vb{nyq_in, N, 0, N / W, 0};
     hipLaunchKernelGGL((k_grad_x0<T, N, W, NTG>), dim3(va.n_wg + vb.n_wg), dim3(NTG), 0, st, va, vb,
                        out_main, out_nyq, tw, G, gscale);
 }
 
 template <class T, int N>
 static void div_axis0_n(PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, cx<T>* out_nyq,
-                        const cx<T>* tw, const T* G, T gscale, hipStream_t st) {
+                        const cx<T>* tw, const T* G, T gscale, hipStream_t st, long px) {
     constexpr int W = lanes_w<T>(N);
-    ViewDesc va{in_main.p[0], (long)N * (N / 2), 0, (int)((long)N * (N / 2) / W)};
-    ViewDesc vb{in_nyq.p[0], N, 0, N / W};
+    ViewDesc va{in_main.p[0], px / 2, 0, (int)((long)N * (N / 2) / W), 0};
+    ViewDesc vb{in_nyq.p[0], N, 0, N / W, 0};
     constexpr int NTG = (grad_nt<T>(N) == 512 && reg_path_ok<N, W, 512>()) ? 512 : NT;
     hipLaunchKernelGGL((k_div_x0<T, N, W, NTG>), dim3(va.n_wg + vb.n_wg), dim3(NTG), 0, st, va, vb,
                        in_main, in_nyq, (void*)out_main, (void*)out_nyq, tw, G, gscale);
@@ -1191,42 +1197,42 @@ template <class T> bool fft_supported(int n) {
 }
 
 template <class T>
-void fft_r2c_rows(int n, T* io, cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post, hipStream_t st,
-                  HaloMerge<T> hm) {
+void fft_r2c_rows(int n, long px, T* io, cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+                  hipStream_t st, HaloMerge<T> hm) {
     long rows = (long)n * n;
-#define ML_CASE(v) if (n == v) return r2c_rows_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st, hm);
+#define ML_CASE(v) if (n == v) return r2c_rows_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st, hm, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
 }
 
 template <class T>
-void fft_c2r_rows(int n, T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+void fft_c2r_rows(int n, long px, T* io, const cx<T>* nyq, const cx<T>* tw_h, const cx<T>* tw_post,
                   hipStream_t st, bool mul_k2) {
     long rows = (long)n * n;
 #define ML_CASE(v) \
-    if (n == v) return c2r_rows_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st, mul_k2 ? 1 : 0);
+    if (n == v) return c2r_rows_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st, mul_k2 ? 1 : 0, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
 }
 
 template <class T>
-void fft_c2r_rows3(int n, PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
+void fft_c2r_rows3(int n, long px, PtrTriple io, PtrTriple nyq, const cx<T>* tw_h, const cx<T>* tw_post,
                    hipStream_t st) {
     long rows = (long)n * n;
-#define ML_CASE(v) if (n == v) return c2r_rows3_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st);
+#define ML_CASE(v) if (n == v) return c2r_rows3_n<T, v / 2>(io, nyq, tw_h, tw_post, rows, st, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
 }
 
 template <class T>
-void fft_c2c_axis1(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
+void fft_c2c_axis1(int n, long px, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
 #define ML_CASE(v)                                                                  \
     if (n == v) {                                                                   \
-        if (sign > 0) return c2c_axis1_n<T, v, 1>(main, nyq, tw, st);               \
-        return c2c_axis1_n<T, v, -1>(main, nyq, tw, st);                            \
+        if (sign > 0) return c2c_axis1_n<T, v, 1>(main, nyq, tw, st, px);               \
+        return c2c_axis1_n<T, v, -1>(main, nyq, tw, st, px);                            \
     }
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
@@ -1234,10 +1240,10 @@ void fft_c2c_axis1(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hi
 }
 
 template <class T>
-void fft_c2c_axis1_dual(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2, const cx<T>* tw,
+void fft_c2c_axis1_dual(int n, long px, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2, const cx<T>* tw,
                         hipStream_t st) {
 #define ML_CASE(v) \
-    if (n == v) return c2c_axis1_dual_n<T, v>(main, nyq, main2, nyq2, tw, st);
+    if (n == v) return c2c_axis1_dual_n<T, v>(main, nyq, main2, nyq2, tw, st, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
@@ -1246,22 +1252,22 @@ void fft_c2c_axis1_dual(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq
 // From 512 up each pass fills the GPU by itself and the two are launched
 // apart (a projection can then start between them).
 template <class T>
-void fft_c2c_axis1_inv_dual(int n, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
+void fft_c2c_axis1_inv_dual(int n, long px, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
                             cx<T>* nyq2, const cx<T>* tw, hipStream_t st) {
 #define ML_CASE(v) \
-    if (n == v) return c2c_axis1_inv_dual_n<T, v>(main0, nyq0, main, nyq, main2, nyq2, tw, st);
+    if (n == v) return c2c_axis1_inv_dual_n<T, v>(main0, nyq0, main, nyq, main2, nyq2, tw, st, px);
     ML_SIZES_D(ML_CASE)
 #undef ML_CASE
-    fft_c2c_axis1<T>(n, -1, main0, nyq0, tw, st);
-    fft_c2c_axis1_dual<T>(n, main, nyq, main2, nyq2, tw, st);
+    fft_c2c_axis1<T>(n, px, -1, main0, nyq0, tw, st);
+    fft_c2c_axis1_dual<T>(n, px, main, nyq, main2, nyq2, tw, st);
 }
 
 template <class T>
-void fft_c2c_axis0(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
+void fft_c2c_axis0(int n, long px, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
 #define ML_CASE(v)                                                                  \
     if (n == v) {                                                                   \
-        if (sign > 0) return c2c_axis0_n<T, v, 1>(main, nyq, tw, st);               \
-        return c2c_axis0_n<T, v, -1>(main, nyq, tw, st);                            \
+        if (sign > 0) return c2c_axis0_n<T, v, 1>(main, nyq, tw, st, px);               \
+        return c2c_axis0_n<T, v, -1>(main, nyq, tw, st, px);                            \
     }
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
@@ -1269,18 +1275,18 @@ void fft_c2c_axis0(int n, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hi
 }
 
 template <class T>
-void fft_grad_axis0(int n, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main, PtrTriple out_nyq,
+void fft_grad_axis0(int n, long px, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main, PtrTriple out_nyq,
                     const cx<T>* tw, const T* G, T gscale, hipStream_t st) {
-#define ML_CASE(v) if (n == v) return grad_axis0_n<T, v>(main_in, nyq_in, out_main, out_nyq, tw, G, gscale, st);
+#define ML_CASE(v) if (n == v) return grad_axis0_n<T, v>(main_in, nyq_in, out_main, out_nyq, tw, G, gscale, st, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
 }
 
 template <class T>
-void fft_div_axis0(int n, PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, cx<T>* out_nyq,
+void fft_div_axis0(int n, long px, PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, cx<T>* out_nyq,
                    const cx<T>* tw, const T* G, T gscale, hipStream_t st) {
-#define ML_CASE(v) if (n == v) return div_axis0_n<T, v>(in_main, in_nyq, out_main, out_nyq, tw, G, gscale, st);
+#define ML_CASE(v) if (n == v) return div_axis0_n<T, v>(in_main, in_nyq, out_main, out_nyq, tw, G, gscale, st, px);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
@@ -1288,23 +1294,23 @@ void fft_div_axis0(int n, PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, 
 
 // ---- batched launches (one launch per pass over the slots of a batch) ----
 template <class T>
-C2cArgs<T> fft_c2c_axis1_args(int n, cx<T>* main, cx<T>* nyq, const cx<T>* tw) {
+C2cArgs<T> fft_c2c_axis1_args(int n, long px, cx<T>* main, cx<T>* nyq, const cx<T>* tw) {
     C2cArgs<T> a{};
     const int W = lanes_w<T>(n);
-    a.va = ViewDesc{main, n / 2, 0, (int)((long)n * (n / 2) / W)};
-    a.vb = ViewDesc{nyq, 1, 1, n / W};
+    a.va = ViewDesc{main, n / 2, 0, (int)((long)n * (n / 2) / W), px / 2};
+    a.vb = ViewDesc{nyq, 1, 1, n / W, 0};
     a.tw = tw;
     a.on = 1;
     return a;
 }
 
 template <class T>
-DualArgs<T> fft_c2c_axis1_dual_args(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2,
+DualArgs<T> fft_c2c_axis1_dual_args(int n, long px, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2,
                                     const cx<T>* tw) {
     DualArgs<T> a{};
     const int W = lanes_w<T>(n);
-    a.va = ViewDesc{main, n / 2, 0, (int)((long)n * (n / 2) / W)};
-    a.vb = ViewDesc{nyq, 1, 1, n / W};
+    a.va = ViewDesc{main, n / 2, 0, (int)((long)n * (n / 2) / W), px / 2};
+    a.vb = ViewDesc{nyq, 1, 1, n / W, 0};
     a.dst2a = main2;
     a.dst2b = nyq2;
     a.tw = tw;
@@ -1313,12 +1319,12 @@ DualArgs<T> fft_c2c_axis1_dual_args(int n, cx<T>* main, cx<T>* nyq, cx<T>* main2
 }
 
 template <class T>
-GradArgs<T> fft_grad_axis0_args(int n, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main,
+GradArgs<T> fft_grad_axis0_args(int n, long px, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main,
                                 PtrTriple out_nyq, const cx<T>* tw, const T* G, T gscale) {
     GradArgs<T> a{};
     const int W = lanes_w<T>(n);
-    a.va = ViewDesc{main_in, (long)n * (n / 2), 0, (int)((long)n * (n / 2) / W)};
-    a.vb = ViewDesc{nyq_in, n, 0, n / W};
+    a.va = ViewDesc{main_in, px / 2, 0, (int)((long)n * (n / 2) / W), 0};
+    a.vb = ViewDesc{nyq_in, n, 0, n / W, 0};
     a.outa = out_main;
     a.outb = out_nyq;
     a.tw = tw;
@@ -1407,10 +1413,10 @@ void fft_grad_axis0_batch(int n, const GradArgs<T>* tab, int slots, hipStream_t 
 }
 
 #define ML_INST_BATCH(T)                                                                           \
-    template C2cArgs<T> fft_c2c_axis1_args<T>(int, cx<T>*, cx<T>*, const cx<T>*);                  \
-    template DualArgs<T> fft_c2c_axis1_dual_args<T>(int, cx<T>*, cx<T>*, cx<T>*, cx<T>*,           \
+    template C2cArgs<T> fft_c2c_axis1_args<T>(int, long, cx<T>*, cx<T>*, const cx<T>*);                  \
+    template DualArgs<T> fft_c2c_axis1_dual_args<T>(int, long, cx<T>*, cx<T>*, cx<T>*, cx<T>*,           \
                                                     const cx<T>*);                                \
-    template GradArgs<T> fft_grad_axis0_args<T>(int, cx<T>*, cx<T>*, PtrTriple, PtrTriple,         \
+    template GradArgs<T> fft_grad_axis0_args<T>(int, long, cx<T>*, cx<T>*, PtrTriple, PtrTriple,         \
                                                 const cx<T>*, const T*, T);                       \
     template void fft_r2c_rows_batch<T>(int, const R2cArgs<T>*, int, hipStream_t);                \
     template void fft_c2r_rows_batch<T>(int, const C2rArgs<T>*, int, hipStream_t);                \
@@ -1422,22 +1428,22 @@ ML_INST_BATCH(float)
 ML_INST_BATCH(double)
 
 #define ML_INST(T)                                                                                  \
-    template void fft_div_axis0<T>(int, PtrTriple, PtrTriple, cx<T>*, cx<T>*, const cx<T>*,        \
+    template void fft_div_axis0<T>(int, long, PtrTriple, PtrTriple, cx<T>*, cx<T>*, const cx<T>*,        \
                                    const T*, T, hipStream_t);                                       \
     template bool fft_supported<T>(int);                                                            \
-    template void fft_r2c_rows<T>(int, T*, cx<T>*, const cx<T>*, const cx<T>*, hipStream_t,        \
+    template void fft_r2c_rows<T>(int, long, T*, cx<T>*, const cx<T>*, const cx<T>*, hipStream_t,        \
                                   HaloMerge<T>);                                                  \
-    template void fft_c2r_rows<T>(int, T*, const cx<T>*, const cx<T>*, const cx<T>*, hipStream_t,  \
+    template void fft_c2r_rows<T>(int, long, T*, const cx<T>*, const cx<T>*, const cx<T>*, hipStream_t,  \
                                   bool);                                                          \
-    template void fft_c2r_rows3<T>(int, PtrTriple, PtrTriple, const cx<T>*, const cx<T>*,          \
+    template void fft_c2r_rows3<T>(int, long, PtrTriple, PtrTriple, const cx<T>*, const cx<T>*,          \
                                    hipStream_t);                                                  \
-    template void fft_c2c_axis1_inv_dual<T>(int, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*,   \
+    template void fft_c2c_axis1_inv_dual<T>(int, long, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*, cx<T>*,   \
                                             const cx<T>*, hipStream_t);                           \
-    template void fft_c2c_axis1<T>(int, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
-    template void fft_c2c_axis1_dual<T>(int, cx<T>*, cx<T>*, cx<T>*, cx<T>*, const cx<T>*,          \
+    template void fft_c2c_axis1<T>(int, long, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
+    template void fft_c2c_axis1_dual<T>(int, long, cx<T>*, cx<T>*, cx<T>*, cx<T>*, const cx<T>*,          \
                                         hipStream_t);                                             \
-    template void fft_c2c_axis0<T>(int, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
-    template void fft_grad_axis0<T>(int, cx<T>*, cx<T>*, PtrTriple, PtrTriple, const cx<T>*,        \
+    template void fft_c2c_axis0<T>(int, long, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
+    template void fft_grad_axis0<T>(int, long, cx<T>*, cx<T>*, PtrTriple, PtrTriple, const cx<T>*,        \
                                     const T*, T, hipStream_t);
 ML_INST(float)
 ML_INST(double)

@@ -25,7 +25,14 @@ struct Geo {
     int nt;      // tiles per side = nm / TILE
     long npart;  // np^3
     int ncb;     // sort blocks per tile column along axis 2 = nt * BPT
+    long px;     // mesh values from one plane of axis 0 to the next
 };
+
+// Values from one axis-0 plane of a force mesh to the next.  At 1024 a plane
+// of nm^2 would put a pencil's rows 4 MB apart, on the same memory channels:
+// an in-place pass over axis 0 then runs at 2.8 TB/s, with 544 values (17
+// lines) between planes at 4.4 (5.2 at 512, where such a gap gains nothing).
+inline long plane_values(int nm) { return (long)nm * nm + (nm == 1024 ? 544 : 0); }
 
 // Cell origin of sort block b (KX x TILE x TILE cells).
 __host__ __device__ __forceinline__ void block_origin(const Geo& g, int b, int& ox, int& oy,
@@ -76,9 +83,10 @@ __device__ __forceinline__ long lattice_index(uint32_t id, int np) {
 
 template <class T>
 void launch_fill(T* p, T v, long n, hipStream_t st);
-// dst[i] = s * src[i]
+// dst[i] = s * src[i] for planes of `plane` values, px apart in src and
+// adjacent in dst, n values in all
 template <class T>
-void launch_scale_copy(T* dst, const T* src, T s, long n, hipStream_t st);
+void launch_scale_copy(T* dst, const T* src, T s, long plane, long px, long n, hipStream_t st);
 void launch_fill_u32(uint32_t* p, uint32_t v, long n, hipStream_t st);
 // Device-to-device copies of arrays that do not overlap, in one launch;
 // false (nothing done) unless every address is a multiple of 16 and every

@@ -96,17 +96,17 @@ bool launch_copy_parts(const CopyParts& c, hipStream_t st) {
 }
 
 template <class T>
-__global__ void k_scale_copy(T* dst, const T* src, T s, long n) {
+__global__ void k_scale_copy(T* dst, const T* src, T s, long plane, long px, long n) {
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-        dst[i] = s * src[i];
+        dst[i] = s * src[(i / plane) * px + i % plane];
 }
 
 template <class T>
-void launch_scale_copy(T* dst, const T* src, T s, long n, hipStream_t st) {
+void launch_scale_copy(T* dst, const T* src, T s, long plane, long px, long n, hipStream_t st) {
     long blocks = (n + PB - 1) / PB;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_scale_copy<T>, dim3(blocks), dim3(PB), 0, st, dst, src, s, n);
+    hipLaunchKernelGGL(k_scale_copy<T>, dim3(blocks), dim3(PB), 0, st, dst, src, s, plane, px, n);
 }
 
 // ---------------------------------------------------------------------------
@@ -605,7 +605,7 @@ __device__ __forceinline__ void paint_group_body(Parts<T> p, SortBufs s, Geo g, 
     constexpr int NI = TILE * TILE * BX::LZ;
     for (int i = tid; i < NI; i += PBP) {
         int x = i / (TILE * BX::LZ), y = (i / BX::LZ) % TILE, z = i % BX::LZ;
-        rho[((ox + x) * nm + (oy + y)) * nm + (oz + z)] =
+        rho[(ox + x) * g.px + (oy + y) * nm + (oz + z)] =
             A::dec(box[(x * TE + y) * BX::EZ + z], inv_scale);
     }
     for (int h = tid; h < BX::HALO; h += PBP) {
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(PB) void k_paint_halo_group(T* rho, const T* halo, 
         else if (f < 31 * LZ) { int h = f - TILE * LZ; lx = 1 + h / LZ; ly = 0; lz = h % LZ; }
         else { int h = f - 31 * LZ; lx = 1 + h / 15; ly = 1 + h % 15; lz = 0; }
         const int X = tx * TILE + lx, Y = ty * TILE + ly, Z = gz * LZ + lz;
-        rho[((long)X * nm + Y) * nm + Z] += halo_sum_g<T, G>(halo, nt, X, Y, Z);
+        rho[X * g.px + Y * nm + Z] += halo_sum_g<T, G>(halo, nt, X, Y, Z);
     }
 }
 
@@ -901,7 +901,7 @@ __device__ __forceinline__ void readout_body(Parts<T> p, SortBufs s, Geo g, cons
                 if (gx >= nm) gx -= nm;
                 if (gy >= nm) gy -= nm;
                 if (gz >= nm) gz -= nm;
-                long c = ((long)gx * nm + gy) * nm + gz;
+                long c = gx * g.px + (long)gy * nm + gz;
                 v0[it] = f0[c];
                 v1[it] = f1[c];
                 v2[it] = f2[c];
@@ -1227,7 +1227,7 @@ ML_INST_BATCH(double)
 
 #define ML_INST(T)                                                                                \
     template void launch_fill<T>(T*, T, long, hipStream_t);                                       \
-    template void launch_scale_copy<T>(T*, const T*, T, long, hipStream_t);                       \
+    template void launch_scale_copy<T>(T*, const T*, T, long, long, long, hipStream_t);           \
     template void launch_kick_drift_key<T>(Parts<T>, SortBufs, Geo, T, T, int, uint32_t*,        \
                                            hipStream_t);                                          \
     template void launch_scatter<T>(Parts<T>, Parts<T>, SortBufs, Geo, hipStream_t, TanCarry<T>); \

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(16, 16), (32, 64), (48, 96), (64, 128), (96, 192), (128, 256),
-                                   (192, 384), (256, 512), (384, 768)],
+                                   (192, 384), (256, 512), (384, 768), (512, 1024)],
                          ids=lambda s: f"{s[0]}p{s[1]}m")
 def test_force_tangent_and_its_transpose_agree(shape):
     """<v, J u> = <J^T v, u> for the force's derivative J at a clustered state,
@@ -24,8 +24,11 @@ def test_force_tangent_and_its_transpose_agree(shape):
     np_side, nm = shape
     box, a0, a1 = float(np_side), 0.5, 0.55
     wl = W.Workload("pair", np_side, nm, box, 0.1, 1.0, 4, 16, 2.0, (1.0,))
-    x = torch.from_numpy(W.clustered_positions(np_side, nm, box, seed=3)).float()
     gen = torch.Generator().manual_seed(4)
+    if nm < 1024:
+        x = torch.from_numpy(W.clustered_positions(np_side, nm, box, seed=3)).float()
+    else:  # (minutes of numpy)
+        x = torch.rand((3, np_side ** 3), generator=gen) * box
     u = torch.randn(x.shape, generator=gen)
     from paper_2012_07266_amd._lib import PM_MODE_TANGENT
     log(f"force and transpose {shape}")
@@ -47,14 +50,15 @@ def test_force_tangent_and_its_transpose_agree(shape):
 
 
 @pytest.mark.parametrize("force", [False, True], ids=["state", "force"])
-@pytest.mark.parametrize("shape", [(16, 16), (16, 32), (48, 96)], ids=lambda s: f"{s[0]}p{s[1]}m")
+@pytest.mark.parametrize("shape", [(16, 16), (16, 32), (48, 96), (512, 1024)],
+                         ids=lambda s: f"{s[0]}p{s[1]}m")
 def test_checkpoint_into_any_buffer(shape, force):
     """Saved into aligned memory and 4 bytes off it, a checkpoint is the same
     bytes, and restores the same state and force."""
     from paper_2012_07266_amd import Simulation, lib
     np_side, nm = shape
     log(f"checkpoint copies {shape} force={force}")
-    x = torch.from_numpy(W.random_positions(np_side ** 3, 32.0, 7)).float()
+    x = torch.rand((3, np_side ** 3), generator=torch.Generator().manual_seed(7)) * 32.0
     with Simulation(np_side, nm, 32.0, 32, 2.0, (1.0,), ckpt_force=force) as sim:
         sim.set_state(x, 0.01 * x, 0.5)
         sim.step(0.5, 0.55)
@@ -66,7 +70,7 @@ def test_checkpoint_into_any_buffer(shape, force):
         assert torch.equal(bufs[0][:n], bufs[1][4:4 + n])
         assert not bufs[0][n:].any() and not bufs[1][4 + n:].any()
         for off, b in zip((0, 4), bufs):
-            sim.set_state(x, x, 0.6)
+            sim.set_state(0.9 * x, x, 0.6)
             assert lib().pm_checkpoint_load(sim._h, ctypes.c_void_p(b.data_ptr() + off),
                                             ctypes.c_double(0.55)) == 0
             assert all(torch.equal(a, b) for a, b in zip(sim.get_state(), want))
