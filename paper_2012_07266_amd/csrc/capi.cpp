@@ -997,7 +997,14 @@ template <class T> struct Sim final : SimBase {
     // most 4/5 of the scratch that is free: xbc and fbc, and with `meshes`
     // (nothing in them yet) also the meshes and the halo before them in the
     // arena.  Else `on` stays 0 and the shell is projected by regions alone.
-    LensBins<T> lens_bins(const LensArgs<T>& la, bool meshes) const {
+    // So it is with `beside` (the projection runs beside the transform, la.rs
+    // is the walk's region side) where the walk by regions is the better one:
+    // in float32 without options, with at least four regions per CU whose
+    // pencils are wider than a tile, so that it rejects few images.  Steps at
+    // 256^3/512^3, four 2048^2 maps, bins against walk: pencils of 23 to 29
+    // cells, whose images would take the meshes before the paint, 3.53 and
+    // 3.47 ms; 16 to 21 cells 3.70 and 3.70; narrower ones stay binned.
+    LensBins<T> lens_bins(const LensArgs<T>& la, bool meshes, bool beside = false) const {
         LensBins<T> b;
         size_t at_cnt;
         if (!bin_counters(b, at_cnt)) return b;
@@ -1005,6 +1012,11 @@ template <class T> struct Sim final : SimBase {
         const size_t at_ent = meshes ? ap.mesh[0] : ap.xbc;
         const size_t cap = (at_cnt - at_ent) / (3 * sizeof(T));
         if (!(shell_images(la) <= 0.8 * (double)cap)) return b;
+        if (sizeof(T) == 4 && beside && !interp && !pgd && !rot) {
+            const double pencil = la.rs * (fov * PI / 180.0 / npix) * 0.5 * (la.cnear_d + la.cfar_d);
+            const long side = (npix + la.rs - 1) / la.rs;
+            if (side * side >= 1024 && pencil > TILE) return b;
+        }
         const double chi_far = la.cfar_d * cell;
         const double half = half_map();
         // tiles per unit: one when replicas are rotated; else as many as
@@ -1028,6 +1040,7 @@ template <class T> struct Sim final : SimBase {
     // meshes hold nothing yet and may be used as scratch.
     int project_shell(double a0, double a1, T* kappa, T sub_k2 = T(0), hipStream_t ls = nullptr,
                       bool meshes = false) {
+        const bool beside = ls != nullptr;
         if (!ls) ls = st;
         LensArgs<T> la;
         MapAdd<T> mv;
@@ -1054,7 +1067,7 @@ template <class T> struct Sim final : SimBase {
         }
         if (interp || pgd) plan_sources(la, cosmo.chi(a1), cosmo.chi(a0), false);
         ProfScope ps(prof, "lens_gather", ls);
-        LensBins<T> bn = lens_bins(la, meshes);
+        LensBins<T> bn = lens_bins(la, meshes, beside);
         if (bn.on) {
             la.rs = bin_side(npix);
             clear_bins(bn, ls);
@@ -1094,21 +1107,21 @@ template <class T> struct Sim final : SimBase {
         return PM_OK;
     }
 
-    // Whether the shell's images are binned in xbc and fbc.
+    // Whether the shell's images are binned in xbc and fbc beside the transform.
     bool shell_binned(double a0, double a1) const {
         LensArgs<T> la;
         MapAdd<T> mv;
-        return plain_lens_args(a0, a1, la, mv) && lens_bins(la, false).on;
+        return plain_lens_args(a0, a1, la, mv) && lens_bins(la, false, true).on;
     }
 
     // Whether the shell's images go to the meshes: they outgrow xbc and fbc,
     // and fit with the meshes (or, in double precision, are cut to fit).
-    bool shell_takes_meshes(double a0, double a1) const {
+    bool shell_takes_meshes(double a0, double a1, bool beside = false) const {
         LensArgs<T> la;
         MapAdd<T> mv;
         if (pgd || !plain_lens_args(a0, a1, la, mv)) return false;
-        if (lens_bins(la, false).on) return false;
-        return sizeof(T) == 8 || lens_bins(la, true).on;
+        if (lens_bins(la, false, beside).on) return false;
+        return sizeof(T) == 8 || lens_bins(la, true, beside).on;
     }
 
     // nsteps KDK steps along agrid with the projection of every shell: the
@@ -1135,7 +1148,7 @@ template <class T> struct Sim final : SimBase {
             // (and the projection needs the shift); without, the projection
             // runs on the second stream beside the transform
             // the meshes are free until the paint
-            const bool early = shell_takes_meshes(a0, a1);
+            const bool early = shell_takes_meshes(a0, a1, st_lens != nullptr);
             if (pgd || !st_lens || early) {
                 int rc;
                 if (early) {

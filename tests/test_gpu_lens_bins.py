@@ -75,3 +75,34 @@ def test_binned_shell_matches_oracle(dtype, name):
         log(f"kappa rel-rms {rel_rms(kg, ko):.2e}, vs particle term {e_part:.2e}")
         assert rel_rms(kg, ko) <= (1e-10 if dtype == torch.float64 else 1e-4)
         assert e_part <= (1e-12 if dtype == torch.float64 else 1e-5)
+
+
+# a_i, a_f, steps: shells of 64^3 particles on 128^3 meshes whose pencils of
+# 64 of 2048 pixels are 22 cells wide, wider than a tile: with images that
+# outgrow the sort's scratch (5 a particle) and that fit it (0.8); and such
+# shells on both sides of that width (16.2 to 15.7 cells, 1.7 a particle)
+FAR = {"many_images": (0.45, 0.4518, 2), "few_images": (0.45, 0.4503, 2),
+       "both_widths": (0.555, 0.567, 16)}
+
+
+@pytest.mark.parametrize("name", list(FAR))
+def test_far_shells_beside_the_transform_match_the_steps(name):
+    """The images of a far shell are walked by regions in a run and binned in
+    a projection by itself.  The images' values and their fixed-point sums are
+    the same on both routes, so the float32 maps are equal bit for bit."""
+    a_i, a_f, steps = FAR[name]
+    wl = W.Workload(name, 64, 128, 42.0, a_i, a_f, steps, 2048, 5.0, (1.5, 2.0))
+    x = torch.from_numpy(particles(64, 128, 42.0, "clustered"))
+    a = np.linspace(a_i, a_f, steps + 1)
+    log(f"far shells {name}")
+    with new_sim(wl, torch.float32) as sim:
+        k1, k2 = sim.new_maps(), sim.new_maps()
+        sim.set_state(x, torch.zeros_like(x), a_i)
+        for a0, a1 in zip(a[:-1], a[1:]):
+            sim.step(a0, a1)
+            sim.lens(a0, a1, k1)
+        sim.set_state(x, torch.zeros_like(x), a_i)
+        sim.steps(a, k2)
+        sim.sync()
+        assert float(k1.abs().max()) > 0
+        assert torch.equal(k1, k2)
