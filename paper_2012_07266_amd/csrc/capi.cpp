@@ -963,20 +963,19 @@ template <class T> struct Sim final : SimBase {
     // in the arena; false when a map of this size leaves no room for them.
     bool bin_counters(LensBins<T>& b, size_t& at) const {
         const int nreg = (npix + bin_side(npix) - 1) / bin_side(npix);
-        const size_t bytes = (3 * (size_t)nreg * nreg + 1) * sizeof(uint32_t);
+        const size_t bytes = (3 * (size_t)nreg * nreg + 2) * sizeof(uint32_t);
         const size_t end = ap.fbc + 3 * (size_t)geo.npart * sizeof(T);
         if (bytes + 256 > end - ap.xbc) return false;
         at = (end - bytes) & ~size_t(255);
         b.nreg2 = nreg * nreg;
-        b.cnt = reinterpret_cast<uint32_t*>(arena + at);
-        b.begin = b.cnt + b.nreg2;
-        b.cur = b.cnt + 2 * b.nreg2;
-        b.pool = b.cnt + 3 * b.nreg2;
+        b.cur = reinterpret_cast<unsigned long long*>(arena + at);
+        b.pool = b.cur + b.nreg2;
+        b.begin = reinterpret_cast<uint32_t*>(b.pool + 1);
         return true;
     }
     void clear_bins(const LensBins<T>& b, hipStream_t s) {
         if (bins_clear) return;
-        launch_fill_u32(b.cnt, 0u, 3L * b.nreg2 + 1, s);
+        launch_fill_u32(reinterpret_cast<uint32_t*>(b.cur), 0u, 2L * b.nreg2 + 2, s);
         bins_clear = true;
     }
 

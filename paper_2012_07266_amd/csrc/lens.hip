@@ -493,12 +493,10 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     if (bn.on) {
         // the region's images wait in its bin: no particle is visited, unless
         // the bins overflowed (then the region is walked as without bins)
-        const uint32_t e0 = bn.begin[b], e1 = bn.cur[b];
-        if (tid == 0) {  // the counters' state between two projections
-            bn.cnt[b] = 0u;
-            if (b == 0) *bn.pool = 0u;
-        }
-        if (e1 <= bn.cap) {
+        const unsigned long long end = bn.cur[b];
+        if (b == 0 && tid == 0) *bn.pool = 0ull;
+        if (end <= bn.cap) {
+            const uint32_t e0 = bn.begin[b], e1 = (uint32_t)end;
             nz1 = nz0 - 1;
             constexpr int EU = 4;  // images per thread in flight
             for (uint32_t e = e0 + tid; e < e1; e += LG * EU) {
@@ -633,6 +631,7 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
         if (lane < qn) deposit(q[lane], q[LQ + lane], q[2 * LQ + lane]);
     }
     __syncthreads();
+    if (bn.on && tid == 0) bn.cur[b] = 0ull;  // as between two projections
     read_maps(tid);
     // the region's pixels of every map; a thread reads KU of them before it
     // writes any, since each read is a round trip to memory
@@ -682,7 +681,8 @@ __global__ __launch_bounds__(LG) void k_lens_gather_b(const LensGatherArgs<T>* _
 // its four pixels lies in.  Within a workgroup ranks are taken in LDS, one
 // global atomic per region and batch of particles.  A region whose segment
 // ends past the buffer is walked as before (clustering beyond what the host
-// allowed for).
+// allowed for); places are 64-bit until they are known to lie in the buffer,
+// since a crowded shell can have more than 2^32 images.
 // Measured (a late shell, walk by regions -> count + place + fill + gather):
 // 256^3/512^3, four 2048^2 maps 1.02 -> 0.041 + 0.005 + 0.065 + 0.096 ms;
 // 512^3/1024^3, ten 4096^2 maps 15.2 -> 0.056 + 0.005 + 0.086 + 0.66 ms;
@@ -827,7 +827,7 @@ __device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs&
                             if (l >= 0) rank[u][q] = atomicAdd(&cnt[l], 1u);
                         } else {
                             if (l >= 0) atomicAdd(&cnt[l], 1u);
-                            else atomicAdd(&bn.cnt[r * nreg + c], 1u);
+                            else atomicAdd(&bn.cur[r * nreg + c], 1ull);
                         }
                     });
                 }
@@ -836,8 +836,11 @@ __device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs&
                         __syncthreads();
                         for (int i = tid; i < nloc; i += LBT)
                             if (cnt[i]) {
-                                first[i] =
-                                    atomicAdd(&bn.cur[(r0 + i / nc) * nreg + c0 + i % nc], cnt[i]);
+                                const unsigned long long f =
+                                    atomicAdd(&bn.cur[(r0 + i / nc) * nreg + c0 + i % nc],
+                                              (unsigned long long)cnt[i]);
+                                // (no place past the buffer plus a rank wraps)
+                                first[i] = (uint32_t)min(f, (unsigned long long)bn.cap);
                                 cnt[i] = 0u;
                             }
                         __syncthreads();
@@ -847,8 +850,9 @@ __device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs&
                         if (!ok[u]) continue;
                         touched(t0[u], t1[u], [&](int q, int r, int c) {
                             const int l = local(r, c);
-                            const uint32_t e = l >= 0 ? first[l] + rank[u][q]
-                                                      : atomicAdd(&bn.cur[r * nreg + c], 1u);
+                            const unsigned long long e =
+                                l >= 0 ? first[l] + rank[u][q]
+                                       : atomicAdd(&bn.cur[r * nreg + c], 1ull);
                             if (e >= bn.cap) return;
                             T* o = bn.ent + (size_t)e * 3;
                             o[0] = t0[u];
@@ -863,7 +867,8 @@ __device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs&
                 if (in_lds)
                     for (int i = tid; i < nloc; i += LBT)
                         if (cnt[i])
-                            atomicAdd(&bn.cnt[(r0 + i / nc) * nreg + c0 + i % nc], cnt[i]);
+                            atomicAdd(&bn.cur[(r0 + i / nc) * nreg + c0 + i % nc],
+                                      (unsigned long long)cnt[i]);
             }
             __syncthreads();  // before the next unit's counters
         }
@@ -883,42 +888,48 @@ __global__ __launch_bounds__(LBT) void k_lens_bin_b(const LensGatherArgs<T>* __r
 }
 
 // Segments of the regions: exclusive prefix of the counts within a workgroup,
-// workgroups in any order (one atomic each).
-__device__ __forceinline__ void lens_place_body(const uint32_t* count, uint32_t* begin,
-                                                uint32_t* cur, uint32_t* pool, int n) {
-    __shared__ uint32_t ws[16], base;
+// workgroups in any order (one atomic each).  A region's count becomes its
+// fill cursor; its first entry is stored too, which only a region whose
+// segment ends in the buffer reads.
+__device__ __forceinline__ void lens_place_body(uint32_t* begin, unsigned long long* cur,
+                                                unsigned long long* pool, int n) {
+    using U = unsigned long long;
+    __shared__ U ws[16], base;
     const int i = blockIdx.x * 1024 + threadIdx.x, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const uint32_t v = i < n ? count[i] : 0u;
-    uint32_t x = v;
+    const U v = i < n ? cur[i] : 0ull;
+    U x = v;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
+        const U y = __shfl_up(x, o, 64);
         if (lane >= o) x += y;
     }
     if (lane == 63) ws[wid] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t t = 0;
+        U t = 0;
         for (int w = 0; w < 16; ++w) {
-            const uint32_t c = ws[w];
+            const U c = ws[w];
             ws[w] = t;
             t += c;
         }
         base = atomicAdd(pool, t);
     }
     __syncthreads();
-    if (i < n) begin[i] = cur[i] = base + ws[wid] + x - v;
+    if (i < n) {
+        cur[i] = base + ws[wid] + x - v;
+        begin[i] = (uint32_t)cur[i];
+    }
 }
 
 template <class T>
 __global__ __launch_bounds__(1024) void k_lens_place(LensBins<T> bn) {
-    lens_place_body(bn.cnt, bn.begin, bn.cur, bn.pool, bn.nreg2);
+    lens_place_body(bn.begin, bn.cur, bn.pool, bn.nreg2);
 }
 template <class T>
 __global__ __launch_bounds__(1024) void k_lens_place_b(const LensGatherArgs<T>* __restrict__ tab) {
     const LensGatherArgs<T>& a = tab[blockIdx.y];
     if (!a.on || !a.bins.on) return;
-    lens_place_body(a.bins.cnt, a.bins.begin, a.bins.cur, a.bins.pool, a.bins.nreg2);
+    lens_place_body(a.bins.begin, a.bins.cur, a.bins.pool, a.bins.nreg2);
 }
 
 // LDS bytes after the accumulator for the D(a(chi)) window of sub-evolution

@@ -287,14 +287,14 @@ __device__ __forceinline__ void split_cell(T u, int& c, T& f) {
     f = u - fl;
 }
 // Scratch of a projection that sorts its images by map region first (on != 0).
-// cnt and *pool are zero between projections; the gather leaves them so.
+// cur and *pool are zero between projections; the gather leaves them so.
 template <class T> struct LensBins {
     int on = 0;
-    int nreg2 = 0;              // regions of the map, ceil(npix / rs)^2
-    uint32_t* cnt = nullptr;    // [nreg2] images per region
-    uint32_t* begin = nullptr;  // [nreg2] first entry of a region's segment
-    uint32_t* cur = nullptr;    // [nreg2] fill cursor, then the segment's end
-    uint32_t* pool = nullptr;   // [1] entries given out
+    int nreg2 = 0;  // regions of the map, ceil(npix / rs)^2
+    // [nreg2] images of a region, then its fill cursor, then its segment's end
+    unsigned long long* cur = nullptr;
+    unsigned long long* pool = nullptr;  // [1] entries given out
+    uint32_t* begin = nullptr;  // [nreg2] first entry of a segment that ends in the buffer
     T* ent = nullptr;           // [cap][3] t0, t1, chi
     uint32_t cap = 0;
     int zt = 1;                 // tiles per unit of the binning passes
