@@ -788,9 +788,10 @@ template <class T> struct Sim final : SimBase {
         if (pgd) pgd_shift(a1);
         // (the force meshes are recomputed where a reverse step needs them;
         // checkpoints that carry them need them at once)
-        const bool meshes = !ckpt_force() && shell_takes_meshes(a0, a1);
-        int rc = project_shell(a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0), nullptr,
-                               meshes);
+        const Shell sh = shell_of(a0, a1);
+        const bool meshes = !ckpt_force() && shell_takes_meshes(sh);
+        int rc = project_shell(sh, a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0),
+                               nullptr, meshes);
         if (meshes) meshes_valid = false;
         return rc ? rc : check_launch();
     }
@@ -873,19 +874,27 @@ template <class T> struct Sim final : SimBase {
     }
 
     // The plain projection's arguments and mean terms of the shell
-    // (chi(a1), chi(a0)]; false when the shell lies wholly behind the
+    // (chi(a1), chi(a0)]; not `on` when the shell lies wholly behind the
     // farthest source plane (its images and its mean term both need
-    // chi < chi_s, so it adds nothing).
-    bool plain_lens_args(double a0, double a1, LensArgs<T>& la, MapAdd<T>& mv) const {
-        la = LensArgs<T>{};
-        mv = MapAdd<T>{};
+    // chi < chi_s, so it adds nothing).  Evaluated once per projection: a mean
+    // term inverts chi(a) at every node of its quadrature, 50 us of host time
+    // per source plane.
+    struct Shell {
+        bool on = false;
+        LensArgs<T> la{};
+        MapAdd<T> mv{};
+    };
+    Shell shell_of(double a0, double a1) const {
+        Shell sh;
+        LensArgs<T>& la = sh.la;
         la.npix = npix;
         la.nsrc = nsrc;
         la.cell = (T)cell;
         double chi_far = cosmo.chi(a0), chi_near = cosmo.chi(a1);
         double chis_max = 0;
         for (double c : chisrc) chis_max = std::max(chis_max, c);
-        if (chi_near >= chis_max) return false;
+        if (chi_near >= chis_max) return sh;
+        sh.on = true;
         la.chi_near = (T)chi_near;
         la.chi_far = (T)chi_far;
         la.cnear_d = chi_near / cell;
@@ -899,8 +908,8 @@ template <class T> struct Sim final : SimBase {
         la.ntab = ATAB_N;
         la.dchi = (T)dchi_tab;
         plan_sources(la, chi_near, chi_far, true);
-        for (int s = 0; s < nsrc; ++s) mv.v[s] = (T)cosmo.shell_mean(chi_near, chi_far, chisrc[s]);
-        return true;
+        for (int s = 0; s < nsrc; ++s) sh.mv.v[s] = (T)cosmo.shell_mean(chi_near, chi_far, chisrc[s]);
+        return sh;
     }
 
     // Which maps take which images of the shell (chi_near, chi_far]: a
@@ -1032,18 +1041,18 @@ template <class T> struct Sim final : SimBase {
         return b;
     }
 
-    // Born projection of the shell (chi(a1), chi(a0)] of the current,
+    // Born projection of sh, the shell (chi(a1), chi(a0)], of the current,
     // tile-sorted positions (which must be those at a1) into kappa.  With
     // sub-evolution the step's drift momentum is mom - sub_k2 * acc.
     // With PGD on, pgd_shift must have run for the current state.  meshes: the
     // meshes hold nothing yet and may be used as scratch.
-    int project_shell(double a0, double a1, T* kappa, T sub_k2 = T(0), hipStream_t ls = nullptr,
-                      bool meshes = false) {
+    int project_shell(const Shell& sh, double a0, double a1, T* kappa, T sub_k2 = T(0),
+                      hipStream_t ls = nullptr, bool meshes = false) {
         const bool beside = ls != nullptr;
         if (!ls) ls = st;
-        LensArgs<T> la;
-        MapAdd<T> mv;
-        if (!plain_lens_args(a0, a1, la, mv)) return PM_OK;
+        if (!sh.on) return PM_OK;
+        LensArgs<T> la = sh.la;
+        MapAdd<T> mv = sh.mv;
         la.rot = rot ? 1 : 0;
         la.rot_seed = (unsigned long long)rot_seed;
         if (interp) {
@@ -1107,20 +1116,14 @@ template <class T> struct Sim final : SimBase {
     }
 
     // Whether the shell's images are binned in xbc and fbc beside the transform.
-    bool shell_binned(double a0, double a1) const {
-        LensArgs<T> la;
-        MapAdd<T> mv;
-        return plain_lens_args(a0, a1, la, mv) && lens_bins(la, false, true).on;
-    }
+    bool shell_binned(const Shell& sh) const { return sh.on && lens_bins(sh.la, false, true).on; }
 
     // Whether the shell's images go to the meshes: they outgrow xbc and fbc,
     // and fit with the meshes (or, in double precision, are cut to fit).
-    bool shell_takes_meshes(double a0, double a1, bool beside = false) const {
-        LensArgs<T> la;
-        MapAdd<T> mv;
-        if (pgd || !plain_lens_args(a0, a1, la, mv)) return false;
-        if (lens_bins(la, false, beside).on) return false;
-        return sizeof(T) == 8 || lens_bins(la, true, beside).on;
+    bool shell_takes_meshes(const Shell& sh, bool beside = false) const {
+        if (pgd || !sh.on) return false;
+        if (lens_bins(sh.la, false, beside).on) return false;
+        return sizeof(T) == 8 || lens_bins(sh.la, true, beside).on;
     }
 
     // nsteps KDK steps along agrid with the projection of every shell: the
@@ -1147,16 +1150,17 @@ template <class T> struct Sim final : SimBase {
             // (and the projection needs the shift); without, the projection
             // runs on the second stream beside the transform
             // the meshes are free until the paint
-            const bool early = shell_takes_meshes(a0, a1, st_lens != nullptr);
+            const Shell sh = shell_of(a0, a1);
+            const bool early = shell_takes_meshes(sh, st_lens != nullptr);
             if (pgd || !st_lens || early) {
                 int rc;
                 if (early) {
-                    if ((rc = project_shell(a0, a1, kap, T(0), nullptr, true))) return rc;
+                    if ((rc = project_shell(sh, a0, a1, kap, T(0), nullptr, true))) return rc;
                     paint(true);
                 } else {
                     if (pgd) pgd_shift(a1);
                     else paint(true);
-                    rc = project_shell(a0, a1, kap, T(0));  // mom is the drift momentum here
+                    rc = project_shell(sh, a0, a1, kap, T(0));  // mom is the drift momentum here
                     if (rc) return rc;
                 }
                 if (pgd) force_from_spectrum();
@@ -1178,10 +1182,10 @@ template <class T> struct Sim final : SimBase {
                         rc = PM_EDEVICE;
                         return;
                     }
-                    rc = project_shell(a0, a1, kap, T(0), st_lens);
+                    rc = project_shell(sh, a0, a1, kap, T(0), st_lens);
                     if (hipEventRecord(ev_join, st_lens) != hipSuccess && !rc) rc = PM_EDEVICE;
                 };
-                const bool binned = shell_binned(a0, a1);
+                const bool binned = shell_binned(sh);
                 paint(true);
                 fft_forward_grad(P.nm, nullptr, tw_nm, tw_hm, twp_nm, paint_halo_merge<T>(geo, halo),
                                  binned ? std::function<void()>() : std::function<void()>(shell),
@@ -1804,7 +1808,9 @@ template <class T> struct Sim final : SimBase {
         std::swap(cur.id, alt.id);
         o.paint = PaintArgs<T>{cur, sb, geo, (T)std::pow((double)geo.B, 3), mesh[0], halo, 1};
         o.lens = LensGatherArgs<T>{};
-        if (kappa && plain_lens_args(a0, a1, o.lens.la, o.lens.mean)) {
+        if (const Shell sh = kappa ? shell_of(a0, a1) : Shell(); sh.on) {
+            o.lens.la = sh.la;
+            o.lens.mean = sh.mv;
             // the batch's grid has one region side for every shell: one
             // accumulator per source
             o.lens.la.dec = 0;
