@@ -850,9 +850,10 @@ __device__ __forceinline__ void lens_bin_body(const Parts<T>& p, const SortBufs&
                         if (!ok[u]) continue;
                         touched(t0[u], t1[u], [&](int q, int r, int c) {
                             const int l = local(r, c);
-                            const unsigned long long e =
+                            const uint32_t e =
                                 l >= 0 ? first[l] + rank[u][q]
-                                       : atomicAdd(&bn.cur[r * nreg + c], 1ull);
+                                       : (uint32_t)min(atomicAdd(&bn.cur[r * nreg + c], 1ull),
+                                                       (unsigned long long)bn.cap);
                             if (e >= bn.cap) return;
                             T* o = bn.ent + (size_t)e * 3;
                             o[0] = t0[u];
