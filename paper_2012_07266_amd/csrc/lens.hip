@@ -333,11 +333,17 @@ template <class T> constexpr size_t lens_queue_bytes(int lg) {
     return sizeof(T) == 4 ? (size_t)(lg / 64) * 3 * LQ * sizeof(T) : 0;
 }
 
-// LG threads per workgroup: 256 for 32 x 32-pixel regions, 1024 for 64 x 64
-// (one workgroup per CU then holds the LDS, so it brings 16 waves)
+// LG threads per workgroup: a walk takes 256 for 32 x 32-pixel regions, 1024
+// for 64 x 64 (one workgroup per CU then holds the LDS, so it brings 16
+// waves); with bins 512 for 32 x 32, 256 for 16 x 16 and 8 x 8.
 // DEC: the maps of the sources beyond the shell come from the shared
 // accumulators A and B (la.dec); else one accumulator per source.
-template <class T, int LG, bool EXT, bool DEC>
+// BIN: the region's images wait in its bin, and a walk is only for a region
+// whose bin overflowed.  A template argument, so that the walk's kernels hold
+// nothing of the bins: as one kernel the plain walk took 97 to 99 registers
+// instead of 91 to 96, a wave per SIMD less, and a shell of 64^3 particles on
+// 64 regions 0.39 ms instead of 0.375.
+template <class T, int LG, bool EXT, bool DEC, bool BIN>
 __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBufs& sb,
                                                  const Geo& g, const LensArgs<T>& la,
                                                  const MapAdd<T>& mean, T* kappa,
@@ -345,7 +351,7 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     using A = LensAcc<T>;
     using S = typename A::S;
     constexpr int LUT = sizeof(T) == 4 ? LU : LU / 2;  // registers of double
-    constexpr bool COMPACT = sizeof(T) == 4;
+    constexpr bool COMPACT = sizeof(T) == 4 && !BIN;  // (an overflowed region has no queue)
     extern __shared__ unsigned char smem[];
     S* acc = reinterpret_cast<S*>(smem);
     const int rs = la.rs;
@@ -362,15 +368,15 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     const int rs2 = rs * rs;
     const int ncell = (DEC ? la.nacc : la.nsrc) * rs2;
     for (int i = tid; i < ncell; i += LG) acc[i] = S(0);
-    // sub-evolution: the part of the D(a(chi)) table that end-of-step
-    // depths in the shell can reach (one entry of margin below, two above)
-    // is copied after the accumulator when it fits in la.dwin entries; the
-    // clamp to the window never moves an index of such a depth, so the
-    // values are those of the table itself
+    // a walk with sub-evolution: the part of the D(a(chi)) table that
+    // end-of-step depths in the shell can reach (one entry of margin below,
+    // two above) is copied after the accumulator when it fits in la.dwin
+    // entries; the clamp to the window never moves an index of such a depth,
+    // so the values are those of the table itself
     T* dw = reinterpret_cast<T*>(acc + ncell);
     int d_lo = 0, d_hi = 0;
     bool d_lds = false;
-    if (EXT && la.sub) {
+    if (EXT && !BIN && la.sub) {
         d_lo = min(max((int)floor(la.chi_near / la.dchi) - 1, 0), la.ntab - 2);
         d_hi = min(max((int)floor(la.chi_far / la.dchi) + 2, d_lo + 1), la.ntab - 1);
         d_lds = d_hi - d_lo + 1 <= la.dwin;
@@ -443,10 +449,6 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     const int lane = tid & 63;
     int qn = 0;
     auto queue_push = [&](bool ok, T t0, T t1, T chi) {
-        if (bn.on) {  // the walk of an overflowed region has no queue
-            if (ok) deposit(t0, t1, chi);
-            return;
-        }
         const unsigned long long m = __ballot(ok);
         if (!m) return;
         if (ok) {
@@ -473,7 +475,7 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     int nz0 = (int)floor(cnear / nmf) - 1;
     if (nz0 < 0) nz0 = 0;
     int nz1 = (int)floor(cmax / nmf) + (zclip > T(0) ? 1 : 0);
-    // the first of the map values that the region adds to
+    // the map values that the region adds to, KU of a thread at a time
     constexpr int KU = 8;
     const int npx = la.nsrc * rs2;
     T k_old[KU];
@@ -490,9 +492,7 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
             k_old[u] = k_at[u] >= 0 ? kappa[k_at[u]] : T(0);
         }
     };
-    if (bn.on) {
-        // the region's images wait in its bin: no particle is visited, unless
-        // the bins overflowed (then the region is walked as without bins)
+    if constexpr (BIN) {
         const unsigned long long end = bn.cur[b];
         if (b == 0 && tid == 0) *bn.pool = 0ull;
         if (end <= bn.cap) {
@@ -631,7 +631,7 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
         if (lane < qn) deposit(q[lane], q[LQ + lane], q[2 * LQ + lane]);
     }
     __syncthreads();
-    if (bn.on && tid == 0) bn.cur[b] = 0ull;  // as between two projections
+    if (BIN && tid == 0) bn.cur[b] = 0ull;  // as between two projections
     read_maps(tid);
     // the region's pixels of every map; a thread reads KU of them before it
     // writes any, since each read is a round trip to memory
@@ -658,14 +658,23 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
 
 template <class T, int LG, bool EXT, bool DEC>
 __global__ __launch_bounds__(LG) void k_lens_gather(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
-                                                    MapAdd<T> mean, T* kappa, LensBins<T> bn) {
-    lens_gather_body<T, LG, EXT, DEC>(p, sb, g, la, mean, kappa, bn);
+                                                    MapAdd<T> mean, T* kappa) {
+    lens_gather_body<T, LG, EXT, DEC, false>(p, sb, g, la, mean, kappa, LensBins<T>());
+}
+template <class T, int LG, bool EXT, bool DEC>
+__global__ __launch_bounds__(LG) void k_lens_gather_bins(Parts<T> p, SortBufs sb, Geo g,
+                                                         LensArgs<T> la, MapAdd<T> mean, T* kappa,
+                                                         LensBins<T> bn) {
+    lens_gather_body<T, LG, EXT, DEC, true>(p, sb, g, la, mean, kappa, bn);
 }
 template <class T, int LG>
 __global__ __launch_bounds__(LG) void k_lens_gather_b(const LensGatherArgs<T>* __restrict__ tab) {
     const LensGatherArgs<T>& a = tab[blockIdx.y];
     if (!a.on) return;
-    lens_gather_body<T, LG, false, false>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
+    if (a.bins.on)
+        lens_gather_body<T, LG, false, false, true>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
+    else
+        lens_gather_body<T, LG, false, false, false>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
 }
 
 // ---------------------------------------------------------------------------
@@ -936,21 +945,33 @@ __global__ __launch_bounds__(1024) void k_lens_place_b(const LensGatherArgs<T>* 
 // LDS bytes after the accumulator for the D(a(chi)) window of sub-evolution
 constexpr size_t DWIN_BYTES = 16384;
 
+// Raises a kernel's dynamic LDS limit above the default.
+template <class K> static void raise_lds(K* kernel) {
+    constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+}
+
 template <class T, int LG, bool EXT, bool DEC>
 static void launch_lens_gather_k(Parts<T> p, SortBufs sb, Geo g, const LensArgs<T>& la,
                                  const MapAdd<T>& mean, T* kappa, size_t lds, hipStream_t st,
                                  const LensBins<T>& bn) {
-    constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
-    // above the default dynamic LDS limit: raised once per instantiation
-    static bool raised = false;
-    if (!raised) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lens_gather<T, LG, EXT, DEC>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
-        raised = true;
-    }
     const int nreg = (la.npix + la.rs - 1) / la.rs;
-    hipLaunchKernelGGL((k_lens_gather<T, LG, EXT, DEC>), dim3(nreg * nreg), dim3(LG), lds, st, p,
-                       sb, g, la, mean, kappa, bn);
+    const dim3 grid(nreg * nreg);
+    // (raised once per instantiation)
+    if (bn.on) {
+        if constexpr (LG <= 512) {
+            static const bool raised = (raise_lds(&k_lens_gather_bins<T, LG, EXT, DEC>), true);
+            (void)raised;
+            hipLaunchKernelGGL((k_lens_gather_bins<T, LG, EXT, DEC>), grid, dim3(LG), lds, st, p, sb,
+                               g, la, mean, kappa, bn);
+        }
+    } else if constexpr (LG != 512) {
+        static const bool raised = (raise_lds(&k_lens_gather<T, LG, EXT, DEC>), true);
+        (void)raised;
+        hipLaunchKernelGGL((k_lens_gather<T, LG, EXT, DEC>), grid, dim3(LG), lds, st, p, sb, g, la,
+                           mean, kappa);
+    }
 }
 
 template <class T, bool EXT>
@@ -962,7 +983,7 @@ void launch_lens_gather_t(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
                  (bn.on ? 0 : lens_queue_bytes<T>(lg));
     constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
     la.dwin = 0;
-    if (EXT && la.sub && lds < LDS_MAX) {
+    if (EXT && !bn.on && la.sub && lds < LDS_MAX) {
         // as much of DWIN_BYTES as the accumulator and the queues leave
         const size_t w = std::min(DWIN_BYTES, LDS_MAX - lds) / (2 * sizeof(T));
         la.dwin = (int)w;
