@@ -133,55 +133,33 @@ template <> struct LensAcc<double> {
     static __device__ __forceinline__ double dec_d(S v) { return v; }
 };
 
-// The four corners of an image's bilinear splat: their weights (0 for a
-// corner outside the region or the map) and their place in the region's
-// accumulator and in a map.  Shared by the image's sources.
-template <class T> struct Corners {
-    T w[4];
-    int at[4];       // accumulator index of a corner; -1: not this region's
-    int row, col;    // of the low corner, map pixels
-};
+// The bilinear splat of weight w at pixel coordinates (t0, t1) into the
+// region's accumulator, a corner weight at or above the fixed-point limit
+// (or every corner, global_only) going to the map kmap with a float atomic.
+// Corner by corner with early exits: the corners' weights and places worked
+// out together, once for all sources, took the walk from 0.36 to 0.375 ms (64
+// regions, one source, 64^3 particles).
 template <class T>
-__device__ __forceinline__ Corners<T> corners(int rs, int p0x, int p0y, int npix, T t0, T t1) {
-#pragma clang fp contract(off)
-    Corners<T> k;
-    const T fl0 = floor(t0), fl1 = floor(t1);
-    k.row = (int)fl0;
-    k.col = (int)fl1;
-    const T f0 = t0 - fl0, f1 = t1 - fl1;
-    const T wa[2] = {T(1) - f0, f0}, wb[2] = {T(1) - f1, f1};
-    const int r = k.row - p0x, c = k.col - p0y;
-    const bool ra[2] = {(unsigned)r < (unsigned)rs && k.row < npix,
-                        (unsigned)(r + 1) < (unsigned)rs && k.row + 1 < npix};
-    const bool cb[2] = {(unsigned)c < (unsigned)rs && k.col < npix,
-                        (unsigned)(c + 1) < (unsigned)rs && k.col + 1 < npix};
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int a = q >> 1, b = q & 1;
-        k.at[q] = ra[a] && cb[b] ? (r + a) * rs + c + b : -1;
-        k.w[q] = wa[a] * wb[b];
-    }
-    return k;
-}
-
-// Weight w over an image's corners into an accumulator, a corner at or
-// above the fixed-point limit (or every corner, global_only) going to the
-// map kmap with a float atomic.
-template <class T>
-__device__ __forceinline__ void splat_region(typename LensAcc<T>::S* acc, const Corners<T>& k,
-                                             int npix, T* kmap, T w, bool global_only = false) {
+__device__ __forceinline__ void splat_region(typename LensAcc<T>::S* acc, int rs, int p0x, int p0y,
+                                             int npix, T* kmap, T t0, T t1, T w,
+                                             bool global_only = false) {
 #pragma clang fp contract(off)
     using A = LensAcc<T>;
+    const T fl0 = floor(t0), fl1 = floor(t1);
+    const int j0 = (int)fl0, j1 = (int)fl1;
+    const T f0 = t0 - fl0, f1 = t1 - fl1;
+    const T wa[2] = {T(1) - f0, f0}, wb[2] = {T(1) - f1, f1};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const T v = w * k.w[q];
-        if (k.at[q] >= 0 && !global_only && v < T(A::LIM)) atomicAdd(&acc[k.at[q]], A::enc(v));
-    }
-    if (global_only || !(w < T(A::LIM))) {  // rare
-        for (int q = 0; q < 4; ++q) {
-            const T v = w * k.w[q];
-            if (k.at[q] >= 0 && (global_only || !(v < T(A::LIM))))
-                unsafeAtomicAdd(&kmap[(long)(k.row + (q >> 1)) * npix + k.col + (q & 1)], v);
+    for (int a = 0; a < 2; ++a) {
+        const int r = j0 + a;
+        if (r < p0x || r >= p0x + rs || r >= npix) continue;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int c = j1 + b;
+            if (c < p0y || c >= p0y + rs || c >= npix) continue;
+            const T v = w * (wa[a] * wb[b]);
+            if (!global_only && v < T(A::LIM)) atomicAdd(&acc[(r - p0x) * rs + (c - p0y)], A::enc(v));
+            else unsafeAtomicAdd(&kmap[(long)r * npix + c], v);
         }
     }
 }
@@ -407,35 +385,35 @@ __device__ __forceinline__ void lens_gather_body(const Parts<T>& p, const SortBu
     auto deposit = [&](T t0, T t1, T chi) {
 #pragma clang fp contract(off)
         T base_w = la.wbase / (chi * a_of_chi(la, chi));
-        const Corners<T> k = corners<T>(rs, p0x, p0y, la.npix, t0, t1);
         if constexpr (!DEC) {
             for (int s = 0; s < la.nsrc; ++s) {
                 T cs = la.chi_src[s];
                 if (chi < cs)
-                    splat_region<T>(acc + s * rs2, k, la.npix, kappa + (long)s * npix2,
-                                    base_w * (cs - chi) / cs);
+                    splat_region<T>(acc + s * rs2, rs, p0x, p0y, la.npix, kappa + (long)s * npix2,
+                                    t0, t1, base_w * (cs - chi) / cs);
             }
             return;
         }
         if (base_w < T(0.5) * T(A::LIM)) {
             // every corner weight is below the limit: the map argument is
             // never written
-            splat_region<T>(acc, k, la.npix, kappa, base_w);
-            splat_region<T>(acc + rs2, k, la.npix, kappa, base_w * chi * la.inv_chi_ref);
+            splat_region<T>(acc, rs, p0x, p0y, la.npix, kappa, t0, t1, base_w);
+            splat_region<T>(acc + rs2, rs, p0x, p0y, la.npix, kappa, t0, t1,
+                            base_w * chi * la.inv_chi_ref);
         } else {
             for (int s = 0; s < la.nsrc; ++s) {
                 if (la.slot[s] != -1) continue;
                 T cs = la.chi_src[s];
-                splat_region<T>(acc, k, la.npix, kappa + (long)s * npix2, base_w * (cs - chi) / cs,
-                                true);
+                splat_region<T>(acc, rs, p0x, p0y, la.npix, kappa + (long)s * npix2, t0, t1,
+                                base_w * (cs - chi) / cs, true);
             }
         }
         for (int d = 0; d < la.ndirect; ++d) {
             const int s = la.direct_src[d];
             T cs = la.chi_src[s];
             if (chi < cs)
-                splat_region<T>(acc + (2 + d) * rs2, k, la.npix, kappa + (long)s * npix2,
-                                base_w * (cs - chi) / cs);
+                splat_region<T>(acc + (2 + d) * rs2, rs, p0x, p0y, la.npix,
+                                kappa + (long)s * npix2, t0, t1, base_w * (cs - chi) / cs);
         }
     };
     // float: a wave's accepted images wait in its own LDS queue (after the
