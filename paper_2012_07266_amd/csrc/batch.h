@@ -121,8 +121,8 @@ template <class T>
 void launch_paint_batch(const PaintArgs<T>* tab, const Geo& g, int slots, hipStream_t st);
 template <class T> void prepare_lens_gather_batch();
 template <class T>
-void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape,
-                              bool bins, int slots, hipStream_t st);
+void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape, bool bins,
+                              int side_bins, bool walk, int side_walk, int slots, hipStream_t st);
 template <class T>
 void launch_readout_batch(const ReadoutArgs<T>* tab, const Geo& g, int slots, hipStream_t st);
 template <class T>

@@ -968,6 +968,21 @@ template <class T> struct Sim final : SimBase {
         return 8;
     }
 
+    // Region side of a batch's walked shells (slots of them side by side):
+    // a walk's own, or smaller where that leaves CUs without a workgroup.
+    // Smaller regions visit the same tile columns, 16 cells wide, more often:
+    // eight 64^3/128^3 slots, 512^2 maps of 3.5 degrees, sides 64 and 16 5.2
+    // and 6.4 ms for four steps; but six 48^3/96^3 slots with 91^2 maps, 9
+    // regions each at side 32, 24 ms, and 5 ms at side 8.
+    static int batch_walk_side(int ns, int np_, int slots) {
+        int rs = region_side(ns, np_);
+        for (; rs > 8; rs /= 2) {
+            const long n = (np_ + rs - 1) / rs;
+            if (n * n * slots >= 256) break;
+        }
+        return rs;
+    }
+
     // The counters of the image bins, at the end of fbc, and where they begin
     // in the arena; false when a map of this size leaves no room for them.
     bool bin_counters(LensBins<T>& b, size_t& at) const {
@@ -1799,7 +1814,9 @@ template <class T> struct Sim final : SimBase {
     // next step's end, whose first half-kick and drift the readout applies;
     // a2 <= 0: the last step), and the host's bookkeeping of the sort's
     // buffer swap.  kappa NULL: no projection.
-    void batch_step_args(double a0, double a1, double a2, T* kappa, BatchSlotArgs<T>& o) {
+    // side_walk: the region side of shells that are not binned.
+    void batch_step_args(double a0, double a1, double a2, T* kappa, int side_walk,
+                         BatchSlotArgs<T>& o) {
         const int nm = P.nm;
         o.scan = ScanArgs{sb.count, sb.start, scan_sum, ntiles, 1};
         o.scatter = ScatterArgs<T>{cur, alt, sb, geo, 1};
@@ -1811,11 +1828,11 @@ template <class T> struct Sim final : SimBase {
         if (const Shell sh = kappa ? shell_of(a0, a1) : Shell(); sh.on) {
             o.lens.la = sh.la;
             o.lens.mean = sh.mv;
-            // the batch's grid has one region side for every shell: one
+            // a batch's grids have one region side for every shell: one
             // accumulator per source
             o.lens.la.dec = 0;
             o.lens.bins = lens_bins(o.lens.la, true);  // before the paint
-            o.lens.la.rs = bin_side(npix);
+            o.lens.la.rs = o.lens.bins.on ? bin_side(npix) : side_walk;
             o.lens.p = cur;
             o.lens.sb = sb;
             o.lens.g = geo;
@@ -1885,9 +1902,11 @@ namespace {
 // The device parameter block holds one array of argument structs per pass
 // (capacity entries; three per slot for the c2r pass).  A step fills a
 // pinned host copy, copies it to the device on the batch's stream and
-// replays the launches (a HIP graph of kernel nodes only, captured at the
-// first step, or the launches themselves), so nothing in the launches
-// changes from step to step.
+// replays the launches (a HIP graph of kernel nodes only, or the launches
+// themselves).  The launches of a step are the same whatever the slots hold,
+// except the lens's: those for binned shells and the one for walked shells
+// are there when a slot needs them, so there are four graphs, each captured
+// at the first step that needs it.
 struct BatchBase {
     virtual ~BatchBase() {}
     virtual int attach(pm_sim* sim, const double* a_grid, int nsteps, int* slot_out) = 0;
@@ -1904,6 +1923,7 @@ template <class T> struct Batch final : BatchBase {
     bool own_stream = false;
     Geo geo{};
     LensArgs<T> lshape{};
+    int side_walk = 0;
     struct Slot {
         pm_sim* h = nullptr;
         Sim<T>* sim = nullptr;
@@ -1920,13 +1940,15 @@ template <class T> struct Batch final : BatchBase {
     hipEvent_t copied[2] = {nullptr, nullptr};
     hipEvent_t handoff = nullptr;  // orders a handle's stream with the batch's
     int ring = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    hipGraph_t graph[4] = {};  // [binned shells | walked shells << 1]
+    hipGraphExec_t exec[4] = {};
 
     ~Batch() override {
         if (st) (void)hipStreamSynchronize(st);
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
+        for (int i = 0; i < 4; ++i) {
+            if (exec[i]) (void)hipGraphExecDestroy(exec[i]);
+            if (graph[i]) (void)hipGraphDestroy(graph[i]);
+        }
         for (int i = 0; i < 2; ++i) {
             if (copied[i]) (void)hipEventDestroy(copied[i]);
             if (host[i]) (void)hipHostFree(host[i]);
@@ -1952,7 +1974,7 @@ template <class T> struct Batch final : BatchBase {
         geo.px = plane_values(p->nm);
         lshape.npix = npix;
         lshape.nsrc = nsrc;
-        lshape.rs = Sim<T>::bin_side(npix);
+        side_walk = Sim<T>::batch_walk_side(nsrc, npix, cap);
         slots.resize(cap);
         size_t b = 0;
         auto take = [&](size_t n) {
@@ -2057,13 +2079,14 @@ template <class T> struct Batch final : BatchBase {
 
     template <class A> A* arr(char* base, size_t off) { return reinterpret_cast<A*>(base + off); }
 
-    void launch_all(char* base) {
+    void launch_all(char* base, int lens) {
         const int nm = shape.nm;
         const int ntiles = geo.nt * geo.nt * geo.ncb;
         launch_scan_batch(arr<ScanArgs>(base, o_scan), ntiles, cap, st);
         launch_scatter_batch<T>(arr<ScatterArgs<T>>(base, o_scatter), geo, cap, st);
         // before the paint: the image bins use the meshes
-        launch_lens_gather_batch<T>(arr<LensGatherArgs<T>>(base, o_lens), lshape, true, cap, st);
+        launch_lens_gather_batch<T>(arr<LensGatherArgs<T>>(base, o_lens), lshape, lens & 1,
+                                    Sim<T>::bin_side(npix), lens & 2, side_walk, cap, st);
         launch_paint_batch<T>(arr<PaintArgs<T>>(base, o_paint), geo, cap, st);
         fft_r2c_rows_batch<T>(nm, arr<R2cArgs<T>>(base, o_r2c), cap, st);
         fft_c2c_axis1_batch<T>(nm, 1, arr<C2cArgs<T>>(base, o_fwd), cap, st);
@@ -2078,7 +2101,7 @@ template <class T> struct Batch final : BatchBase {
         char* h = host[ring];
         HIPCHK(hipEventSynchronize(copied[ring]));  // its last copy has been read
         std::memset(h, 0, bytes);  // every pass of an idle slot: on = 0
-        int running = 0;
+        int running = 0, lens = 0;
         for (int k = 0; k < cap; ++k) {
             Slot& s = slots[k];
             const int n = (int)s.agrid.size() - 1;
@@ -2086,7 +2109,8 @@ template <class T> struct Batch final : BatchBase {
             const int i = s.next;
             BatchSlotArgs<T> a;
             s.sim->batch_step_args(s.agrid[i], s.agrid[i + 1], i + 1 < n ? s.agrid[i + 2] : -1.0,
-                                   s.kappa, a);
+                                   s.kappa, side_walk, a);
+            if (a.lens.on) lens |= a.lens.bins.on ? 1 : 2;
             arr<ScanArgs>(h, o_scan)[k] = a.scan;
             arr<ScatterArgs<T>>(h, o_scatter)[k] = a.scatter;
             arr<PaintArgs<T>>(h, o_paint)[k] = a.paint;
@@ -2106,20 +2130,20 @@ template <class T> struct Batch final : BatchBase {
         HIPCHK(hipEventRecord(copied[ring], st));
         ring ^= 1;
         if (!use_graph) {
-            launch_all(dev);
+            launch_all(dev, lens);
             return hipGetLastError() == hipSuccess ? PM_OK : PM_EDEVICE;
         }
-        if (!exec) {
+        if (!exec[lens]) {
             HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-            launch_all(dev);
-            hipError_t e = hipStreamEndCapture(st, &graph);
-            if (e != hipSuccess || !graph) {
+            launch_all(dev, lens);
+            hipError_t e = hipStreamEndCapture(st, &graph[lens]);
+            if (e != hipSuccess || !graph[lens]) {
                 (void)hipGetLastError();
                 return PM_EDEVICE;
             }
-            HIPCHK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+            HIPCHK(hipGraphInstantiate(&exec[lens], graph[lens], nullptr, nullptr, 0));
         }
-        HIPCHK(hipGraphLaunch(exec, st));
+        HIPCHK(hipGraphLaunch(exec[lens], st));
         return PM_OK;
     }
 };

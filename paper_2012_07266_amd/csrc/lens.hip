@@ -645,14 +645,11 @@ __global__ __launch_bounds__(LG) void k_lens_gather_bins(Parts<T> p, SortBufs sb
                                                          LensBins<T> bn) {
     lens_gather_body<T, LG, EXT, DEC, true>(p, sb, g, la, mean, kappa, bn);
 }
-template <class T, int LG>
+template <class T, int LG, bool BIN>
 __global__ __launch_bounds__(LG) void k_lens_gather_b(const LensGatherArgs<T>* __restrict__ tab) {
     const LensGatherArgs<T>& a = tab[blockIdx.y];
-    if (!a.on) return;
-    if (a.bins.on)
-        lens_gather_body<T, LG, false, false, true>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
-    else
-        lens_gather_body<T, LG, false, false, false>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
+    if (!a.on || (a.bins.on != 0) != BIN) return;
+    lens_gather_body<T, LG, false, false, BIN>(a.p, a.sb, a.g, a.la, a.mean, a.kappa, a.bins);
 }
 
 // ---------------------------------------------------------------------------
@@ -985,30 +982,47 @@ void launch_lens_gather_t(Parts<T> p, SortBufs sb, Geo g, LensArgs<T> la,
     }
 }
 
-// The plain projection over the slots of a batch (one shape: the map size,
-// source count and region side of `shape` are every slot's).
+// The plain projection over the slots of a batch (one shape: the map size and
+// source count of `shape` are every slot's): `bins`, the slots whose images
+// are binned, with the region side `side_bins`; `walk`, the others, with
+// `side_walk`.
 // Raises the batched kernels' dynamic LDS limit (before any capture).
 template <class T>
 void prepare_lens_gather_batch() {
-    constexpr size_t LDS_MAX = 163840;  // per workgroup on gfx950
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_lens_gather_b<T, 256>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
+    raise_lds(&k_lens_gather_b<T, 256, true>);
+    raise_lds(&k_lens_gather_b<T, 256, false>);
+    raise_lds(&k_lens_gather_b<T, 1024, false>);
 }
 
 template <class T>
-void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape,
-                              bool bins, int slots, hipStream_t st) {
-    const int nreg = (shape.npix + shape.rs - 1) / shape.rs;
+void launch_lens_gather_batch(const LensGatherArgs<T>* tab, const LensArgs<T>& shape, bool bins,
+                              int side_bins, bool walk, int side_walk, int slots, hipStream_t st) {
+    const auto regions = [&](int rs) {
+        const int n = (shape.npix + rs - 1) / rs;
+        return n * n;
+    };
+    const auto lds = [&](int rs) {
+        return (size_t)shape.nsrc * rs * rs * sizeof(typename LensAcc<T>::S);
+    };
     if (bins) {
         const dim3 grid(std::max(LBG / slots, 64), slots);
+        const int nreg2 = regions(side_bins);
         hipLaunchKernelGGL((k_lens_bin_b<T, false>), grid, dim3(LBT), 0, st, tab);
-        hipLaunchKernelGGL((k_lens_place_b<T>), dim3((nreg * nreg + 1023) / 1024, slots), dim3(1024),
-                           0, st, tab);
+        hipLaunchKernelGGL((k_lens_place_b<T>), dim3((nreg2 + 1023) / 1024, slots), dim3(1024), 0,
+                           st, tab);
         hipLaunchKernelGGL((k_lens_bin_b<T, true>), grid, dim3(LBT), 0, st, tab);
+        hipLaunchKernelGGL((k_lens_gather_b<T, 256, true>), dim3(nreg2, slots), dim3(256),
+                           lds(side_bins), st, tab);
     }
-    const size_t lds = (size_t)shape.nsrc * shape.rs * shape.rs * sizeof(typename LensAcc<T>::S) +
-                       lens_queue_bytes<T>(256);
-    hipLaunchKernelGGL((k_lens_gather_b<T, 256>), dim3(nreg * nreg, slots), dim3(256), lds, st, tab);
+    if (walk) {
+        const dim3 grid(regions(side_walk), slots);
+        if (side_walk >= 64)
+            hipLaunchKernelGGL((k_lens_gather_b<T, 1024, false>), grid, dim3(1024),
+                               lds(side_walk) + lens_queue_bytes<T>(1024), st, tab);
+        else
+            hipLaunchKernelGGL((k_lens_gather_b<T, 256, false>), grid, dim3(256),
+                               lds(side_walk) + lens_queue_bytes<T>(256), st, tab);
+    }
 }
 
 // The plain projection is its own instantiation, free of the per-particle
@@ -1093,10 +1107,10 @@ template void launch_lens_gather<double>(Parts<double>, SortBufs, Geo, const Len
 template void prepare_lens_gather_batch<float>();
 template void prepare_lens_gather_batch<double>();
 template void launch_lens_gather_batch<float>(const LensGatherArgs<float>*,
-                                              const LensArgs<float>&, bool, int,
+                                              const LensArgs<float>&, bool, int, bool, int, int,
                                               hipStream_t);
 template void launch_lens_gather_batch<double>(const LensGatherArgs<double>*,
-                                               const LensArgs<double>&, bool, int,
+                                               const LensArgs<double>&, bool, int, bool, int, int,
                                                hipStream_t);
 
 }  // namespace ml

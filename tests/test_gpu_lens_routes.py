@@ -55,3 +55,57 @@ def test_shell_with_more_images_than_32_bits_count():
     worst = float(((full - want).abs() / want.abs()).max())
     log(f"largest relative difference {worst:.2e}")
     assert worst <= 1e-6
+
+
+@pytest.mark.parametrize("npix", [96, 512])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["f32", "f64"])
+def test_batched_shells_of_every_route_equal_each_run_alone(dtype, npix):
+    """Slots whose shells outgrow the bins (walked), fit them, and overflow
+    them (every particle on the line of sight), stepped together; 96 and 512
+    pixels are the smallest and the largest side of a walk's regions.  float32
+    maps are the same bits as each run's alone, float64 sums differ in their
+    order (some 10^4 additions a pixel)."""
+    from paper_2012_07266_amd.sim import Batch
+    # box, field of view, particles
+    slots = [(48.0, 8.0, "clustered"), (256.0, 1.0, "clustered"), (32.0, 0.2, "axis"),
+             (40.0, 6.0, "clustered")]
+    a = np.linspace(0.55, 0.8, 4)
+    log(f"batched routes {dtype} {npix}")
+    sims, maps, want = [], [], []
+    for i, (box, fov, kind) in enumerate(slots):
+        wl = W.Workload(f"s{i}", 16, 32, box, 0.1, 1.0, 4, npix, fov, (1.0,))
+        x = W.clustered_positions(16, 32, box, seed=61 + i)
+        if kind == "axis":
+            gen = np.random.Generator(np.random.Philox(key=62))
+            x[:2] = 0.5 * box + gen.normal(0.0, 0.02 * box / 16, size=x[:2].shape)
+        x = torch.from_numpy(x)
+        with new_sim(wl, dtype) as sim:
+            sim.set_state(x, torch.zeros_like(x), a[0])
+            k = sim.new_maps()
+            sim.steps(a, k)
+            sim.sync()
+            want.append((k.clone(), *(t.clone() for t in sim.get_state())))
+        sims.append(new_sim(wl, dtype))
+        sims[-1].set_state(x, torch.zeros_like(x), a[0])
+        maps.append(sims[-1].new_maps())
+    with Batch(sims[0], len(slots)) as b:
+        for sim, k in zip(sims[:3], maps):
+            b.attach(sim, a, k)
+        b.step()
+        b.attach(sims[3], a, maps[3])  # walks alone in its last step
+        while b.step():
+            pass
+        for sim in sims:
+            b.detach(sim)
+    for i, (sim, k, w) in enumerate(zip(sims, maps, want)):
+        x, p = sim.get_state()
+        sim.sync()
+        sim.close()
+        e = float((k - w[0]).abs().max() / w[0].abs().max())
+        log(f"slot {i}: largest difference over the largest value {e:.1e}")
+        assert float(w[0].abs().max()) > 0
+        if dtype == torch.float32:
+            assert torch.equal(k, w[0]) and torch.equal(x, w[1]) and torch.equal(p, w[2]), i
+        else:
+            assert e <= 1e-12, i
+            assert float((x - w[1]).abs().max()) <= 1e-10 * slots[i][0], i
