@@ -1056,6 +1056,32 @@ template <class T> struct Sim final : SimBase {
         return b;
     }
 
+    // A float64 shell in the fewest thinner shells of equal volume, up to 16,
+    // whose images fit the bins one after the other; empty where none do.
+    std::vector<LensArgs<T>> thin_shells(const LensArgs<T>& la, bool meshes) const {
+        std::vector<LensArgs<T>> part;
+        LensBins<T> b;
+        size_t at_cnt;
+        if (sizeof(T) != 8 || !bin_counters(b, at_cnt)) return part;
+        const double room = 0.8 * (double)((at_cnt - (meshes ? ap.mesh[0] : ap.xbc)) / (3 * sizeof(T)));
+        const double n3 = std::pow(la.cnear_d, 3), f3 = std::pow(la.cfar_d, 3);
+        for (int q = (int)std::min(17.0, std::max(2.0, std::floor(shell_images(la) / room))); q <= 16; ++q) {
+            part.assign(q, la);
+            bool fits = true;
+            for (int i = 0; i < q && fits; ++i) {
+                if (i > 0) part[i].cnear_d = std::cbrt(n3 + (f3 - n3) * i / q);
+                if (i + 1 < q) part[i].cfar_d = std::cbrt(n3 + (f3 - n3) * (i + 1) / q);
+                part[i].chi_near = (T)(part[i].cnear_d * cell);
+                part[i].chi_far = (T)(part[i].cfar_d * cell);
+                part[i].rs = bin_side(npix);
+                fits = lens_bins(part[i], meshes).on != 0;
+            }
+            if (fits) return part;
+        }
+        part.clear();
+        return part;
+    }
+
     // Born projection of sh, the shell (chi(a1), chi(a0)], of the current,
     // tile-sorted positions (which must be those at a1) into kappa.  With
     // sub-evolution the step's drift momentum is mom - sub_k2 * acc.
@@ -1102,30 +1128,13 @@ template <class T> struct Sim final : SimBase {
         // few workgroups for it: 0.7 ms against 0.2 at 64^3 particles and a
         // 256^2 map); in single precision its maps would depend on where the
         // scratch lies, through the rounding of the partial sums.
-        if constexpr (sizeof(T) == 8) {
-            for (int q = 2; q <= 16; ++q) {
-                std::vector<LensArgs<T>> part(q, la);
-                bool fits = true;
-                for (int i = 0; i < q && fits; ++i) {
-                    // cuts of equal volume
-                    const double n3 = std::pow(la.cnear_d, 3), f3 = std::pow(la.cfar_d, 3);
-                    if (i > 0) part[i].cnear_d = std::cbrt(n3 + (f3 - n3) * i / q);
-                    if (i + 1 < q) part[i].cfar_d = std::cbrt(n3 + (f3 - n3) * (i + 1) / q);
-                    part[i].chi_near = (T)(part[i].cnear_d * cell);
-                    part[i].chi_far = (T)(part[i].cfar_d * cell);
-                    part[i].rs = bin_side(npix);
-                    fits = lens_bins(part[i], meshes).on != 0;
-                }
-                if (!fits) continue;
-                for (int i = 0; i < q; ++i) {
-                    bn = lens_bins(part[i], meshes);
-                    clear_bins(bn, ls);
-                    launch_lens_gather<T>(cur, sb, geo, part[i], mv, kappa, ls, bn);
-                    mv = MapAdd<T>{};  // the mean term once
-                }
-                return PM_OK;
-            }
+        for (const LensArgs<T>& part : thin_shells(la, meshes)) {
+            bn = lens_bins(part, meshes);
+            clear_bins(bn, ls);
+            launch_lens_gather<T>(cur, sb, geo, part, mv, kappa, ls, bn);
+            mv = MapAdd<T>{};  // the mean term once
         }
+        if (bn.on) return PM_OK;
         launch_lens_gather<T>(cur, sb, geo, la, mv, kappa, ls, bn);
         return PM_OK;
     }
@@ -1134,11 +1143,12 @@ template <class T> struct Sim final : SimBase {
     bool shell_binned(const Shell& sh) const { return sh.on && lens_bins(sh.la, false, true).on; }
 
     // Whether the shell's images go to the meshes: they outgrow xbc and fbc,
-    // and fit with the meshes (or, in double precision, are cut to fit).
+    // and fit with the meshes (or, in double precision, are cut to fit; a
+    // shell that no cut fits is walked, which needs no scratch).
     bool shell_takes_meshes(const Shell& sh, bool beside = false) const {
         if (pgd || !sh.on) return false;
         if (lens_bins(sh.la, false, beside).on) return false;
-        return sizeof(T) == 8 || lens_bins(sh.la, true, beside).on;
+        return lens_bins(sh.la, true, beside).on || !thin_shells(sh.la, true).empty();
     }
 
     // nsteps KDK steps along agrid with the projection of every shell: the

@@ -109,3 +109,34 @@ def test_batched_shells_of_every_route_equal_each_run_alone(dtype, npix):
         else:
             assert e <= 1e-12, i
             assert float((x - w[1]).abs().max()) <= 1e-10 * slots[i][0], i
+
+
+# np, nm, box, npix, fov, z_src, a0, a1, dtype: shells that outgrow the bins'
+# own scratch by so much that no cut into thinner shells fits
+KEPT = {"no_cut_fits": (16, 32, 48.0, 64, 22.0, (1.0,), 0.52, 0.56, torch.float64)}
+
+
+@pytest.mark.parametrize("name", list(KEPT))
+def test_walked_shell_keeps_the_force_meshes(name):
+    """A projection that walks its shell uses no scratch, so a reverse step
+    after it finds the step's force meshes and paints no density."""
+    np_side, nm, box, npix, fov, zs, a0, a1, dtype = KEPT[name]
+    wl = W.Workload(name, np_side, nm, box, 0.1, 1.0, 4, npix, fov, zs)
+    x = torch.from_numpy(W.clustered_positions(np_side, nm, box, seed=71))
+    log(f"force meshes kept {name}")
+    with new_sim(wl, dtype) as sim:
+        sim.set_state(x, torch.zeros_like(x), a0)
+        sim.step(a0, a1)
+        k = sim.new_maps()
+        sim.lens(a0, a1, k)
+        x_bar = torch.zeros((3, sim.n_particles), dtype=dtype, device=sim.device)
+        p_bar = torch.ones_like(x_bar)
+        sim.sync()
+        sim.profile(True)
+        sim.step_vjp(a0, a1, -1.0, x_bar, p_bar, None)
+        launches = {n: c for n, (_, c) in sim.profile_read().items()}
+        sim.profile(False)
+        log(f"launches of the reverse step {launches}")
+        assert float(k.abs().max()) > 0 and float(x_bar.abs().max()) > 0
+        assert launches.get("vjp_readout") == 1
+        assert "paint" not in launches
