@@ -789,9 +789,10 @@ template <class T> struct Sim final : SimBase {
         // (the force meshes are recomputed where a reverse step needs them;
         // checkpoints that carry them need them at once)
         const Shell sh = shell_of(a0, a1);
-        const bool meshes = !ckpt_force() && shell_takes_meshes(sh);
-        int rc = project_shell(sh, a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0),
-                               nullptr, meshes);
+        const bool hidden = meshes_valid && sh.on && !lens_bins(sh.la, false).on;
+        const bool meshes = !ckpt_force() && shell_takes_meshes(sh, hidden);
+        int rc = project_shell(sh, a0, a1, reinterpret_cast<T*>(kappa), interp ? kdk_k2 : T(0), st,
+                               meshes, hidden);
         if (meshes) meshes_valid = false;
         return rc ? rc : check_launch();
     }
@@ -1016,30 +1017,52 @@ template <class T> struct Sim final : SimBase {
         return (double)geo.npart * vol / (P.box * P.box * P.box) * dup * dup;
     }
 
+    // The walk's cost of a shell, per image:
+    //   x = (1 + TILE / pencil)^2 rounds / regions,
+    // pencil being a region's width in cells half way through the shell (a
+    // walk visits whole tile columns, so wide pencils reject few images) and
+    // rounds the times that 256 CUs, a region each, have to be filled.  The
+    // bins' cost per image is about constant, so a walk is the better one for
+    // far shells on many regions.
+    double walk_cost(const LensArgs<T>& la) const {
+        const double pencil = la.rs * (fov * PI / 180.0 / npix) * 0.5 * (la.cnear_d + la.cfar_d);
+        const long side = (npix + la.rs - 1) / la.rs, regions = side * side;
+        return (1.0 + TILE / pencil) * (1.0 + TILE / pencil) * (double)((regions + 255) / 256) /
+               (double)regions;
+    }
+
+    // Whether a shell without options is better walked by regions, also where
+    // its images fit the bins.  Bins over walk (microseconds, regions of 64
+    // pixels), a shell by itself in float32: 192^3/384^3, a 1024^2 map of 5
+    // degrees, x = 0.0077, 0.0082, 0.0092, 0.011, 0.0122: 867/574, 627/474,
+    // 494/372, 294/278, 242/274; 256^3/512^3, four 2048^2 maps, x = 0.0139 and
+    // 0.0159: 504/502, 438/447.  `hidden`: beside the transform, where a walk
+    // is partly hidden, while images that outgrow xbc and fbc would be binned
+    // before the paint with nothing beside them (a step of 128^3/256^3, a
+    // 1024^2 map of 5 degrees, x = 0.0096, 0.0108, 0.0134, 0.0147: 1231/1101,
+    // 1147/1065, 1093/1023, 1075/1002), or where the bins would take force
+    // meshes that a reverse step needs.  In float64 both cost more, the bins
+    // twice as much where the shell has to be `cut` to fit: 128^3/256^3,
+    // x = 0.0090, 0.0099, 0.0108: 692/547, 463/457, 353/391; cut, 64^3/128^3, a
+    // 600^2 map of 7 degrees, x = 0.0155, 0.0165, 0.0180, 0.0193: 2036/1332,
+    // 1291/991, 770/687, 522/536.
+    bool walk_better(const LensArgs<T>& la, bool hidden, bool cut) const {
+        if (interp || pgd || rot) return false;
+        return walk_cost(la) < (sizeof(T) == 8 ? (cut ? 0.0185 : 0.010) : (hidden ? 0.0156 : 0.012));
+    }
+
     // The image bins of a shell whose images, at the mean density, fill at
     // most 4/5 of the scratch that is free: xbc and fbc, and with `meshes`
-    // (nothing in them yet) also the meshes and the halo before them in the
-    // arena.  Else `on` stays 0 and the shell is projected by regions alone.
-    // So it is with `beside` (the projection runs beside the transform, la.rs
-    // is the walk's region side) where the walk by regions is the better one:
-    // in float32 without options, with at least four regions per CU whose
-    // pencils are wider than a tile, so that it rejects few images.  Steps at
-    // 256^3/512^3, four 2048^2 maps, bins against walk: pencils of 23 to 29
-    // cells, whose images would take the meshes before the paint, 3.53 and
-    // 3.47 ms; 16 to 21 cells 3.70 and 3.70; narrower ones stay binned.
-    LensBins<T> lens_bins(const LensArgs<T>& la, bool meshes, bool beside = false) const {
+    // (nothing in them that is still needed) also the meshes and the halo
+    // before them in the arena.  Else `on` stays 0 and the shell is projected
+    // by regions alone.
+    LensBins<T> lens_bins(const LensArgs<T>& la, bool meshes) const {
         LensBins<T> b;
         size_t at_cnt;
         if (!bin_counters(b, at_cnt)) return b;
-        const int rs = bin_side(npix);
         const size_t at_ent = meshes ? ap.mesh[0] : ap.xbc;
         const size_t cap = (at_cnt - at_ent) / (3 * sizeof(T));
         if (!(shell_images(la) <= 0.8 * (double)cap)) return b;
-        if (sizeof(T) == 4 && beside && !interp && !pgd && !rot) {
-            const double pencil = la.rs * (fov * PI / 180.0 / npix) * 0.5 * (la.cnear_d + la.cfar_d);
-            const long side = (npix + la.rs - 1) / la.rs;
-            if (side * side >= 1024 && pencil > TILE) return b;
-        }
         const double chi_far = la.cfar_d * cell;
         const double half = half_map();
         // tiles per unit: one when replicas are rotated; else as many as
@@ -1057,12 +1080,13 @@ template <class T> struct Sim final : SimBase {
     }
 
     // A float64 shell in the fewest thinner shells of equal volume, up to 16,
-    // whose images fit the bins one after the other; empty where none do.
-    std::vector<LensArgs<T>> thin_shells(const LensArgs<T>& la, bool meshes) const {
+    // whose images fit the bins one after the other; empty where none do or a
+    // walk is better.
+    std::vector<LensArgs<T>> thin_shells(const LensArgs<T>& la, bool meshes, bool hidden) const {
         std::vector<LensArgs<T>> part;
         LensBins<T> b;
         size_t at_cnt;
-        if (sizeof(T) != 8 || !bin_counters(b, at_cnt)) return part;
+        if (sizeof(T) != 8 || walk_better(la, hidden, true) || !bin_counters(b, at_cnt)) return part;
         const double room = 0.8 * (double)((at_cnt - (meshes ? ap.mesh[0] : ap.xbc)) / (3 * sizeof(T)));
         const double n3 = std::pow(la.cnear_d, 3), f3 = std::pow(la.cfar_d, 3);
         for (int q = (int)std::min(17.0, std::max(2.0, std::floor(shell_images(la) / room))); q <= 16; ++q) {
@@ -1086,11 +1110,9 @@ template <class T> struct Sim final : SimBase {
     // tile-sorted positions (which must be those at a1) into kappa.  With
     // sub-evolution the step's drift momentum is mom - sub_k2 * acc.
     // With PGD on, pgd_shift must have run for the current state.  meshes: the
-    // meshes hold nothing yet and may be used as scratch.
-    int project_shell(const Shell& sh, double a0, double a1, T* kappa, T sub_k2 = T(0),
-                      hipStream_t ls = nullptr, bool meshes = false) {
-        const bool beside = ls != nullptr;
-        if (!ls) ls = st;
+    // meshes may be used as scratch; hidden: see walk_better.
+    int project_shell(const Shell& sh, double a0, double a1, T* kappa, T sub_k2, hipStream_t ls,
+                      bool meshes, bool hidden) {
         if (!sh.on) return PM_OK;
         LensArgs<T> la = sh.la;
         MapAdd<T> mv = sh.mv;
@@ -1116,7 +1138,8 @@ template <class T> struct Sim final : SimBase {
         }
         if (interp || pgd) plan_sources(la, cosmo.chi(a1), cosmo.chi(a0), false);
         ProfScope ps(prof, "lens_gather", ls);
-        LensBins<T> bn = lens_bins(la, meshes, beside);
+        LensBins<T> bn;
+        if (!walk_better(la, hidden, false)) bn = lens_bins(la, meshes);
         if (bn.on) {
             la.rs = bin_side(npix);
             clear_bins(bn, ls);
@@ -1124,11 +1147,11 @@ template <class T> struct Sim final : SimBase {
             return PM_OK;
         }
         // Too many images for the scratch.  In double precision the shell is
-        // then projected as a few thinner ones (the walk by regions has to
-        // few workgroups for it: 0.7 ms against 0.2 at 64^3 particles and a
-        // 256^2 map); in single precision its maps would depend on where the
+        // then projected as a few thinner ones where the walk by regions has
+        // too few workgroups for it (0.7 ms against 0.2 at 64^3 particles and
+        // a 256^2 map); in single precision its maps would depend on where the
         // scratch lies, through the rounding of the partial sums.
-        for (const LensArgs<T>& part : thin_shells(la, meshes)) {
+        for (const LensArgs<T>& part : thin_shells(la, meshes, hidden)) {
             bn = lens_bins(part, meshes);
             clear_bins(bn, ls);
             launch_lens_gather<T>(cur, sb, geo, part, mv, kappa, ls, bn);
@@ -1140,15 +1163,22 @@ template <class T> struct Sim final : SimBase {
     }
 
     // Whether the shell's images are binned in xbc and fbc beside the transform.
-    bool shell_binned(const Shell& sh) const { return sh.on && lens_bins(sh.la, false, true).on; }
+    bool shell_binned(const Shell& sh) const {
+        return sh.on && !walk_better(sh.la, true, false) && lens_bins(sh.la, false).on;
+    }
 
     // Whether the shell's images go to the meshes: they outgrow xbc and fbc,
-    // and fit with the meshes (or, in double precision, are cut to fit; a
-    // shell that no cut fits is walked, which needs no scratch).
-    bool shell_takes_meshes(const Shell& sh, bool beside = false) const {
-        if (pgd || !sh.on) return false;
-        if (lens_bins(sh.la, false, beside).on) return false;
-        return lens_bins(sh.la, true, beside).on || !thin_shells(sh.la, true).empty();
+    // and fit with the meshes (or, in double precision, are cut to fit).  A
+    // shell that is walked needs no scratch.  With options a walk costs more,
+    // but one hidden beside the transform is still better for the farthest
+    // shells (192^3/384^3 with rotated replicas, a 1024^2 map of 5 degrees, in
+    // the meshes before the paint against the walk, x = 0.0077: a step of 4.62
+    // and 4.07 ms; x = 0.0092: 3.96 and 3.85).
+    bool shell_takes_meshes(const Shell& sh, bool hidden) const {
+        if (pgd || !sh.on || walk_better(sh.la, hidden, false)) return false;
+        if (lens_bins(sh.la, false).on) return false;
+        if (sizeof(T) == 4 && hidden && (interp || rot) && walk_cost(sh.la) < 0.0115) return false;
+        return lens_bins(sh.la, true).on || !thin_shells(sh.la, true, hidden).empty();
     }
 
     // nsteps KDK steps along agrid with the projection of every shell: the
@@ -1180,12 +1210,13 @@ template <class T> struct Sim final : SimBase {
             if (pgd || !st_lens || early) {
                 int rc;
                 if (early) {
-                    if ((rc = project_shell(sh, a0, a1, kap, T(0), nullptr, true))) return rc;
+                    if ((rc = project_shell(sh, a0, a1, kap, T(0), st, true, st_lens != nullptr))) return rc;
                     paint(true);
                 } else {
                     if (pgd) pgd_shift(a1);
                     else paint(true);
-                    rc = project_shell(sh, a0, a1, kap, T(0));  // mom is the drift momentum here
+                    // (mom is the drift momentum here)
+                    rc = project_shell(sh, a0, a1, kap, T(0), st, false, false);
                     if (rc) return rc;
                 }
                 if (pgd) force_from_spectrum();
@@ -1207,7 +1238,7 @@ template <class T> struct Sim final : SimBase {
                         rc = PM_EDEVICE;
                         return;
                     }
-                    rc = project_shell(sh, a0, a1, kap, T(0), st_lens);
+                    rc = project_shell(sh, a0, a1, kap, T(0), st_lens, false, true);
                     if (hipEventRecord(ev_join, st_lens) != hipSuccess && !rc) rc = PM_EDEVICE;
                 };
                 const bool binned = shell_binned(sh);
@@ -1841,7 +1872,8 @@ template <class T> struct Sim final : SimBase {
             // a batch's grids have one region side for every shell: one
             // accumulator per source
             o.lens.la.dec = 0;
-            o.lens.bins = lens_bins(o.lens.la, true);  // before the paint
+            if (!walk_better(o.lens.la, false, false))
+                o.lens.bins = lens_bins(o.lens.la, true);  // before the paint
             o.lens.la.rs = o.lens.bins.on ? bin_side(npix) : side_walk;
             o.lens.p = cur;
             o.lens.sb = sb;

@@ -112,8 +112,10 @@ def test_batched_shells_of_every_route_equal_each_run_alone(dtype, npix):
 
 
 # np, nm, box, npix, fov, z_src, a0, a1, dtype: shells that outgrow the bins'
-# own scratch by so much that no cut into thinner shells fits
-KEPT = {"no_cut_fits": (16, 32, 48.0, 64, 22.0, (1.0,), 0.52, 0.56, torch.float64)}
+# own scratch by so much that no cut into thinner shells fits (float64), or
+# that are better walked (float32, pencils of 26 cells)
+KEPT = {"no_cut_fits": (16, 32, 48.0, 64, 22.0, (1.0,), 0.52, 0.56, torch.float64),
+        "wide_pencils": (64, 128, 42.0, 2048, 6.0, (1.5, 2.0), 0.45, 0.4509, torch.float32)}
 
 
 @pytest.mark.parametrize("name", list(KEPT))
