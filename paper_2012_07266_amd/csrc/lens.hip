@@ -865,8 +865,12 @@ __global__ __launch_bounds__(LBT) void k_lens_bin(Parts<T> p, SortBufs sb, Geo g
                                                   LensBins<T> bn) {
     lens_bin_body<T, EXT, FILL>(p, sb, g, la, bn);
 }
+// (six waves per SIMD asked for in float32, for which the filling pass would
+// take one register too many: eight slots of 64^3/128^3, four steps, 3.64 and
+// 3.63 ms)
 template <class T, bool FILL>
-__global__ __launch_bounds__(LBT) void k_lens_bin_b(const LensGatherArgs<T>* __restrict__ tab) {
+__global__ __launch_bounds__(LBT, (sizeof(T) == 4 ? 6 : 1)) void k_lens_bin_b(
+    const LensGatherArgs<T>* __restrict__ tab) {
     const LensGatherArgs<T>& a = tab[blockIdx.y];
     if (!a.on || !a.bins.on) return;
     lens_bin_body<T, false, FILL>(a.p, a.sb, a.g, a.la, a.bins);
