@@ -632,20 +632,16 @@ template <class T> struct Sim final : SimBase {
     }
 
     // The inverse passes from the fused axis-0 pass's spectra, component 0 in
-    // (m0, q0), the others in mesh 1 (to mesh 1 and 2).  between: called
-    // between the inverse and the dual axis-1 pass where they are launched
-    // apart, else before both.
-    void fft_inverse(int n, long px, T* m0, cx<T>* q0, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
-                     const std::function<void()>& between = nullptr) {
+    // (m0, q0), the others in mesh 1 (to mesh 1 and 2).
+    void fft_inverse(int n, long px, T* m0, cx<T>* q0, const cx<T>* tw, const cx<T>* twh,
+                     const cx<T>* twp) {
         cx<T>*c0 = reinterpret_cast<cx<T>*>(m0), *c1 = reinterpret_cast<cx<T>*>(mesh[1]),
              *c2 = reinterpret_cast<cx<T>*>(mesh[2]);
-        if (n < 512) {
-            if (between) between();
+        if (fft_inv_dual_merged(n)) {
             ProfScope ps(prof, "fft_c2c_axis1_inv_dual");
             fft_c2c_axis1_inv_dual<T>(n, px, c0, q0, c1, nyq[1], c2, nyq[2], tw, st);
         } else {
             { ProfScope ps(prof, "fft_c2c_axis1_inv"); fft_c2c_axis1<T>(n, px, -1, c0, q0, tw, st); }
-            if (between) between();
             // axis 1: n1 times mesh 1 in place, the plain transform into mesh 2
             ProfScope ps(prof, "fft_c2c_axis1_dual");
             fft_c2c_axis1_dual<T>(n, px, c1, nyq[1], c2, nyq[2], tw, st);
@@ -659,7 +655,7 @@ template <class T> struct Sim final : SimBase {
     void fft_forward_grad(int n, const T* G, const cx<T>* tw, const cx<T>* twh, const cx<T>* twp,
                           HaloMerge<T> hm = HaloMerge<T>(),
                           const std::function<void()>& after_fwd = nullptr,
-                          const std::function<void()>& after_inv = nullptr) {
+                          const std::function<void()>& after_grad = nullptr) {
         // Poisson: G(q) = 1 / (2 pi q Nm^2) computed in the kernel (G == NULL)
         const T gscale = (T)(1.0 / (2.0 * PI * (double)n * (double)n));
         // the particle lattice (G set) has its planes adjacent
@@ -672,7 +668,8 @@ template <class T> struct Sim final : SimBase {
         // axis 0: IFFT0(n0 h) -> mesh 0, IFFT0(h) -> mesh 1 (h = i G X)
         { ProfScope ps(prof, "fft_grad_axis0");
           fft_grad_axis0<T>(n, px, reinterpret_cast<cx<T>*>(mesh[0]), nyq[0], om, on, tw, G, gscale, st); }
-        fft_inverse(n, px, mesh[0], nyq[0], tw, twh, twp, after_inv);
+        if (after_grad) after_grad();
+        fft_inverse(n, px, mesh[0], nyq[0], tw, twh, twp);
     }
 
     // CIC density into mesh[0].  With defer_merge the paint boxes' shells are
@@ -1226,11 +1223,12 @@ template <class T> struct Sim final : SimBase {
                 // The shell's projection shares the GPU with the rest of the
                 // transform.  By regions alone it takes 1 ms at 256^3/512^3
                 // and starts after the forward axis-1 pass; with its images
-                // binned it takes 0.2 ms and costs the step least beside the
-                // dual pass (4 steps from a snapshot at 256^3/512^3, started
+                // binned it takes 0.2 ms and starts after the fused axis-0
+                // pass (four steps from a snapshot at 256^3/512^3, started
                 // after the forward pass, the fused axis-0 pass, the inverse
-                // pass or the dual pass: 17.57, 17.34, 17.41, 17.46 ms; at
-                // 192^3/384^3 8.18, 8.21, 8.14, 8.18 ms).
+                // axis-1 pass or the dual pass: 17.57, 17.34, 17.41, 17.46 ms;
+                // after the fused or the inverse pass at 512^3/1024^3 118.0
+                // and 118.4 ms, at 192^3/384^3 7.83 and 7.84 ms).
                 int rc = 0;
                 const auto shell = [&] {
                     if (hipEventRecord(ev_fork, st) != hipSuccess ||

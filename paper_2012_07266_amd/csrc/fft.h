@@ -53,8 +53,11 @@ void fft_c2c_axis1(int n, long px, int sign, cx<T>* main, cx<T>* nyq, const cx<T
 template <class T>
 void fft_c2c_axis1_dual(int n, long px, cx<T>* main, cx<T>* nyq, cx<T>* main2, cx<T>* nyq2, const cx<T>* tw,
                         hipStream_t st);
+// Whether the inverse and the dual pass of a mesh this size go in one launch
+// (fft_c2c_axis1_inv_dual); larger meshes fill the GPU with each of them.
+inline bool fft_inv_dual_merged(int n) { return n <= 256; }
 // fft_c2c_axis1 (inverse) on (main0, nyq0) and fft_c2c_axis1_dual on the
-// other two, in one launch below 512.
+// other two in one launch, for n of fft_inv_dual_merged.
 template <class T>
 void fft_c2c_axis1_inv_dual(int n, long px, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
                             cx<T>* nyq2, const cx<T>* tw, hipStream_t st);

@@ -1187,6 +1187,8 @@ static void div_axis0_n(PtrTriple in_main, PtrTriple in_nyq, cx<T>* out_main, cx
 // Supported lengths.  float: every mesh length; double: up to 256.
 #define ML_SIZES_F(X) X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024)
 #define ML_SIZES_D(X) X(16) X(32) X(48) X(64) X(96) X(128) X(192) X(256)
+// Those of fft_inv_dual_merged.
+#define ML_SIZES_MERGED(X) ML_SIZES_D(X)
 
 template <class T> bool fft_supported(int n) {
 #define ML_CASE(v) if (n == v) return true;
@@ -1249,17 +1251,13 @@ void fft_c2c_axis1_dual(int n, long px, cx<T>* main, cx<T>* nyq, cx<T>* main2, c
 #undef ML_CASE
 }
 
-// From 512 up each pass fills the GPU by itself and the two are launched
-// apart (a projection can then start between them).
 template <class T>
 void fft_c2c_axis1_inv_dual(int n, long px, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
                             cx<T>* nyq2, const cx<T>* tw, hipStream_t st) {
 #define ML_CASE(v) \
     if (n == v) return c2c_axis1_inv_dual_n<T, v>(main0, nyq0, main, nyq, main2, nyq2, tw, st, px);
-    ML_SIZES_D(ML_CASE)
+    ML_SIZES_MERGED(ML_CASE)
 #undef ML_CASE
-    fft_c2c_axis1<T>(n, px, -1, main0, nyq0, tw, st);
-    fft_c2c_axis1_dual<T>(n, px, main, nyq, main2, nyq2, tw, st);
 }
 
 template <class T>

@@ -142,3 +142,26 @@ def test_walked_shell_keeps_the_force_meshes(name):
         assert float(k.abs().max()) > 0 and float(x_bar.abs().max()) > 0
         assert launches.get("vjp_readout") == 1
         assert "paint" not in launches
+
+
+@pytest.mark.parametrize("shape", [(128, 256), (192, 384)], ids=["128p256m", "192p384m"])
+def test_inverse_and_dual_axis1_passes_are_named_as_launched(shape):
+    """Up to 256 the two passes are one launch, above they are two, and the
+    per-kernel times carry their names."""
+    np_side, nm = shape
+    wl = W.Workload("passes", np_side, nm, float(np_side), 0.1, 1.0, 4, 64, 2.0, (1.0,))
+    a = np.linspace(0.6, 0.7, 3)
+    x = torch.rand((3, np_side ** 3), generator=torch.Generator().manual_seed(9)) * wl.box
+    log(f"axis-1 passes {shape}")
+    with new_sim(wl, torch.float32) as sim:
+        sim.set_state(x, torch.zeros_like(x), a[0])
+        sim.sync()
+        sim.profile(True)
+        sim.steps(a, sim.new_maps())
+        launches = {n: c for n, (_, c) in sim.profile_read().items()}
+        sim.profile(False)
+    log(f"launches of two steps {launches}")
+    merged = {"fft_c2c_axis1_inv_dual": 2}
+    apart = {"fft_c2c_axis1_inv": 2, "fft_c2c_axis1_dual": 2}
+    for n, c in {**merged, **apart}.items():
+        assert launches.get(n, 0) == (c if n in (merged if nm <= 256 else apart) else 0)
