@@ -130,7 +130,7 @@ void fft_r2c_rows_batch(int n, const R2cArgs<T>* tab, int slots, hipStream_t st)
 template <class T>
 void fft_c2r_rows_batch(int n, const C2rArgs<T>* tab, int slots, hipStream_t st);
 template <class T>
-void fft_c2c_axis1_batch(int n, int sign, const C2cArgs<T>* tab, int slots, hipStream_t st);
+void fft_c2c_axis1_fwd_batch(int n, const C2cArgs<T>* tab, int slots, hipStream_t st);
 // the inverse pass of inv's slots and the dual pass of dual's
 template <class T>
 void fft_c2c_axis1_inv_dual_batch(int n, const C2cArgs<T>* inv, const DualArgs<T>* dual, int slots,

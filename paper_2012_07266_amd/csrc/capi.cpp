@@ -627,7 +627,7 @@ template <class T> struct Sim final : SimBase {
     void sort(T kick, T drift) {
         clear_count(st);
         { ProfScope ps(prof, "kick_drift_key");
-          launch_kick_drift_key<T>(cur, sb, geo, kick, drift, MODE_KICK | MODE_DRIFT, status, st); }
+          launch_kick_drift_key<T>(cur, sb, geo, kick, drift, status, st); }
         sort_move();
     }
 
@@ -1840,7 +1840,7 @@ template <class T> struct Sim final : SimBase {
         size_t at;
         if (bin_counters(bn, at)) clear_bins(bn, bst);
         launch_kick_drift_key<T>(cur, sb, geo, (T)cosmo.kick(a0, ah, a0),
-                                 (T)cosmo.drift(a0, a1, ah), MODE_KICK | MODE_DRIFT, status, bst);
+                                 (T)cosmo.drift(a0, a1, ah), status, bst);
         a_cur = -1.0;  // between steps until the batch leaves it at a step's end
         ic_fresh = false;
         tan_valid = false;
@@ -2129,7 +2129,7 @@ template <class T> struct Batch final : BatchBase {
                                     Sim<T>::bin_side(npix), lens & 2, side_walk, cap, st);
         launch_paint_batch<T>(arr<PaintArgs<T>>(base, o_paint), geo, cap, st);
         fft_r2c_rows_batch<T>(nm, arr<R2cArgs<T>>(base, o_r2c), cap, st);
-        fft_c2c_axis1_batch<T>(nm, 1, arr<C2cArgs<T>>(base, o_fwd), cap, st);
+        fft_c2c_axis1_fwd_batch<T>(nm, arr<C2cArgs<T>>(base, o_fwd), cap, st);
         fft_grad_axis0_batch<T>(nm, arr<GradArgs<T>>(base, o_grad), cap, st);
         fft_c2c_axis1_inv_dual_batch<T>(nm, arr<C2cArgs<T>>(base, o_inv),
                                         arr<DualArgs<T>>(base, o_dual), cap, st);

@@ -61,9 +61,6 @@ inline bool fft_inv_dual_merged(int n) { return n <= 256; }
 template <class T>
 void fft_c2c_axis1_inv_dual(int n, long px, cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* nyq, cx<T>* main2,
                             cx<T>* nyq2, const cx<T>* tw, hipStream_t st);
-// c2c along axis 0 on main and nyq.
-template <class T>
-void fft_c2c_axis0(int n, long px, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st);
 // Fused axis-0 pass: forward, h = i G(|n|^2) X, then inverse of n0 h (zero
 // where |n0| = n/2) into out[0] and inverse of h into out[1] (out[2] is not
 // used).  G(q) is the table G[q], or gscale / q when G is NULL (q > 0;

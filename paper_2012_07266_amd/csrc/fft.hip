@@ -567,13 +567,13 @@ __global__ __launch_bounds__(NT) void k_c2c_view(ViewDesc va, ViewDesc vb, const
     __shared__ cx<T> tws[N];
     c2c_view_body<T, N, W, S>(va, vb, tw, buf, tws);
 }
-template <class T, int N, int W, int S>
+template <class T, int N, int W>
 __global__ __launch_bounds__(NT) void k_c2c_view_b(const C2cArgs<T>* __restrict__ tab) {
     __shared__ cx<T> buf[N * (W + 1)];  // the pencils, and the twiddles
     __shared__ cx<T> tws[N];
     const C2cArgs<T> a = tab[blockIdx.y];
     if (!a.on) return;
-    c2c_view_body<T, N, W, S>(a.va, a.vb, a.tw, buf, tws);
+    c2c_view_body<T, N, W, 1>(a.va, a.vb, a.tw, buf, tws);
 }
 
 // ---------------------------------------------------------------------------
@@ -1149,14 +1149,6 @@ static void c2c_axis1_inv_dual_n(cx<T>* main0, cx<T>* nyq0, cx<T>* main, cx<T>* 
                        va, vb, main2, nyq2, tw);
 }
 
-template <class T, int N, int S>
-static void c2c_axis0_n(cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st, long px) {
-    constexpr int W = lanes_w<T>(N);
-    ViewDesc va{main, px / 2, 0, (int)((long)N * (N / 2) / W), 0};
-    ViewDesc vb{nyq, N, 0, N / W, 0};
-    ML_LAUNCH((k_c2c_view<T, N, W, S>), va.n_wg + vb.n_wg, st, va, vb, tw);
-}
-
 // The fused pass holds the spectrum and one component in registers; from 512
 // up it runs 512 threads per workgroup so that each thread holds half as
 // many values and the CU keeps four waves per SIMD.
@@ -1261,18 +1253,6 @@ void fft_c2c_axis1_inv_dual(int n, long px, cx<T>* main0, cx<T>* nyq0, cx<T>* ma
 }
 
 template <class T>
-void fft_c2c_axis0(int n, long px, int sign, cx<T>* main, cx<T>* nyq, const cx<T>* tw, hipStream_t st) {
-#define ML_CASE(v)                                                                  \
-    if (n == v) {                                                                   \
-        if (sign > 0) return c2c_axis0_n<T, v, 1>(main, nyq, tw, st, px);               \
-        return c2c_axis0_n<T, v, -1>(main, nyq, tw, st, px);                            \
-    }
-    if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
-    else { ML_SIZES_D(ML_CASE) }
-#undef ML_CASE
-}
-
-template <class T>
 void fft_grad_axis0(int n, long px, cx<T>* main_in, cx<T>* nyq_in, PtrTriple out_main, PtrTriple out_nyq,
                     const cx<T>* tw, const T* G, T gscale, hipStream_t st) {
 #define ML_CASE(v) if (n == v) return grad_axis0_n<T, v>(main_in, nyq_in, out_main, out_nyq, tw, G, gscale, st, px);
@@ -1342,11 +1322,11 @@ static void c2r_rows_batch_n(const C2rArgs<T>* tab, long nrows, int slots, hipSt
     constexpr int W = rows_w<T>(2 * H);
     hipLaunchKernelGGL((k_c2r_rows_b<T, H, W>), dim3(nrows / W, slots), dim3(NT), 0, st, tab);
 }
-template <class T, int N, int S>
-static void c2c_axis1_batch_n(const C2cArgs<T>* tab, int slots, hipStream_t st) {
+template <class T, int N>
+static void c2c_axis1_fwd_batch_n(const C2cArgs<T>* tab, int slots, hipStream_t st) {
     constexpr int W = lanes_w<T>(N);
     const int nwg = (int)((long)N * (N / 2) / W) + N / W;
-    hipLaunchKernelGGL((k_c2c_view_b<T, N, W, S>), dim3(nwg, slots), dim3(NT), 0, st, tab);
+    hipLaunchKernelGGL((k_c2c_view_b<T, N, W>), dim3(nwg, slots), dim3(NT), 0, st, tab);
 }
 template <class T, int N>
 static void c2c_axis1_inv_dual_batch_n(const C2cArgs<T>* inv, const DualArgs<T>* dual, int slots,
@@ -1382,12 +1362,8 @@ void fft_c2r_rows_batch(int n, const C2rArgs<T>* tab, int slots, hipStream_t st)
 }
 
 template <class T>
-void fft_c2c_axis1_batch(int n, int sign, const C2cArgs<T>* tab, int slots, hipStream_t st) {
-#define ML_CASE(v)                                                                  \
-    if (n == v) {                                                                   \
-        if (sign > 0) return c2c_axis1_batch_n<T, v, 1>(tab, slots, st);            \
-        return c2c_axis1_batch_n<T, v, -1>(tab, slots, st);                         \
-    }
+void fft_c2c_axis1_fwd_batch(int n, const C2cArgs<T>* tab, int slots, hipStream_t st) {
+#define ML_CASE(v) if (n == v) return c2c_axis1_fwd_batch_n<T, v>(tab, slots, st);
     if constexpr (sizeof(T) == 4) { ML_SIZES_F(ML_CASE) }
     else { ML_SIZES_D(ML_CASE) }
 #undef ML_CASE
@@ -1418,7 +1394,7 @@ void fft_grad_axis0_batch(int n, const GradArgs<T>* tab, int slots, hipStream_t 
                                                 const cx<T>*, const T*, T);                       \
     template void fft_r2c_rows_batch<T>(int, const R2cArgs<T>*, int, hipStream_t);                \
     template void fft_c2r_rows_batch<T>(int, const C2rArgs<T>*, int, hipStream_t);                \
-    template void fft_c2c_axis1_batch<T>(int, int, const C2cArgs<T>*, int, hipStream_t);          \
+    template void fft_c2c_axis1_fwd_batch<T>(int, const C2cArgs<T>*, int, hipStream_t);           \
     template void fft_c2c_axis1_inv_dual_batch<T>(int, const C2cArgs<T>*, const DualArgs<T>*, int, \
                                                   hipStream_t);                                   \
     template void fft_grad_axis0_batch<T>(int, const GradArgs<T>*, int, hipStream_t);
@@ -1440,7 +1416,6 @@ ML_INST_BATCH(double)
     template void fft_c2c_axis1<T>(int, long, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
     template void fft_c2c_axis1_dual<T>(int, long, cx<T>*, cx<T>*, cx<T>*, cx<T>*, const cx<T>*,          \
                                         hipStream_t);                                             \
-    template void fft_c2c_axis0<T>(int, long, int, cx<T>*, cx<T>*, const cx<T>*, hipStream_t);           \
     template void fft_grad_axis0<T>(int, long, cx<T>*, cx<T>*, PtrTriple, PtrTriple, const cx<T>*,        \
                                     const T*, T, hipStream_t);
 ML_INST(float)

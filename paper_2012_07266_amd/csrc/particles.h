@@ -63,8 +63,6 @@ struct SortBufs {
     uint32_t* start;  // [ntiles+1] exclusive prefix
 };
 
-enum { MODE_KICK = 1, MODE_DRIFT = 2 };
-
 // Particle ids pack the lattice coordinates (i0, i1, i2), each < 1024, as
 // i0 << 20 | i1 << 10 | i2.
 __device__ __forceinline__ uint32_t pack_id(int i0, int i1, int i2) {
@@ -104,11 +102,11 @@ struct CopyParts {
 };
 bool launch_copy_parts(const CopyParts& c, hipStream_t st);
 
-// mom += kick*acc (MODE_KICK), disp += drift*mom (MODE_DRIFT); then tile
-// key and histogram of every particle.  `count` must be zero.
+// mom += kick*acc, disp += drift*mom; then tile key and histogram of every
+// particle.  `count` must be zero.
 template <class T>
-void launch_kick_drift_key(Parts<T> p, SortBufs s, Geo g, T kick, T drift, int mode,
-                           uint32_t* status, hipStream_t st);
+void launch_kick_drift_key(Parts<T> p, SortBufs s, Geo g, T kick, T drift, uint32_t* status,
+                           hipStream_t st);
 // Exclusive prefix sum of count[0..n) into start[0..n], start[n] = total;
 // block_sum: scratch of (n + 1023) / 1024 entries (n <= 1024 * 1024).
 void launch_scan(const uint32_t* count, uint32_t* start, uint32_t* block_sum, int n,

@@ -193,7 +193,7 @@ __device__ __forceinline__ uint32_t wave_take_rank(const WaveGroup& w, uint32_t 
 
 template <class T>
 __global__ __launch_bounds__(PB) void k_kick_drift_key(Parts<T> p, SortBufs s, Geo g, T kick,
-                                                       T drift, int mode, uint32_t* status) {
+                                                       T drift, uint32_t* status) {
     const long n = g.npart;
     for (long base = blockIdx.x * (long)PB; base < n; base += (long)gridDim.x * PB) {
         long k = base + threadIdx.x;
@@ -206,13 +206,10 @@ __global__ __launch_bounds__(PB) void k_kick_drift_key(Parts<T> p, SortBufs s, G
                 d[a] = p.disp[a * n + k];
                 m[a] = p.mom[a * n + k];
             }
-            if (mode & MODE_KICK) {
 #pragma unroll
-                for (int a = 0; a < 3; ++a) m[a] += kick * p.acc[a * n + k];
-            }
-            if (mode & MODE_DRIFT) {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) d[a] += drift * m[a];
+            for (int a = 0; a < 3; ++a) {
+                m[a] += kick * p.acc[a * n + k];
+                d[a] += drift * m[a];
             }
             if (!finite3(d[0], d[1], d[2])) {
                 atomicOr(status, 1u);
@@ -221,7 +218,7 @@ __global__ __launch_bounds__(PB) void k_kick_drift_key(Parts<T> p, SortBufs s, G
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 p.disp[a * n + k] = d[a];
-                if (mode & MODE_KICK) p.mom[a * n + k] = m[a];
+                p.mom[a * n + k] = m[a];
             }
             key = tile_key<T>(p.id[k], d, g);
             s.key[k] = key;
@@ -231,12 +228,12 @@ __global__ __launch_bounds__(PB) void k_kick_drift_key(Parts<T> p, SortBufs s, G
 }
 
 template <class T>
-void launch_kick_drift_key(Parts<T> p, SortBufs s, Geo g, T kick, T drift, int mode,
-                           uint32_t* status, hipStream_t st) {
+void launch_kick_drift_key(Parts<T> p, SortBufs s, Geo g, T kick, T drift, uint32_t* status,
+                           hipStream_t st) {
     long blocks = (g.npart + PB - 1) / PB;
     if (blocks > 16384) blocks = 16384;
     hipLaunchKernelGGL(k_kick_drift_key<T>, dim3(blocks), dim3(PB), 0, st, p, s, g, kick, drift,
-                       mode, status);
+                       status);
 }
 
 // ---------------------------------------------------------------------------
@@ -1228,7 +1225,7 @@ ML_INST_BATCH(double)
 #define ML_INST(T)                                                                                \
     template void launch_fill<T>(T*, T, long, hipStream_t);                                       \
     template void launch_scale_copy<T>(T*, const T*, T, long, long, long, hipStream_t);           \
-    template void launch_kick_drift_key<T>(Parts<T>, SortBufs, Geo, T, T, int, uint32_t*,        \
+    template void launch_kick_drift_key<T>(Parts<T>, SortBufs, Geo, T, T, uint32_t*,             \
                                            hipStream_t);                                          \
     template void launch_scatter<T>(Parts<T>, Parts<T>, SortBufs, Geo, hipStream_t, TanCarry<T>); \
     template void launch_paint<T>(Parts<T>, SortBufs, Geo, T, T*, T*, hipStream_t, bool);         \
