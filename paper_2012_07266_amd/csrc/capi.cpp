@@ -1067,7 +1067,11 @@ template <class T> struct Sim final : SimBase {
         const double reach = half * chi_far / cell / TILE;
         const double tiles = 4.0 * (reach + 1.0) * (reach + 1.0) *
                              ((chi_far / cell - la.cnear_d) / TILE + 1.0);
-        if (tiles > 1e9) return b;
+        // the passes count their units in 32 bits; moved images widen the box
+        // of units by up to a simulation box for each option (lens_margin)
+        const double slack = 1.0 + geo.nt * ((interp ? 1 : 0) + (pgd ? 1 : 0));
+        const double wide = 2.0 * (reach + slack) + 2.0;
+        if (wide * wide * ((chi_far / cell - la.cnear_d) / TILE + 2.0 * slack + 2.0) > 1e9) return b;
         for (b.zt = rot ? 1 : 4; b.zt > 1; b.zt /= 2)
             if (geo.nt % b.zt == 0 && tiles / b.zt >= 4096) break;
         b.ent = reinterpret_cast<T*>(arena + at_ent);
