@@ -77,7 +77,11 @@ def algorithmic_bytes(wl, esize=4):
         "readout_kick": 3 * M + 52 * P,    # R 3 meshes, disp,id,mom  W mom,acc
         # fused with the next step's kick, drift and keys:
         "readout_kick_drift_key": 3 * M + 56 * P,  # R 3 meshes, disp,id,mom  W disp,mom,key
-        "lens_gather": 16 * P + 2 * maps,  # R disp,id  RW maps (incl. mean term)
+        # the whole projection (a binned shell: four kernels), the least that
+        # either route moves: R disp,id  RW maps (incl. mean term).  Bins read
+        # disp, id of the shell's tiles twice and write and read 12 bytes an
+        # image on top.
+        "lens_gather": 16 * P + 2 * maps,
         "scan": 0,
     }
 
@@ -113,7 +117,7 @@ KERNEL_SYMBOL = {
     "scan": ("k_scan_", "paper_2012_07266_amd/csrc/particles.hip"),
     "scatter": ("k_scatter<float", "paper_2012_07266_amd/csrc/particles.hip"),
     "paint": ("k_paint_group<float", "paper_2012_07266_amd/csrc/particles.hip"),
-    "lens_gather": ("k_lens_gather<float", "paper_2012_07266_amd/csrc/lens.hip"),
+    "lens_gather": ("k_lens_", "paper_2012_07266_amd/csrc/lens.hip"),  # bins, place and gather
     "fft_r2c_axis2": ("k_r2c_rows<float", "paper_2012_07266_amd/csrc/fft.hip"),
     "fft_c2c_axis1_fwd": ("k_c2c_view<float, 512, 16, 1>", "paper_2012_07266_amd/csrc/fft.hip"),
     "fft_grad_axis0": ("k_grad_x0<float", "paper_2012_07266_amd/csrc/fft.hip"),
@@ -169,7 +173,8 @@ def traffic_from_pmc(fetch_csv, write_csv, workload, step):
     for (name, f), (_, w) in zip(fetch, write):
         cls = next((c for c, (sub, _) in KERNEL_SYMBOL.items() if sub in name), name[:48])
         e = per.setdefault(cls, {"launches": 0, "fetch_bytes": 0.0, "write_bytes": 0.0})
-        e["launches"] += 1
+        # (a projection ends with its gather; the bins' passes belong to it)
+        e["launches"] += 0 if cls == "lens_gather" and "k_lens_gather" not in name else 1
         e["fetch_bytes"] += f * sf
         e["write_bytes"] += w * sw
     out = {"_about": ("HBM bytes of one steady-state pm_run step late in the schedule, from "

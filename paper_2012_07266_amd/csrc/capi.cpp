@@ -920,10 +920,12 @@ template <class T> struct Sim final : SimBase {
     // accumulators A and B, their maps A - ratio B with ratio = 1 / (cs
     // inv_chi_ref), inv_chi_ref being the factor the kernel applies in T,
     // and the sources in front of it then take no accumulator.  That is
-    // done when it lets the region grow against one accumulator per source
-    // (the region side follows from the accumulator count): at the same
+    // done when it lets a walk's region grow against one accumulator per
+    // source (the region side follows from the accumulator count): at the same
     // region side it measured slower.  A shell with no source beyond it
-    // keeps A and B unused.
+    // keeps A and B unused.  A binned shell has a region side of its own and
+    // follows the walk all the same: A - ratio B rounds differently from a
+    // sum of its own, and a shell's maps are the same bits by either route.
     void plan_sources(LensArgs<T>& la, double chi_near, double chi_far, bool fixed_bounds) const {
         int nbeyond = 0, nnone = 0;
         for (int s = 0; s < nsrc; ++s) {
