@@ -667,10 +667,12 @@ __global__ __launch_bounds__(LG) void k_lens_gather_b(const LensGatherArgs<T>* _
 // ends past the buffer is walked as before (clustering beyond what the host
 // allowed for); places are 64-bit until they are known to lie in the buffer,
 // since a crowded shell can have more than 2^32 images.
-// Measured (a late shell, walk by regions -> count + place + fill + gather):
-// 256^3/512^3, four 2048^2 maps 1.02 -> 0.041 + 0.005 + 0.065 + 0.096 ms;
-// 512^3/1024^3, ten 4096^2 maps 15.2 -> 0.056 + 0.005 + 0.086 + 0.66 ms;
-// float64 32^3/32^3, one 64^2 map 0.51 -> 0.019 + 0.004 + 0.028 + 0.006 ms.
+// Measured, count + place + fill + gather of a late shell (a walk by regions
+// took 1.02, 15.2 and 0.51 ms):
+// 256^3/512^3, four 2048^2 maps, a = 0.78 0.025 + 0.006 + 0.038 + 0.083 ms;
+// 512^3/1024^3, ten 4096^2 maps, a = 0.78 0.025 + 0.005 + 0.040 + 0.65 ms;
+// float64 32^3/32^3, one 64^2 map, a = 0.64 0.013 + 0.003 + 0.022 + 0.013 ms.
+// Far shells on many regions are still walked (the host's walk_better).
 // The counting and filling passes wait on memory (about 16 bytes an image
 // read twice, 12 written), the gather on LDS atomics and the maps' read and
 // write.

@@ -31,7 +31,9 @@ struct Geo {
 // Values from one axis-0 plane of a force mesh to the next.  At 1024 a plane
 // of nm^2 would put a pencil's rows 4 MB apart, on the same memory channels:
 // an in-place pass over axis 0 then runs at 2.8 TB/s, with 544 values (17
-// lines) between planes at 4.4 (5.2 at 512, where such a gap gains nothing).
+// lines) between planes at 4.4 (5.2 at 512 with and without).  A whole step
+// gains 2% at 1024.  At 768 (four steps of 384^3/768^3 61.1 -> 60.4 ms) and 512
+// (256^3/512^3 17.12 -> 16.97 ms) the same gap gains 1%; they have none.
 inline long plane_values(int nm) { return (long)nm * nm + (nm == 1024 ? 544 : 0); }
 
 // Cell origin of sort block b (KX x TILE x TILE cells).
